@@ -16,10 +16,11 @@
 // spectrum; the loss is the smooth maximum (1/kappa) log mean exp(kappa d).
 //
 // Kernels: features of a batch of dense matrices, forward pass, the
-// spectral loss with its gradient, backward pass (per-sample deltas, then one
-// thread per weight summing over the batch in a fixed order -- deterministic),
-// and Adam.  The sizes are tiny (about 9.7k parameters), so every contraction
-// runs on the vector ALUs.
+// spectral loss with its gradient, backward pass (per-sample deltas, then the
+// weight gradients summed over the batch in a fixed order -- deterministic),
+// and Adam.  The forward pass and the weight gradients are contractions over
+// the units and over the batch and run on the FP32 matrix cores; the
+// per-sample deltas are small matrix-vector products on the vector ALUs.
 #include <cmath>
 #include <mutex>
 
@@ -183,40 +184,83 @@ __global__ void __launch_bounds__(256) k_rh_features(int ld, const int* __restri
 }
 
 // ---------------------------------------------------------------------------
-// forward pass: 4 samples per 256-thread workgroup, one thread per unit;
-// act (optional) keeps a1, a2, a3 for the backward pass
+// forward pass: 16 samples per 256-thread workgroup on the FP32 matrix cores
+// (v_mfma_f32_16x16x4f32, FP32 accumulation); wave w finishes units
+// 16 w .. 16 w + 15 of a hidden layer, wave 0 the output layer.  Operand
+// layout: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16], accumulator
+// element i of lane l is D[4 (l / 16) + i][l % 16].  The products of a layer
+// of NV inputs are dealt so that lane group q = l / 16 takes the inputs
+// q NV/4 .. (q + 1) NV/4 - 1: a lane then reads contiguous runs of its weight
+// row (16-byte loads) and of its sample's activations.
+// Bound by latency (three layers, one weight read each): with one lane per
+// unit, as this kernel was before, every lane walked its own weight row in
+// 4-byte loads, 64 cache lines per load, and a layer took 64 of them; 12.7 us
+// for 2048 samples, now 8.3.
+// act (optional) keeps a1, a2, a3 for the backward pass.
+typedef float nk_f4 __attribute__((ext_vector_type(4)));
+constexpr int FS = 16;       // samples per workgroup
+constexpr int FLD = MH + 4;  // padded row of activations (16-byte aligned)
+
+// the pre-activations of the 16 samples (rows of in, leading dimension FLD)
+// and 16 units whose weight rows start at W (leading dimension NV); units past
+// nu read row 0 and are ignored by the caller
+template <int NV>
+__device__ __forceinline__ nk_f4 layer16(const float* __restrict__ W, int nu, const float* in, int lane) {
+  const int l16 = lane & 15, q = lane >> 4;
+  constexpr int NK = NV / 4;
+  const float* wr = W + (size_t)(l16 < nu ? l16 : 0) * NV + q * NK;
+  const float* ar = in + l16 * FLD + q * NK;
+  nk_f4 wv[NK / 4], av[NK / 4];
+#pragma unroll
+  for (int c = 0; c < NK / 4; ++c) {
+    // the flat parameter array gives no more than 4-byte alignment
+    wv[c] = nk_f4{wr[4 * c], wr[4 * c + 1], wr[4 * c + 2], wr[4 * c + 3]};
+    av[c] = *reinterpret_cast<const nk_f4*>(ar + 4 * c);
+  }
+  nk_f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < NK / 4; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c][e], wv[c][e], acc, 0, 0, 0);
+  return acc;
+}
+
 __global__ void __launch_bounds__(256) k_mlp_fwd(int B, const float* __restrict__ P, const float* __restrict__ feat,
                                                  float* __restrict__ y, float* __restrict__ act) {
-  __shared__ float sx[4][MI];
-  __shared__ float sa[4][2][MH];
-  const int sl = threadIdx.x >> 6, u = threadIdx.x & 63;
-  const int b = blockIdx.x * 4 + sl;
-  const bool live = b < B;
-  if (u < MI) sx[sl][u] = live ? (feat[(size_t)b * MI + u] - P[OMEAN + u]) * P[OISTD + u] : 0.f;
+  __shared__ __align__(16) float sx[FS][FLD];
+  __shared__ __align__(16) float sa[2][FS][FLD];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int b0 = blockIdx.x * FS;
+  {
+    const int sl = tid / MI, v = tid % MI;  // 16 samples x 16 features
+    const int b = b0 + sl;
+    sx[sl][v] = b < B ? (feat[(size_t)b * MI + v] - P[OMEAN + v]) * P[OISTD + v] : 0.f;
+  }
   __syncthreads();
-  float h = P[OB1 + u];
-  for (int v = 0; v < MI; ++v) h += P[OW1 + u * MI + v] * sx[sl][v];
-  float a = tanhf(h);
-  sa[sl][0][u] = a;
-  if (live && act) act[((size_t)b * 3 + 0) * MH + u] = a;
+  const int u = 16 * w + (lane & 15), r0 = 4 * (lane >> 4);
+  auto finish = [&](nk_f4 h, float bias, int layer, float (*out)[FLD]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float a = tanhf(h[i] + bias);
+      const int b = b0 + r0 + i;
+      out[r0 + i][u] = a;
+      if (act && b < B) act[((size_t)b * 3 + layer) * MH + u] = a;
+    }
+  };
+  finish(layer16<MI>(P + OW1 + 16 * w * MI, 16, &sx[0][0], lane), P[OB1 + u], 0, sa[0]);
   __syncthreads();
-  h = P[OB2 + u];
-  for (int v = 0; v < MH; ++v) h += P[OW2 + u * MH + v] * sa[sl][0][v];
-  a = tanhf(h);
-  sa[sl][1][u] = a;
-  if (live && act) act[((size_t)b * 3 + 1) * MH + u] = a;
+  finish(layer16<MH>(P + OW2 + 16 * w * MH, 16, &sa[0][0][0], lane), P[OB2 + u], 1, sa[1]);
   __syncthreads();
-  h = P[OB3 + u];
-  for (int v = 0; v < MH; ++v) h += P[OW3 + u * MH + v] * sa[sl][1][v];
-  a = tanhf(h);
+  finish(layer16<MH>(P + OW3 + 16 * w * MH, 16, &sa[1][0][0], lane), P[OB3 + u], 2, sa[0]);
   __syncthreads();
-  sa[sl][0][u] = a;
-  if (live && act) act[((size_t)b * 3 + 2) * MH + u] = a;
-  __syncthreads();
-  if (live && u < MT) {
-    float o = P[OB4 + u];
-    for (int v = 0; v < MH; ++v) o += P[OW4 + u * MH + v] * sa[sl][0][v];
-    y[(size_t)b * MT + u] = o;
+  if (w == 0) {
+    const nk_f4 o = layer16<MH>(P + OW4, MT, &sa[0][0][0], lane);
+    const int t = lane & 15;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int b = b0 + r0 + i;
+      if (t < MT && b < B) y[(size_t)b * MT + t] = o[i] + P[OB4 + t];
+    }
   }
 }
 
@@ -225,7 +269,16 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(int B, const float* __restrict_
 // gradient with respect to y, scaled by gscale; one workgroup per sample,
 // FP64 arithmetic.  Step t uses mu_t = exp(y_t - mean_i log|z_{i,t}|): the
 // determinant scale of the eigenvalues times the learned correction.
-constexpr int SPT = 4;  // eigenvalues per thread: at most 1024 per matrix
+// SPT eigenvalues per thread: 1 for spectra of up to 256, 4 up to 1024.  Each
+// launch of the pair takes the samples of its own class and returns at once on
+// the others (their sizes are on the device); slots and whole waves past a
+// sample's spectrum are branched over.  Bound by FP64 issue: the logarithm,
+// exponential and division of every step and eigenvalue.  So a step divides
+// once, and the backward sweep reuses its 1/w: 1/w^2 = (1/w)^2 and
+// z/|z|^2 = conj(1/z) = mu conj(1/w).  With four slots for every sample, each
+// of them computed, and two more divisions and an exponential per step, as
+// before, 2048 samples of 16 to 300 eigenvalues took 52.6 us; now 23 + 19
+// (7 and 2 workgroups per compute unit at 72 and 200 registers).
 
 // sum over the 256 threads of the workgroup, the same value in every thread
 __device__ __forceinline__ double block_sum256(double v, double* sh) {
@@ -237,46 +290,54 @@ __device__ __forceinline__ double block_sum256(double v, double* sh) {
   return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
+template <int SPT>
 __global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, const C64* __restrict__ lam,
                                                    const float* __restrict__ y, float gscale,
                                                    float* __restrict__ loss, float* __restrict__ dy) {
   __shared__ double sh[4];
   const int b = blockIdx.x;
   const int i0 = off[b], n = off[b + 1] - off[b];
+  if ((SPT == 1) != (n <= 256)) return;  // the other launch's sample
   if (n <= 0) {  // no eigenvalues: nothing to learn from this sample
     if (threadIdx.x < MT) dy[(size_t)b * MT + threadIdx.x] = 0.f;
     if (threadIdx.x == 0) loss[b] = 0.f;
     return;
   }
-  C64 z[SPT][MT + 1];
-  double sg[SPT], lmu[MT];
+  bool on[SPT];
+  C64 z[SPT];                  // z_t of the current step
+  C64 w[SPT][MT], iw[SPT][MT];  // w_t = mu_t z_t and 1 / w_t
+  double sg[SPT], mu[MT];
 #pragma unroll
   for (int r = 0; r < SPT; ++r) {
     const int i = threadIdx.x + r * 256;
-    z[r][0] = i < n ? lam[i0 + i] : mk(1.0, 0.0);
-    sg[r] = z[r][0].re > 0 ? 1.0 : -1.0;
+    on[r] = i < n;
+    z[r] = mk(1.0, 0.0);
+    if (on[r]) z[r] = lam[i0 + i];
+    sg[r] = z[r].re > 0 ? 1.0 : -1.0;
   }
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
     double ls = 0.0;
 #pragma unroll
     for (int r = 0; r < SPT; ++r)
-      if (threadIdx.x + r * 256 < n) ls += 0.5 * log(norm2(z[r][t]));
-    lmu[t] = (double)y[(size_t)b * MT + t] - block_sum256(ls, sh) / n;
-    const double mu = exp(lmu[t]);
+      if (on[r]) ls += 0.5 * log(norm2(z[r]));
+    mu[t] = exp((double)y[(size_t)b * MT + t] - block_sum256(ls, sh) / n);
 #pragma unroll
-    for (int r = 0; r < SPT; ++r) {
-      const C64 wv = mu * z[r][t];
-      z[r][t + 1] = 0.5 * (wv + cdiv1(wv));
-    }
+    for (int r = 0; r < SPT; ++r)
+      if (on[r]) {
+        w[r][t] = mu[t] * z[r];
+        iw[r][t] = cdiv1(w[r][t]);
+        z[r] = 0.5 * (w[r][t] + iw[r][t]);
+      }
   }
   double dl[SPT], e[SPT], dmax = -INFINITY;
 #pragma unroll
-  for (int r = 0; r < SPT; ++r) {
-    e[r] = norm2(z[r][MT] - mk(sg[r], 0.0));
-    dl[r] = 0.5 * log(e[r] + FLOOR);
-    if (threadIdx.x + r * 256 < n) dmax = fmax(dmax, dl[r]);
-  }
+  for (int r = 0; r < SPT; ++r)
+    if (on[r]) {
+      e[r] = norm2(z[r] - mk(sg[r], 0.0));
+      dl[r] = 0.5 * log(e[r] + FLOOR);
+      dmax = fmax(dmax, dl[r]);
+    }
   dmax = wmax(dmax);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = dmax;
@@ -284,34 +345,34 @@ __global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, 
   const double m = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
   double ex[SPT], se = 0.0;
 #pragma unroll
-  for (int r = 0; r < SPT; ++r) {
-    ex[r] = threadIdx.x + r * 256 < n ? exp(KAPPA * (dl[r] - m)) : 0.0;
-    se += ex[r];
-  }
+  for (int r = 0; r < SPT; ++r)
+    if (on[r]) {
+      ex[r] = exp(KAPPA * (dl[r] - m));
+      se += ex[r];
+    }
   const double S = block_sum256(se, sh);
   // backward: gradients as complex numbers dRe + i dIm
   C64 gz[SPT];
 #pragma unroll
-  for (int r = 0; r < SPT; ++r) gz[r] = (ex[r] / S / (e[r] + FLOOR)) * (z[r][MT] - mk(sg[r], 0.0));
+  for (int r = 0; r < SPT; ++r)
+    if (on[r]) gz[r] = (ex[r] / (S * (e[r] + FLOOR))) * (z[r] - mk(sg[r], 0.0));
   double g[MT];
 #pragma unroll
   for (int t = MT - 1; t >= 0; --t) {
-    const double mu = exp(lmu[t]);
-    C64 gw[SPT];
     double pg = 0.0;
 #pragma unroll
-    for (int r = 0; r < SPT; ++r) {
-      const C64 wv = mu * z[r][t];
-      const C64 dfw = 0.5 * (mk(1.0, 0.0) - cdiv1(cmul(wv, wv)));
-      gw[r] = cmulc(dfw, gz[r]);  // conj(f'(w)) gz, through z_{t+1} = (w + 1/w) / 2
-      pg += gw[r].re * wv.re + gw[r].im * wv.im;
-    }
+    for (int r = 0; r < SPT; ++r)
+      if (on[r]) {
+        const C64 q = cmul(iw[r][t], iw[r][t]);
+        gz[r] = cmulc(mk(0.5 * (1.0 - q.re), -0.5 * q.im), gz[r]);  // conj(f'(w)) gz, through z_{t+1} = (w + 1/w) / 2
+        pg += gz[r].re * w[r][t].re + gz[r].im * w[r][t].im;
+      }
     const double glm = block_sum256(pg, sh);  // dL/dlog mu_t = dL/dy_t
     g[t] = glm;
     // through w = mu z_t, and through the determinant scale -mean log|z_t|
 #pragma unroll
-    for (int r = 0; r < SPT; ++r)  // lanes past n stay at zero
-      gz[r] = threadIdx.x + r * 256 < n ? mu * gw[r] - (glm / (n * norm2(z[r][t]))) * z[r][t] : mk(0.0, 0.0);
+    for (int r = 0; r < SPT; ++r)
+      if (on[r]) gz[r] = mu[t] * (gz[r] - (glm / n) * conj(iw[r][t]));
   }
   if (threadIdx.x == 0) {
     loss[b] = (float)(m + log(S / n) / KAPPA);
@@ -354,41 +415,85 @@ __global__ void __launch_bounds__(256) k_mlp_delta(int B, const float* __restric
   if (live) delta[ab + 0 * MH + u] = d;
 }
 
-// backward, step 2: one thread per trainable parameter, summing over the
-// batch in order (deterministic)
-__global__ void __launch_bounds__(256) k_mlp_wgrad(int B, const float* __restrict__ P, const float* __restrict__ feat,
+// backward, step 2: the weight gradients sum_b delta[b][u] in[b][v] as matrix
+// products over the batch on the FP32 matrix cores (layout as in k_mlp_fwd:
+// A = delta^T, B = the layer's input).  One workgroup of 16 waves per 16 x 16
+// tile of a weight matrix: 4 tiles of W1, 16 of W2, 16 of W3 and 4 of W4 (its
+// 4 rows of 16).  Wave w takes samples 4 w .. 4 w + 3 of every 64, one product
+// each, in order; the 16 accumulators then meet in LDS and are added in wave
+// order, so the result does not depend on timing.  The bias gradient of 16
+// units comes from the same delta entries, in the workgroups of the first
+// column tile.  No scratch memory.
+// Bound by the latency of the loads (the batch's deltas and activations stay
+// in L2 between the 40 workgroups): one thread per parameter walking the
+// whole batch, as before, is a chain of 2048 dependent additions, 519 us for
+// 2048 samples; now 10.7.
+constexpr int WGT = 1024, WGW = WGT / 64;
+constexpr int NWT = 40;  // weight tiles
+
+__global__ void __launch_bounds__(WGT) k_mlp_wgrad(int B, const float* __restrict__ P, const float* __restrict__ feat,
                                                    const float* __restrict__ act, const float* __restrict__ dy,
                                                    const float* __restrict__ delta, float* __restrict__ grad) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= NK_MLP_NTRAIN) return;
-  float acc = 0.f;
-  if (k < OB1) {  // W1[u][v]: delta1[u] x[v]
-    const int u = k / MI, v = k % MI;
-    const float mv = P[OMEAN + v], iv = P[OISTD + v];
-    for (int b = 0; b < B; ++b) acc += delta[((size_t)b * 3 + 0) * MH + u] * ((feat[(size_t)b * MI + v] - mv) * iv);
-  } else if (k < OW2) {
-    const int u = k - OB1;
-    for (int b = 0; b < B; ++b) acc += delta[((size_t)b * 3 + 0) * MH + u];
-  } else if (k < OB2) {  // W2[u][v]: delta2[u] a1[v]
-    const int u = (k - OW2) / MH, v = (k - OW2) % MH;
-    for (int b = 0; b < B; ++b) acc += delta[((size_t)b * 3 + 1) * MH + u] * act[((size_t)b * 3 + 0) * MH + v];
-  } else if (k < OW3) {
-    const int u = k - OB2;
-    for (int b = 0; b < B; ++b) acc += delta[((size_t)b * 3 + 1) * MH + u];
-  } else if (k < OB3) {  // W3[u][v]: delta3[u] a2[v]
-    const int u = (k - OW3) / MH, v = (k - OW3) % MH;
-    for (int b = 0; b < B; ++b) acc += delta[((size_t)b * 3 + 2) * MH + u] * act[((size_t)b * 3 + 1) * MH + v];
-  } else if (k < OW4) {
-    const int u = k - OB3;
-    for (int b = 0; b < B; ++b) acc += delta[((size_t)b * 3 + 2) * MH + u];
-  } else if (k < OB4) {  // W4[t][v]: dy[t] a3[v]
-    const int t = (k - OW4) / MH, v = (k - OW4) % MH;
-    for (int b = 0; b < B; ++b) acc += dy[(size_t)b * MT + t] * act[((size_t)b * 3 + 2) * MH + v];
-  } else {
-    const int t = k - OB4;
-    for (int b = 0; b < B; ++b) acc += dy[(size_t)b * MT + t];
+  __shared__ float sacc[WGW][16][17];
+  __shared__ float sb[WGW][16];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, q = lane >> 4;
+  // the tile: layer 0..3, first unit u0 and first input v0
+  const int tile = blockIdx.x;
+  const int layer = tile < 4 ? 0 : tile < 20 ? 1 : tile < 36 ? 2 : 3;
+  const int tl = tile - (layer == 0 ? 0 : layer == 1 ? 4 : layer == 2 ? 20 : 36);
+  const int u0 = layer == 0 ? 16 * tl : layer == 3 ? 0 : 16 * (tl >> 2);
+  const int v0 = layer == 0 ? 0 : layer == 3 ? 16 * tl : 16 * (tl & 3);
+  const int u = u0 + l16, v = v0 + l16;
+  // element (b, u) of the output-side gradients and (b, v) of the input side
+  const float* ga = layer == 3 ? dy : delta + layer * MH;
+  const int lda = layer == 3 ? MT : 3 * MH;
+  const float* gb = layer == 0 ? feat : act + (layer - 1) * MH;
+  const int ldb = layer == 0 ? MI : 3 * MH;
+  const bool ua = layer != 3 || u < MT;
+  const float mv = layer == 0 ? P[OMEAN + v] : 0.f, iv = layer == 0 ? P[OISTD + v] : 1.f;
+  nk_f4 acc = {0.f, 0.f, 0.f, 0.f};
+  float bsum = 0.f;
+  constexpr int U = 4;  // loads of four products in flight
+  for (int b0 = 4 * w; b0 < B; b0 += 64 * U) {  // wave-uniform: every lane takes part in the products
+    float av[U], bv[U];
+#pragma unroll
+    for (int s = 0; s < U; ++s) {
+      const int b = b0 + 64 * s + q;
+      const bool in = b < B;
+      const size_t bb = in ? b : 0;
+      const float x = ga[bb * lda + (ua ? u : 0)], z = gb[bb * ldb + v];
+      av[s] = in && ua ? x : 0.f;
+      bv[s] = in ? (layer == 0 ? (z - mv) * iv : z) : 0.f;
+    }
+#pragma unroll
+    for (int s = 0; s < U; ++s) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s], bv[s], acc, 0, 0, 0);
+      bsum += av[s];
+    }
   }
-  grad[k] = acc;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) sacc[w][4 * q + i][l16] = acc[i];
+  bsum += __shfl_xor(bsum, 16, 64);
+  bsum += __shfl_xor(bsum, 32, 64);
+  if (q == 0) sb[w][l16] = bsum;
+  __syncthreads();
+  if (tid < 256) {
+    const int r = tid >> 4, c = tid & 15;
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < WGW; ++k) t += sacc[k][r][c];
+    const int ow = layer == 0 ? OW1 : layer == 1 ? OW2 : layer == 2 ? OW3 : OW4;
+    const int ld = layer == 0 ? MI : MH;
+    if (layer != 3 || r < MT) grad[ow + (u0 + r) * ld + v0 + c] = t;
+  }
+  if (v0 == 0 && tid < 16 && (layer != 3 || tid < MT)) {
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < WGW; ++k) t += sb[k][tid];
+    const int ob = layer == 0 ? OB1 : layer == 1 ? OB2 : layer == 2 ? OB3 : OB4;
+    grad[ob + u0 + tid] = t;
+  }
 }
 
 __global__ void k_adam(int n, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -429,7 +534,7 @@ int mlp_features(int batch, int ld, const int* nvec_dev, const C64* S, float* fe
 
 int mlp_forward(int batch, const float* P, const float* feat, float* y, float* act, hipStream_t st) {
   if (batch <= 0) return NK_OK;
-  hipLaunchKernelGGL(k_mlp_fwd, dim3((batch + 3) / 4), dim3(256), 0, st, batch, P, feat, y, act);
+  hipLaunchKernelGGL(k_mlp_fwd, dim3((batch + FS - 1) / FS), dim3(256), 0, st, batch, P, feat, y, act);
   NK_HIP(hipGetLastError());
   return NK_OK;
 }
@@ -437,7 +542,8 @@ int mlp_forward(int batch, const float* P, const float* feat, float* y, float* a
 int mlp_spectral_loss(int batch, const int* off, const C64* lam, const float* y, float gscale, float* loss,
                       float* dy, hipStream_t st) {
   if (batch <= 0) return NK_OK;
-  hipLaunchKernelGGL(k_spec_loss, dim3(batch), dim3(256), 0, st, off, lam, y, gscale, loss, dy);
+  hipLaunchKernelGGL(k_spec_loss<1>, dim3(batch), dim3(256), 0, st, off, lam, y, gscale, loss, dy);
+  hipLaunchKernelGGL(k_spec_loss<4>, dim3(batch), dim3(256), 0, st, off, lam, y, gscale, loss, dy);
   NK_HIP(hipGetLastError());
   return NK_OK;
 }
@@ -445,8 +551,7 @@ int mlp_spectral_loss(int batch, const int* off, const C64* lam, const float* y,
 int mlp_backward(int batch, const float* P, const float* feat, const float* act, const float* dy, float* delta,
                  float* grad, hipStream_t st) {
   if (batch > 0) hipLaunchKernelGGL(k_mlp_delta, dim3((batch + 3) / 4), dim3(256), 0, st, batch, P, act, dy, delta);
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3((NK_MLP_NTRAIN + 255) / 256), dim3(256), 0, st, batch, P, feat, act, dy, delta,
-                     grad);
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3(NWT), dim3(WGT), 0, st, batch, P, feat, act, dy, delta, grad);
   NK_HIP(hipGetLastError());
   return NK_OK;
 }
