@@ -334,6 +334,7 @@ nk_lattice::~nk_lattice() {
   defl.release();
   ovl.release();
   eig.release();
+  eig_pin.release();
   for (hipEvent_t e : evpool) (void)hipEventDestroy(e);
 }
 

@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "hostbuf.h"
 #include "nk.h"
 
 namespace nk {
@@ -205,7 +206,8 @@ struct nk_lattice {
   nk::DevBuf bsmall;   // multi-source path: coefficients, partial sums, small problems
   nk::DevBuf defl;     // deflation: partial sums, projections, projected sources
   nk::DevBuf ovl;      // overlap operator and solver: CG vectors, sign temporaries
-  nk::DevBuf eig;      // eigensolver: four blocks of p vectors, partial sums, p x p matrices
+  nk::DevBuf eig;      // eigensolver: four or six blocks of p vectors, partial sums, p x p matrices
+  nk::HostBuf eig_pin; // eigensolver: the p x p matrices on their way between host and device
   // multi-source path: sweeps captured as HIP graphs, keyed by their launch arguments
   struct Graph {
     std::vector<char> key;
@@ -274,6 +276,18 @@ int unpack_spinor(const Geom& g, const Cx<R>* dev, C64* canon, hipStream_t st);
 int apply_dw_dev(nk_lattice* lat, double m_w, double mu, int g5, const C64* x, C64* y, hipStream_t st);
 int apply_pair_dev(nk_lattice* lat, double m_w, double mu, const C64* v, const C64* w, C64* av, C64* adw,
                    hipStream_t st);
+// gamma5 Dw on blocks of p packed vectors, one block per side: out = A x, or
+// (cheb) out = ca A x + cb y + cc out (cc = 0: out is not read); ef / eb are
+// each side's temporal hop factors e^{+mu}, e^{-mu}
+struct ApplyBlock {
+  const C64* x[2];
+  const C64* y[2];
+  C64* out[2];
+  double ef[2], eb[2];
+  double ca, cb, cc;
+  int p;
+};
+int apply_block_dev(nk_lattice* lat, double m_w, const ApplyBlock& a, int sides, bool cheb, hipStream_t st);
 
 // krylov.hip -- outer basis; coefficient arrays stay on the device
 struct Coefs {

@@ -4,8 +4,10 @@ import numpy as np
 import pytest
 
 import latgen
+from oracle import deflation as DF
 from oracle import learned as L
-from tests.gpu_helpers import banner, nk, torch_cuda
+from oracle import wilson as W
+from tests.gpu_helpers import M_W, banner, make_lattice, nk, to_dev, to_host, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -41,3 +43,37 @@ def test_mlp_batch_remainders(B, shift):
     for i in range(3):
         assert off(act.cpu().numpy()[:, i], acts[1 + i]) < 2e-5
     assert off(grad.cpu().numpy(), g) < 2e-5
+
+
+@pytest.mark.parametrize("p", [4, 15, 16, 17, 32, 33, 48, 65, 81, 97, 112, 113, 128])
+@pytest.mark.parametrize("mu", [0.0, 0.3])
+def test_eigenpairs_block_sizes(p, mu):
+    """Blocks around the 16- and 32-vector tiles of the Gram and rotation
+    kernels, up to the largest, on 2x2x4x4: the three eigenvalues nearest the
+    imaginary axis against the dense eigen-decomposition, and the residuals of
+    right and left vectors with the oracle's operator (tolerances of the
+    solver's own tests)."""
+    torch = torch_cuda()
+    b = nk()
+    dims, m = (2, 2, 4, 4), 3
+    n = 12 * 64
+    banner(f"eigenpairs p={p} mu={mu}")
+    lat, u = make_lattice(dims, 0.8, seed=0)
+    v0 = to_dev(latgen.random_sources(dims, p, 11))
+    r = torch.empty(m * n, dtype=torch.complex128, device="cuda")
+    left = torch.empty_like(r)
+    if mu == 0.0:
+        lam, _, resid, rc = b.nk_eig_hermitian_device(lat.h, M_W, m, p, 20, 1e-11, 400, v0, r)
+        left.copy_(r)
+    else:
+        lam, _, resid, rc = b.nk_eig_critical_device(lat.h, M_W, mu, m, p, 20, 1e-11, 400, v0, r, left)
+    assert rc == 0
+    ld, _, _ = DF.critical_eigenpairs(W.dense_matrix(u, M_W, mu), m, mu == 0.0)
+    assert np.max(np.abs(np.sort_complex(lam) - np.sort_complex(ld))) < 1e-10
+    R, Lv = to_host(r).reshape(m, n), to_host(left).reshape(m, n)
+    assert np.linalg.norm(Lv.conj() @ R.T - np.eye(m)) < 1e-10
+    for i in range(m):
+        f = lambda v, s: W.a_apply(u, v.reshape(4, 4, 2, 2, 4, 3), M_W, s).reshape(-1)  # noqa: E731
+        assert np.linalg.norm(f(R[i], mu) - lam[i] * R[i]) < 2e-10
+        assert np.linalg.norm(f(Lv[i], -mu) - np.conj(lam[i]) * Lv[i]) < 2e-10 * np.linalg.norm(Lv[i])
+    lat.close()
