@@ -702,8 +702,9 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
   NK_HIP(hipGetLastError());
   std::vector<int> its(r);
   std::vector<double> res(r);
+  const TriIn tri{abd, abd + ld, abd + 2 * ld, (size_t)3 * ld};
   const int erh = rh_sign_batched(r, ld, lus.data(), S, p->rh_scaling, p->rh_maxit, p->rh_tol, its.data(), res.data(),
-                                  st);
+                                  st, &tri);
   if (erh < 0) return erh;
   if (erh > 0 && warn == NK_OK) warn = erh;
   hipLaunchKernelGGL(k_bz, dim3((k + 255) / 256, r), dim3(256), 0, st, k, ld, kv, lv, nested, Vl, S, z);

@@ -15,6 +15,7 @@
 #include <hip/hip_ext.h>
 
 #include "stencil.h"
+#include "wave.h"
 
 namespace nk {
 
@@ -23,31 +24,6 @@ constexpr int NT = 256;
 #ifndef NK_AUTOTUNE
 #define NK_AUTOTUNE 1  // choose the direction groups of K1 by timing both on first use
 #endif
-
-// v from the lane that the DPP pattern CTRL selects (a row shift or a row
-// broadcast, in the rows of ROWMASK), 0.0 where the pattern has no source
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ double dpp_take(double v) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWMASK, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWMASK, 0xf, false);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// sum over the 64 lanes of a wave in a fixed order (DPP row shifts, then the
-// row broadcasts; lane 63 ends with the total), returned in every lane
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp_take<0x111, 0xf>(v);  // row_shr:1
-  v += dpp_take<0x112, 0xf>(v);  // row_shr:2
-  v += dpp_take<0x114, 0xf>(v);  // row_shr:4
-  v += dpp_take<0x118, 0xf>(v);  // row_shr:8
-  v += dpp_take<0x142, 0xa>(v);  // row_bcast:15
-  v += dpp_take<0x143, 0xc>(v);  // row_bcast:31
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, 63);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), 63);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 
 template <int NQ>
 __device__ __forceinline__ void block_sum(double (&v)[NQ]) {

@@ -355,8 +355,17 @@ int rh_tile_force(int rm, int pth, int tile);
 // the Newton-Schulz tail of the large path on (1) or off (0); returns the previous setting
 int rh_newton_schulz(int enable);
 int rh_tile_choice(int maxn, int batch, int* nb, int* rm, int* pth, int* tile);
+// a batch of tridiagonal matrices on the device: diagonal, super- and
+// sub-diagonal of matrix m at a/b/d + m * stride
+struct TriIn {
+  const C64* a;
+  const C64* b;
+  const C64* d;
+  size_t stride;
+};
+// tri: the same matrices as tridiagonals (S holds them dense), where they are
 int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, int maxit, double tol,
-                    int* iters_host, double* resid_host, hipStream_t st);
+                    int* iters_host, double* resid_host, hipStream_t st, const TriIn* tri = nullptr);
 
 // mlp.hip -- learned Roberts-Higham scaling (device pointers)
 int mlp_features(int batch, int ld, const int* nvec_dev, const C64* S, float* feat, hipStream_t st);

@@ -1,8 +1,10 @@
 // Roberts-Higham iteration S_{n+1} = (S_n + S_n^{-1}) / 2 (Eq. (4)) for a
 // batch of dense complex matrices of uneven sizes, on gfx950.
 //
-// Orders up to 128 run every iteration in one launch per batch (k_rh_small,
-// below).  Larger ones invert each iterate by a blocked Gauss-Jordan
+// Tridiagonal start matrices (the Ritz matrices) take their first steps in
+// closed form (rhtri.hip), usually all of them.  Other matrices, and steps
+// past those: orders up to 128 run every iteration in one launch per batch
+// (k_rh_small, below).  Larger ones invert each iterate by a blocked Gauss-Jordan
 // elimination with partial pivoting in which rows are never moved: posof[r]
 // is the column whose pivot row is r (-1 while r is unused) and rowof[c] the
 // pivot row of column c, and the eliminated matrix X holds
@@ -44,6 +46,7 @@
 
 #include "hostbuf.h"
 #include "nk_internal.h"
+#include "rhtri.h"
 
 namespace nk {
 
@@ -655,7 +658,8 @@ __device__ __forceinline__ unsigned piv_key32(double v, int r) {
 template <int SQ>  // rows per thread, at least ceil(n / floor(512 / n)) (the host picks it)
 __global__ void __launch_bounds__(ST_RH) k_rh_small(int ld, const int* __restrict__ nvec, C64* __restrict__ S_b,
                                                    int scaling, const double* __restrict__ mu_sched, int mu_steps,
-                                                   int maxit, double tol, int* __restrict__ iters,
+                                                   int maxit, double tol, const int* __restrict__ start,
+                                                   const double* __restrict__ prev0, int* __restrict__ iters,
                                                    int* __restrict__ sing) {
   const int b = blockIdx.x;
   const int n = nvec[b];
@@ -663,6 +667,9 @@ __global__ void __launch_bounds__(ST_RH) k_rh_small(int ld, const int* __restric
     if (threadIdx.x == 0) iters[b] = 0;
     return;
   }
+  // steps already taken on S (< 0: this matrix has converged) and the last one's change
+  const int it0 = start ? start[b] : 0;
+  if (it0 < 0) return;
   C64* S = S_b + (size_t)b * ld * ld;
   __shared__ C64 s_col[2][SMAX];
   __shared__ C64 s_row[2][SMAX];
@@ -679,9 +686,9 @@ __global__ void __launch_bounds__(ST_RH) k_rh_small(int ld, const int* __restric
   const int rend = min(n, r0 + rps);  // rows r0 .. rend - 1
   const bool colok = seg < nseg;
   C64 a[SQ];
-  double prev = INFINITY;
+  double prev = prev0 ? prev0[b] : INFINITY;
   int it = 0, bad = 0;
-  for (it = 1; it <= maxit; ++it) {
+  for (it = it0 + 1; it <= maxit; ++it) {
     // a per-iteration copy of the base pointer that the compiler cannot see
     // through: otherwise it hoists SQ 64-bit element addresses out of the
     // iteration loop and keeps them live through every pivot step
@@ -999,7 +1006,7 @@ int rh_tile_choice(int maxn, int batch, int* nb, int* rm, int* pth, int* tile) {
 // scratch buffer G0 and the partial sums of |I - S^2|_F^2), then the sums,
 // written by k_rh_resid_sum straight into pinned host memory
 static int rh_residuals(int batch, int maxn, int ld, const int* nvec, const C64* S, double* resid_host,
-                        hipStream_t st) {
+                        hipStream_t st) {  // waits for the stream
   const int ntile = (maxn + 31) / 32;
   const size_t nsp = (size_t)batch * ntile * ntile * 2;
   if (g_nsp.ensure(nsp * sizeof(double) + (size_t)batch * sizeof(int))) return NK_ENOMEM;
@@ -1019,7 +1026,7 @@ static int rh_residuals(int batch, int maxn, int ld, const int* nvec, const C64*
 }
 
 int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, int maxit, double tol,
-                    int* iters_host, double* resid_host, hipStream_t st) {
+                    int* iters_host, double* resid_host, hipStream_t st, const TriIn* tri) {
   std::lock_guard<std::mutex> lock(g_rh_mu);
   if (batch <= 0 || ld <= 0) return NK_OK;
   if (ld > 4 * PT) {
@@ -1078,8 +1085,68 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
     if (int e = mlp_schedule(batch, ld, nvec, S, g_sched.as<double>(), &have, st)) return e;
     if (have) mdev = g_sched.as<double>();
   }
+  // the steps of a tridiagonal start matrix in closed form, with Eq. (4)'s
+  // stopping test on every step; what has not converged by then goes on below
+  // from there (step it0 + 1)
+  int it0 = 0;
+  std::vector<int> done(batch, 0), state(batch, 0);
+  std::vector<double> change0(batch, INFINITY);
+  if (const int L = tri ? tri_rh_steps(batch, ld, maxn, scaling, maxit) : 0) {
+    const double* sums = nullptr;
+    const int e = tri_rh_run(batch, ld, maxn, nvec, *tri, S, scaling, mdev, mu_steps, L, &sums, st);
+    if (e < 0) return e;
+    if (e == 0) {  // (1: no memory for its workspace)
+      if (resid_host) {
+        if (int e2 = rh_residuals(batch, maxn, ld, nvec, S, resid_host, st)) return e2;
+      } else {
+        NK_HIP(hipStreamSynchronize(st));
+      }
+      it0 = L;
+      bool all = true;
+      for (int b = 0; b < batch; ++b) {
+        const double* v = sums + (size_t)b * (2 * L + 1);
+        iters_host[b] = 0;
+        if (n_host[b] <= 0) {
+          done[b] = 1;
+          continue;
+        }
+        double prev = INFINITY;
+        for (int m = 0; m < L && !done[b]; ++m) {
+          const double change = std::sqrt(v[2 * m] / v[2 * m + 1]);
+          iters_host[b] = m + 1;
+          if (!(change > tol) || (change < 1e-6 && change > 0.5 * prev)) done[b] = 1;
+          if (!std::isfinite(change)) state[b] = 1;
+          prev = change;
+        }
+        change0[b] = prev;
+        if (v[2 * L] != 0.0) {
+          state[b] = 1;
+          done[b] = 1;
+        }
+        if (!done[b] && L >= maxit) {
+          state[b] = 2;  // the cap ended the iteration before the stopping test held
+          done[b] = 1;
+        }
+        all = all && done[b];
+      }
+      if (all) return rh_outcome(batch, state.data(), maxit);
+    }
+  }
   if (maxn <= SMAX) {
     NK_HIP(hipMemcpyAsync(sing, pin_zero, batch * sizeof(int), hipMemcpyHostToDevice, st));
+    const int* start = nullptr;
+    const double* prev0 = nullptr;
+    if (it0 > 0) {  // in the slots of the large path's flags and stopping sums
+      double* ph = const_cast<double*>(sums_h);
+      for (int b = 0; b < batch; ++b) {
+        pin_gj[b] = done[b] ? -1 : it0;
+        ph[b] = change0[b];
+      }
+      NK_HIP(hipMemcpyAsync(rowof, pin_gj, batch * sizeof(int), hipMemcpyHostToDevice, st));
+      NK_HIP(hipMemcpyAsync(resid, ph, batch * sizeof(double), hipMemcpyHostToDevice, st));
+      start = rowof;
+      prev0 = resid;
+    }
     int rps = 0;  // largest rows-per-thread over the batch
     for (int b = 0; b < batch; ++b)
       if (n_host[b] > 0) rps = std::max(rps, (n_host[b] + ST_RH / n_host[b] - 1) / (ST_RH / n_host[b]));
@@ -1088,33 +1155,37 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
     // per-pivot work each time it halves
     if (rps <= 2)
       hipLaunchKernelGGL(k_rh_small<2>, dim3(batch), dim3(ST_RH), 0, st, ld, nvec, S, scaling, mdev, mu_steps, maxit,
-                         tol, act, sing);
+                         tol, start, prev0, act, sing);
     else if (rps <= 4)
       hipLaunchKernelGGL(k_rh_small<4>, dim3(batch), dim3(ST_RH), 0, st, ld, nvec, S, scaling, mdev, mu_steps, maxit,
-                         tol, act, sing);
+                         tol, start, prev0, act, sing);
     else if (rps <= 8)
       hipLaunchKernelGGL(k_rh_small<8>, dim3(batch), dim3(ST_RH), 0, st, ld, nvec, S, scaling, mdev, mu_steps, maxit,
-                         tol, act, sing);
+                         tol, start, prev0, act, sing);
     else if (rps <= 16)
       hipLaunchKernelGGL(k_rh_small<16>, dim3(batch), dim3(ST_RH), 0, st, ld, nvec, S, scaling, mdev, mu_steps, maxit,
-                         tol, act, sing);
+                         tol, start, prev0, act, sing);
     else
       hipLaunchKernelGGL(k_rh_small<32>, dim3(batch), dim3(ST_RH), 0, st, ld, nvec, S, scaling, mdev, mu_steps, maxit,
-                         tol, act, sing);
+                         tol, start, prev0, act, sing);
     NK_HIP(hipGetLastError());
     NK_HIP(hipMemcpyAsync(pin_iters, act, batch * sizeof(int), hipMemcpyDeviceToHost, st));
     NK_HIP(hipMemcpyAsync(pin_state, sing, batch * sizeof(int), hipMemcpyDeviceToHost, st));
     if (resid_host)
       if (int e = rh_residuals(batch, maxn, ld, nvec, S, resid_host, st)) return e;
     NK_HIP(hipStreamSynchronize(st));
-    std::copy(pin_iters, pin_iters + batch, iters_host);
-    return rh_outcome(batch, pin_state, maxit);
+    for (int b = 0; b < batch; ++b)
+      if (!done[b]) {
+        iters_host[b] = pin_iters[b];
+        state[b] = pin_state[b];
+      }
+    return rh_outcome(batch, state.data(), maxit);
   }
   maxn = 0;
   for (int b = 0; b < batch; ++b) {
     maxn = std::max(maxn, n_host[b]);
-    act_h[b] = n_host[b] > 0 ? 1 : 0;
-    iters_host[b] = 0;
+    act_h[b] = n_host[b] > 0 && !done[b] ? 1 : 0;
+    if (it0 == 0) iters_host[b] = 0;
   }
   std::copy(act_h.begin(), act_h.end(), pin_act0);
   NK_HIP(hipMemcpyAsync(act, pin_act0, batch * sizeof(int), hipMemcpyHostToDevice, st));
@@ -1135,7 +1206,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
                         &shape))
     return e;
   NK_HIP(hipMemcpyAsync(sing, pin_zero, batch * sizeof(int), hipMemcpyHostToDevice, st));
-  std::vector<double> prev(batch, INFINITY);
+  std::vector<double> prev(change0);
   // a flag array to the device, only when it differs from its last upload;
   // the staging slot is rewritten only here, after the stopping sums of a
   // later point of the stream (or a synchronisation) have been seen, so its
@@ -1178,7 +1249,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
   // the step at which a matrix may try the Newton-Schulz test: once its
   // relative change has fallen below this (earlier tests would only fail)
   const double ns_try = 0.05;
-  for (int it = 1; it <= maxit; ++it) {
+  for (int it = it0 + 1; it <= maxit; ++it) {
     bool any = false;
     for (int b = 0; b < batch; ++b) any = any || act_h[b];
     if (!any) break;
@@ -1247,9 +1318,11 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
   if (resid_host)
     if (int e = rh_residuals(batch, maxn, ld, nvec, S, resid_host, st)) return e;
   NK_HIP(hipStreamSynchronize(st));
-  for (int b = 0; b < batch; ++b)
-    if (act_h[b] && !pin_state[b]) pin_state[b] = 2;  // still active after maxit iterations
-  return rh_outcome(batch, pin_state, maxit);
+  for (int b = 0; b < batch; ++b) {
+    if (!done[b]) state[b] = pin_state[b];
+    if (act_h[b] && !state[b]) state[b] = 2;  // still active after maxit iterations
+  }
+  return rh_outcome(batch, state.data(), maxit);
 }
 
 }  // namespace nk

@@ -1,0 +1,21 @@
+// Roberts-Higham from a tridiagonal start matrix (rhtri.hip), called by
+// rh.hip under its lock.
+#pragma once
+
+#include "nk_internal.h"
+
+namespace nk {
+
+// RH steps that tri_rh_run takes in closed form for this batch, 0 = none
+int tri_rh_steps(int batch, int ld, int maxn, int scaling, int maxit);
+
+// S (dense S_0 = H of every matrix, leading dimension ld) <- S_L after L
+// steps; sched: [batch][nsched] learned corrections or null.  *sums (host
+// memory, valid once the stream has been waited for): per matrix the pairs
+// |S_{n+1} - mu_n S_n|^2, |S_{n+1}|^2 of the L steps, then nonzero if an
+// elimination ended on a zero pivot.  Returns 1, with S unchanged, when there
+// is no memory for the workspace.
+int tri_rh_run(int batch, int ld, int maxn, const int* nvec, const TriIn& h, C64* S, int scaling, const double* sched,
+               int nsched, int L, const double** sums, hipStream_t st);
+
+}  // namespace nk

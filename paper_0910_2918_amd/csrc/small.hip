@@ -813,7 +813,8 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
     NK_HIP(hipGetLastError());
     int it = 0;
     double res = 0;
-    int e = rh_sign_batched(1, k, &k, H, rh_scaling, rh_maxit, rh_tol, &it, &res, st);
+    const TriIn tri{alpha, beta, delta, 0};
+    int e = rh_sign_batched(1, k, &k, H, rh_scaling, rh_maxit, rh_tol, &it, &res, st, &tri);
     if (e < 0) return e;
     hipLaunchKernelGGL(k_col0, dim3((k + 255) / 256), dim3(256), 0, st, k, H, z);
     NK_HIP(hipGetLastError());
@@ -874,7 +875,8 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
   NK_HIP(hipGetLastError());
   int it = 0;
   double res = 0;
-  int e = rh_sign_batched(1, lu, &lu, Hl, rh_scaling, rh_maxit, rh_tol, &it, &res, st);
+  const TriIn tri{s.a, s.b, s.d, 0};
+  int e = rh_sign_batched(1, lu, &lu, Hl, rh_scaling, rh_maxit, rh_tol, &it, &res, st, arnoldi ? nullptr : &tri);
   if (e < 0) return e;
   hipLaunchKernelGGL(k_in_lift, dim3((k + 255) / 256), dim3(256), 0, st, k, lu, s.V, Hl, lu, z);
   NK_HIP(hipGetLastError());

@@ -54,8 +54,8 @@ __global__ void __launch_bounds__(256) k_apply(Geom g, LK lk, R diag, int g5, Fi
 // with old the vector that out replaces (each entry is read before it is
 // written; cc = 0 reads none).  One launch per application of the block: on
 // 8^4 one vector is 64 workgroups, a quarter of the compute units, and its
-// launch took as long as its work (5.2 us + 7 us between launches for one of 48
-// vectors); the block runs 48 vectors in @C us.  The hardware deals
+// launches follow each other no faster than every 5 us; the block runs 48
+// vectors in 28 us (with the recurrence step 34).  The hardware deals
 // workgroup b to XCD b mod 8, so every vector's site block lands on the XCD
 // that holds its links.  Folding the recurrence step in saves writing and
 // reading A x (a third of the bytes of the step).

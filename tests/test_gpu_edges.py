@@ -77,3 +77,100 @@ def test_eigenpairs_block_sizes(p, mu):
         assert np.linalg.norm(f(R[i], mu) - lam[i] * R[i]) < 2e-10
         assert np.linalg.norm(f(Lv[i], -mu) - np.conj(lam[i]) * Lv[i]) < 2e-10 * np.linalg.norm(Lv[i])
     lat.close()
+
+
+def _tridiag(kind, n, seed):
+    """Tridiagonal matrices (diagonal, super-, sub-diagonal) away from the imaginary axis."""
+    rng = np.random.default_rng([seed, n])
+    c = lambda: rng.standard_normal(n) + 1j * rng.standard_normal(n)  # noqa: E731
+    if kind == "zerodiag":  # zero pivots at every other step; spectrum +-(1 +- 0.3)
+        b = np.where(np.arange(n) % 2 == 0, 1.3, 0.3) + 0j
+        return np.zeros(n, np.complex128), b, b.copy()
+    if kind == "real":  # Hermitian, two intervals
+        a = np.where(np.arange(n) % 2 == 0, 2.0, -2.0) + 0.3 * rng.standard_normal(n)
+        b = 0.8 + 0.2 * rng.random(n)
+        return a + 0j, b + 0j, b + 0j
+    if kind == "complex":
+        a = np.where(rng.random(n) < 0.5, 3.0, -3.0) + 0.3 * c()
+        return a, 0.6 * c(), 0.6 * c()
+    a, b, d = _tridiag("real", n, seed)  # slow: an eigenvalue 1e-4 of the others' size in an uncoupled corner
+    a[-1] = 2e-4
+    if n > 1:
+        b[n - 2] = d[n - 2] = 0.0
+    return a, b, d
+
+
+def _dense(a, b, d):
+    return np.diag(a) + np.diag(b[:-1], 1) + np.diag(d[:-1], -1)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 16, 31, 63, 64, 65, 127, 128, 129, 192, 193, 255, 257, 320, 511])
+@pytest.mark.parametrize("kind", ["real", "complex", "zerodiag", "slow"])
+def test_tridiagonal_sign_orders(kind, n):
+    """sgn(T) e_1 of tridiagonal T over the edges of the 64-column and 128-row
+    tiles and of the rule between 4 and 16 poles at a time, unscaled and with
+    determinant scaling: against the oracle's Roberts-Higham iteration with
+    explicit inverses (1e-10, the tolerance of the dense iteration's tests) and
+    the spectral sign, with the iteration count to +-1.  "zerodiag" meets exact
+    zero pivots, "slow" goes past the steps taken in closed form."""
+    from oracle import dense as D
+    from oracle import rh as R
+    if kind == "zerodiag" and n % 2:
+        n += 1  # an odd one is singular
+    b = nk()
+    a, be, de = _tridiag(kind, n, 5)
+    T = _dense(a, be, de)
+    banner(f"tridiagonal sign {kind} n={n}")
+    so, ito, _ = R.roberts_higham(T)
+    ref = D.sign_spectral(T, hermitian=False)
+    for scaling in (b.NK_RH_NONE, b.NK_RH_DET):
+        z, info, rc = b.nk_small_sign(n, 0, kind != "complex", a, be, de, b.nk_sign_params_default(rh_scaling=scaling))
+        assert rc == 0
+        assert np.linalg.norm(z - so[:, 0]) < 1e-10 and np.linalg.norm(z - ref[:, 0]) < 1e-9
+        assert info.rh_residual < 1e-9
+        if scaling == b.NK_RH_NONE:
+            assert abs(info.rh_iters - ito) <= 1
+        else:
+            _, itd, _ = R.roberts_higham(T, scale=R.determinant_scale)
+            assert abs(info.rh_iters - itd) <= 1
+
+
+@pytest.mark.parametrize("n", [6, 60, 128, 130, 300])
+@pytest.mark.parametrize("maxit", [1, 2, 3, 4, 5, 7, 9, 10, 11])
+@pytest.mark.parametrize("det", [False, True])
+def test_tridiagonal_sign_capped(n, maxit, det):
+    """The iterate after every possible cap equals the oracle's (the steps taken
+    in closed form, and those after them, are Eq. (4)'s)."""
+    from oracle import rh as R
+    b = nk()
+    a, be, de = _tridiag("slow", n, 9)
+    T = _dense(a, be, de)
+    S, it, _ = R.roberts_higham(T, maxit=maxit, scale=R.determinant_scale if det else None)
+    banner(f"tridiagonal sign n={n} maxit={maxit} det={det}")
+    p = b.nk_sign_params_default(rh_maxit=maxit, rh_scaling=b.NK_RH_DET if det else b.NK_RH_NONE)
+    z, info, rc = b.nk_small_sign(n, 0, True, a, be, de, p)
+    assert info.rh_iters == it
+    assert rc == (b.NK_WARN_NOTCONV if it == maxit else 0) or it == maxit
+    assert np.linalg.norm(z - S[:, 0]) <= 1e-11 * max(1.0, np.linalg.norm(S[:, 0]))
+
+
+@pytest.mark.parametrize("n", [1, 3, 97, 200])
+def test_tridiagonal_sign_singular(n):
+    """A singular matrix, and one with the eigenvalue i (whose first iterate is
+    singular), are reported as by the dense iteration."""
+    b = nk()
+    for last in (0.0, 1j):
+        a, be, de = _tridiag("slow", n, 3)
+        a[-1] = last
+        banner(f"tridiagonal sign n={n} with eigenvalue {last}")
+        _, _, rc = b.nk_small_sign(n, 0, False, a, be, de)
+        assert rc == b.NK_WARN_NOTCONV
+        assert "singular" in b.nk_last_error()
+
+
+def test_tridiagonal_sign_nan_is_reported():
+    b = nk()
+    a, be, de = _tridiag("real", 70, 4)
+    a[30] = np.nan
+    _, _, rc = b.nk_small_sign(70, 0, True, a, be, de)
+    assert rc == b.NK_WARN_NOTCONV
