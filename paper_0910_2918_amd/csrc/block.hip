@@ -392,22 +392,11 @@ __global__ void k_tri_dense_b(int ld, const int* __restrict__ nvec, const C64* _
   }
 }
 
-// z = column 0 of S (non-nested) or V_ell times it (nested), per source
-__global__ void k_bz(int kmax, int ld, const int* __restrict__ kvec, const int* __restrict__ lvec, int nested,
-                     const C64* __restrict__ Vl, const C64* __restrict__ S, C64* __restrict__ z) {
+// z = column 0 of S, per source (non-nested)
+__global__ void k_bz(int kmax, int ld, const int* __restrict__ kvec, const C64* __restrict__ S, C64* __restrict__ z) {
   const int s = blockIdx.y;
-  const int k = kvec[s], l = lvec[s];
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= k) return;
-  const C64* Ss = S + (size_t)s * ld * ld;
-  C64 acc = mk(0.0, 0.0);
-  if (nested) {
-    const C64* V = Vl + (size_t)s * kmax * ld;
-    for (int c = 0; c < l; ++c) acc = acc + cmul(V[(size_t)c * k + r], Ss[(size_t)c * ld]);
-  } else {
-    acc = Ss[(size_t)r * ld];
-  }
-  z[(size_t)s * kmax + r] = acc;
+  if (r < kvec[s]) z[(size_t)s * kmax + r] = S[(size_t)s * ld * ld + (size_t)r * ld];
 }
 
 // lc_j = ||x|| z_j sv_j per source (||x|| = 1 / sv_0)
@@ -672,21 +661,13 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
     }
   }
   // small problems: one inner projection per source, one batched Roberts-Higham
-  std::vector<C64> hab((size_t)r * 3 * ld, mk(0.0, 0.0));
   if (nested) {
-    std::vector<const C64*> pa(r), pb(r), pd(r);
     std::vector<int> ls(r);
-    for (int s = 0; s < r; ++s) {
-      pa[s] = a.alpha + (size_t)s * k;
-      pb[s] = a.beta + (size_t)s * k;
-      pd[s] = a.delta + (size_t)s * k;
-      ls[s] = std::min(ell[s], kus[s]);
-    }
-    const int e = small_inner_batch(r, kus.data(), ls.data(), 0, pa.data(), pb.data(), pd.data(), hab.data(), ld, Vl,
+    for (int s = 0; s < r; ++s) ls[s] = std::min(ell[s], kus[s]);
+    const int e = small_inner_batch(r, kus.data(), ls.data(), 0, a.alpha, a.beta, a.delta, k, abd, ld, Vl,
                                     (size_t)k * ld, lus.data(), st);
     if (e < 0) return e;
     if (e > 0 && warn == NK_OK) warn = e;
-    NK_HIP(hipMemcpyAsync(abd, hab.data(), hab.size() * sizeof(C64), hipMemcpyHostToDevice, st));
   } else {
     for (int s = 0; s < r; ++s) {
       lus[s] = kus[s];
@@ -707,7 +688,10 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
                                   st, &tri);
   if (erh < 0) return erh;
   if (erh > 0 && warn == NK_OK) warn = erh;
-  hipLaunchKernelGGL(k_bz, dim3((k + 255) / 256, r), dim3(256), 0, st, k, ld, kv, lv, nested, Vl, S, z);
+  if (nested)
+    small_lift_batch(r, k, kv, lv, Vl, (size_t)k * ld, S, ld, z, k, st);
+  else
+    hipLaunchKernelGGL(k_bz, dim3((k + 255) / 256, r), dim3(256), 0, st, k, ld, kv, S, z);
   NK_HIP(hipGetLastError());
   NK_HIP(hipEventRecord(ev[2], st));
   // lift

@@ -341,10 +341,14 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
                    int rh_scaling, int rh_maxit, double rh_tol, C64* z, SmallOut* out, hipStream_t st,
                    int inner = NK_INNER_SAME);
 
-// the inner projections of r problems at once (see small.hip)
-int small_inner_batch(int r, const int* k, const int* ell, int hermitian, const C64* const* alpha,
-                      const C64* const* beta, const C64* const* delta, C64* hl_host, int ldh, C64* vl_dev,
-                      size_t vl_stride, int* ell_used, hipStream_t st);
+// the inner projections of r problems at once: problem s has its H_k at
+// alpha/beta/delta + s * cstride (see small.hip)
+int small_inner_batch(int r, const int* k, const int* ell, int hermitian, const C64* alpha, const C64* beta,
+                      const C64* delta, size_t cstride, C64* hl_dev, int ldh, C64* vl_dev, size_t vl_stride,
+                      int* ell_used, hipStream_t st);
+// z_s = V_s (first column of S_s) for every source s (kv, lv on the device)
+void small_lift_batch(int r, int kmax, const int* kv, const int* lv, const C64* V, size_t vstride, const C64* S,
+                      int ld, C64* z, int zstride, hipStream_t st);
 
 // rh.hip -- batched Roberts-Higham on dense matrices (S on the device, row-major,
 // matrix b at b * ld * ld)

@@ -18,12 +18,47 @@
 
 #include "hostbuf.h"
 #include "nk_internal.h"
+#include "wave.h"
 
 namespace nk {
 
-constexpr int ST = 256;
+constexpr int LMAX = 512;  // largest inner size (LDS of k_in_sub)
+
+// one inner problem
+struct Inner {
+  int k, herm, lmax;
+  const C64 *al, *be, *de;  // H_k: diagonal, super- and sub-diagonal
+  C64 *Lm, *U0i, *U1, *U2;  // its elimination
+  int* Sw;
+  int* out;      // host memory: receives the two flags at the last step
+  C64* B;
+  C64* BH;
+  C64* V;
+  C64* W;
+  C64* uraw[2];  // ping-pong raw vectors (u side)
+  C64* qraw[2];  // (q side)
+  C64* part1;    // [2][nb1][lmax] partial projections from k_in_gemv
+  C64* part2;    // [2][nb2][lmax] second-pass partial projections
+  double* part3; // [4][nb2] normalisation partial sums
+  int nb1, nb2;
+  C64* a;
+  C64* b;
+  C64* d;
+  int* flags;
+  C64* hcol;     // [lmax][lmax] Arnoldi: column i of H_l at i * lmax (both passes summed)
+  int arnoldi;   // 1: one-sided recurrence on a general B, every coefficient kept
+};
 
 __device__ __forceinline__ double cabs1s(C64 a) { return fabs(a.re) + fabs(a.im); }
+// a b with the two ways to round the imaginary part
+__device__ __forceinline__ C64 cmul_a(C64 a, C64 b) {
+  return mk(fma(a.re, b.re, -(a.im * b.im)), fma(a.im, b.re, a.re * b.im));
+}
+__device__ __forceinline__ C64 cmul_b(C64 a, C64 b) {
+  return mk(fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re));
+}
+// c ? a : b by component (a select of two structs goes through scratch memory)
+__device__ __forceinline__ C64 csel(bool c, C64 a, C64 b) { return mk(c ? a.re : b.re, c ? a.im : b.im); }
 // 1 / b = conj(b) / |b|^2 with b first scaled by a power of two (exact) so
 // that |b|^2 neither overflows nor underflows: one division on the
 // recurrence's critical path instead of cdiv's four
@@ -45,72 +80,202 @@ __device__ __forceinline__ C64 cdiv(C64 a, C64 b) {
 // sub delta).  Row i of U holds 1/U0i[i], U1[i], U2[i] on columns i, i+1, i+2;
 // Lm[i] is the multiplier that eliminates column i of the row below the
 // pivot row; Sw[i] says whether rows i and i+1 were exchanged.  The
-// elimination is sequential (one thread); the coefficients are first staged
-// in LDS by the whole block so the loop does not wait on global memory.
+// elimination is sequential (one thread) and bound by the latency of its
+// dependent operations; the coefficients are first staged in LDS by the whole
+// block and read a step ahead.  Up to TRI_REC_MAX the reciprocals of the
+// sub-diagonal are staged too, which are the pivots' wherever rows are
+// exchanged, and the results take the places of the consumed coefficients
+// until the whole block writes them out.  Measured at k = 500: 98 us, 128 us
+// with crecip on the chain and the coefficients of a step read in that step.
 constexpr int TRI_LDS_MAX = 1365;  // 3 k complex in LDS (<= 64 KB of dynamic LDS)
+constexpr int TRI_REC_MAX = 960;   // 4 k complex and k int
 
-// the sequential elimination, with the coefficients read through al/be/de
+// where the factors go
+struct TriLu {
+  gp<C64> Lm, U0i, U1, U2;
+  gp<int> Sw;
+};
+
+// The sequential elimination, with the coefficients read through al/be/de
 // (LDS or global: one instantiation each, so every access has its own
-// address space)
+// address space).  The products are rounded in a fixed order (the other one in
+// a1's imaginary part): the inner recurrence can amplify a last bit of
+// H^{-1}.  Returns 1 if a pivot vanishes.
 template <class P>
-__device__ __forceinline__ void tri_lu_seq(int k, P al, P be, P de, C64* __restrict__ Lm, int* __restrict__ Sw,
-                                           C64* __restrict__ U0i, C64* __restrict__ U1, C64* __restrict__ U2,
-                                           int* __restrict__ sing) {
+__device__ __forceinline__ int tri_lu_seq(int k, P al, P be, P de, const TriLu& o) {
   const C64 z = mk(0.0, 0.0);
   C64 a0 = ldg(al), a1 = k > 1 ? ldg(be) : z, a2 = z;
   int bad = 0;
   for (int i = 0; i + 1 < k; ++i) {
     const C64 b0 = ldg(de + i), b1 = ldg(al + i + 1), b2 = (i + 2 < k) ? ldg(be + i + 1) : z;
     const bool sw = cabs1s(a0) < cabs1s(b0);
-    const C64 p0 = sw ? b0 : a0, p1 = sw ? b1 : a1, p2 = sw ? b2 : a2;
-    const C64 o0 = sw ? a0 : b0, o1 = sw ? a1 : b1, o2 = sw ? a2 : b2;
+    const C64 p0 = csel(sw, b0, a0), p1 = csel(sw, b1, a1), p2 = csel(sw, b2, a2);
+    const C64 o0 = csel(sw, a0, b0), o1 = csel(sw, a1, b1), o2 = csel(sw, a2, b2);
     if (!(cabs1s(p0) > 0.0)) bad = 1;
     const C64 inv = crecip(p0);
-    const C64 m = cmul(o0, inv);
-    U0i[i] = inv;
-    U1[i] = p1;
-    U2[i] = p2;
-    Lm[i] = m;
-    Sw[i] = sw ? 1 : 0;
-    a0 = o1 - cmul(m, p1);
-    a1 = o2 - cmul(m, p2);
+    const C64 m = cmul_a(o0, inv);
+    stg(o.U0i + i, inv);
+    stg(o.U1 + i, p1);
+    stg(o.U2 + i, p2);
+    stg(o.Lm + i, m);
+    o.Sw[i] = sw ? 1 : 0;
+    a0 = o1 - cmul_a(m, p1);
+    a1 = o2 - cmul_b(m, p2);
     a2 = z;
   }
   if (!(cabs1s(a0) > 0.0)) bad = 1;
-  U0i[k - 1] = crecip(a0);
-  U1[k - 1] = z;
-  U2[k - 1] = z;
-  if (k >= 2) U2[k - 2] = z;
-  *sing = bad;
+  stg(o.U0i + k - 1, crecip(a0));
+  stg(o.U1 + k - 1, z);
+  stg(o.U2 + k - 1, z);
+  if (k >= 2) stg(o.U2 + k - 2, z);
+  return bad;
 }
 
-__global__ void __launch_bounds__(256) k_tri_lu(int k, const C64* __restrict__ alpha, const C64* __restrict__ beta,
-                                                const C64* __restrict__ delta, C64* __restrict__ Lm,
-                                                int* __restrict__ Sw, C64* __restrict__ U0i, C64* __restrict__ U1,
-                                                C64* __restrict__ U2, int* __restrict__ sing) {
+// The same in LDS, with the same bits, for pivots between 2^-200 and 2^200
+// (returns 2, with nothing else of use, if one is not).  sm holds al, be, de,
+// the reciprocals of de (k each, zeros past the end of be and de); the
+// factors of step i take the places of the coefficients that it consumes: U0i
+// al[i], U1 be[i], U2 de[i], Lm the reciprocal's, Sw behind them.  Bound by the
+// number of instructions and their latency: no selects (a branch per step,
+// whose two sides drop the products with the zero of row i), no scaling in
+// the reciprocal (exact, so it only guards the range); the coefficients of four
+// steps are read together, in the four before.
+__device__ __forceinline__ int tri_lu_mid(int k, C64* sm) {
+  C64 *s0 = sm, *s1 = sm + k, *s2 = sm + 2 * k, *s3 = sm + 3 * k;
+  int* ssw = reinterpret_cast<int*>(sm + 4 * k);
+  constexpr int NS = 4;  // steps whose coefficients are read together
+  struct Row {
+    C64 b0, b1, b2, rb;
+  };
+  Row c[NS], nx[NS];
+  auto fetch = [&](Row(&v)[NS], int i) {
+#pragma unroll
+    for (int r = 0; r < NS; ++r) {
+      const int j = min(i + r, k - 1), j1 = min(i + r + 1, k - 1);
+      v[r].b0 = s2[j];
+      v[r].b1 = s0[j1];
+      v[r].b2 = s1[j1];
+      v[r].rb = s3[j];
+    }
+  };
+  C64 a0 = s0[0], a1 = s1[0];
+  double lo = 1.0, hi = 1.0;  // the pivots' range
+  auto step = [&](int i, const Row& w) {
+    const C64 b0 = w.b0, b1 = w.b1, b2 = w.b2, rb = w.rb;
+    const double n = fma(a0.re, a0.re, a0.im * a0.im);
+    double y = __builtin_amdgcn_rcp(n);
+    y = fma(y, fma(-n, y, 1.0), y);
+    y = fma(y, fma(-n, y, 1.0), y);
+    y = fma(fma(-n, y, 1.0), y, y);
+    const double na = cabs1s(a0), nb = cabs1s(b0);
+    const double np = fmax(na, nb);
+    lo = fmin(lo, np);
+    hi = fmax(hi, np);
+    if (__builtin_amdgcn_ballot_w64(na < nb) != 0) {
+      const C64 m = cmul_a(a0, rb);
+      s0[i] = rb;
+      s1[i] = b1;
+      s2[i] = b2;
+      s3[i] = m;
+      ssw[i] = 1;
+      a0 = a1 - cmul_a(m, b1);
+      a1 = mk(0.0, 0.0) - cmul_b(m, b2);
+    } else {
+      const C64 inv = mk(a0.re * y, y * -a0.im);
+      const C64 m = cmul_a(b0, inv);
+      s0[i] = inv;
+      s1[i] = a1;
+      s2[i] = mk(0.0, 0.0);
+      s3[i] = m;
+      ssw[i] = 0;
+      a0 = b1 - cmul_a(m, a1);
+      a1 = b2;
+    }
+  };
+  fetch(c, 0);
+  int i = 0;
+  for (; i + NS < k; i += NS) {
+    fetch(nx, i + NS);
+#pragma unroll
+    for (int r = 0; r < NS; ++r) step(i + r, c[r]);
+#pragma unroll
+    for (int r = 0; r < NS; ++r) c[r] = nx[r];
+  }
+#pragma unroll
+  for (int r = 0; r < NS; ++r)
+    if (i + r + 1 < k) step(i + r, c[r]);
+  const double last = cabs1s(a0);
+  s0[k - 1] = crecip(a0);
+  s1[k - 1] = mk(0.0, 0.0);
+  s2[k - 1] = mk(0.0, 0.0);
+  if (k >= 2) s2[k - 2] = mk(0.0, 0.0);
+  if (!(lo > 0x1p-200 && hi < 0x1p200)) return 2;
+  return last > 0.0 ? 0 : 1;
+}
+
+// dynamic LDS for problems of order up to kmax
+static size_t tri_lu_lds(int kmax) {
+  const size_t r = std::min(kmax, TRI_REC_MAX) * (4 * sizeof(C64) + sizeof(int));
+  return kmax > TRI_REC_MAX ? std::max(r, std::min(kmax, TRI_LDS_MAX) * 3 * sizeof(C64)) : r;
+}
+
+// one workgroup per problem (s0 for one, SS for a batch); the state of the
+// inner recurrence starts here too
+__global__ void __launch_bounds__(256) k_tri_lu(const Inner s0, const Inner* __restrict__ SS) {
   extern __shared__ C64 sm[];
-  const bool lds = k <= TRI_LDS_MAX;
+  const Inner& s = SS ? SS[blockIdx.x] : s0;
+  const int k = s.k;
+  gp<const C64> alpha = as_global(s.al), beta = as_global(s.be), delta = as_global(s.de);
+  const C64 z = mk(0.0, 0.0);
+  for (int j = threadIdx.x; j < s.lmax; j += blockDim.x) {
+    stg(as_global(s.a) + j, z);
+    stg(as_global(s.b) + j, z);
+    stg(as_global(s.d) + j, z);
+  }
+  gp<int> flags = as_global(s.flags);
+  if (threadIdx.x == 0) flags[0] = 0;
+  const bool lds = k <= TRI_LDS_MAX, rec = k <= TRI_REC_MAX;
   if (lds) {
     for (int i = threadIdx.x; i < k; i += blockDim.x) {
-      sm[i] = alpha[i];
-      sm[k + i] = i + 1 < k ? beta[i] : mk(0.0, 0.0);
-      sm[2 * k + i] = i + 1 < k ? delta[i] : mk(0.0, 0.0);
+      const int p = i + 1 < k ? i : 0;
+      const C64 be = ldg(beta + p), dv = ldg(delta + p), de = csel(i + 1 < k, dv, z);
+      sm[i] = ldg(alpha + i);
+      sm[k + i] = csel(i + 1 < k, be, z);
+      sm[2 * k + i] = de;
+      if (rec) sm[3 * k + i] = crecip(de);
     }
     __syncthreads();
   }
-  if (threadIdx.x != 0) return;
-  if (lds)
-    tri_lu_seq(k, (const C64*)sm, (const C64*)sm + k, (const C64*)sm + 2 * k, Lm, Sw, U0i, U1, U2, sing);
-  else
-    tri_lu_seq(k, as_global(alpha), as_global(beta), as_global(delta), Lm, Sw, U0i, U1, U2, sing);
+  const C64* l = sm;
+  const TriLu o{as_global(s.Lm), as_global(s.U0i), as_global(s.U1), as_global(s.U2), as_global(s.Sw)};
+  __shared__ int s_bad;
+  if (threadIdx.x == 0) {
+    int bad = rec ? tri_lu_mid(k, sm) : 2;
+    s_bad = bad;
+    if (bad == 2)
+      bad = lds && !rec ? tri_lu_seq(k, l, l + k, l + 2 * k, o) : tri_lu_seq(k, alpha, beta, delta, o);
+    flags[1] = bad;
+  }
+  if (!rec) return;
+  __syncthreads();
+  if (s_bad == 2) return;
+  for (int i = threadIdx.x; i < k; i += blockDim.x) {
+    stg(o.U0i + i, sm[i]);
+    stg(o.U1 + i, sm[k + i]);
+    stg(o.U2 + i, sm[2 * k + i]);
+    stg(o.Lm + i, sm[3 * k + i]);
+    o.Sw[i] = reinterpret_cast<const int*>(sm + 4 * k)[i];
+  }
 }
 
 // column j of H^{-1} (solve H x = e_j), then B = H + H^{-1}; B row-major k x k.
 // The factors are staged in LDS when they fit.  The forward sweep of e_j is
-// zero before row j - 1, so it starts there.  The backward sweep reads eight
-// rows of the forward result ahead of the recurrence (rows below the one
-// being written, so the reads never see a row of this sweep), which keeps
-// eight loads in flight instead of one.
+// zero before row j - 1, so a wave starts before its first column.  The backward sweep reads eight
+// rows of the forward result at a time, sixteen rows ahead of the recurrence
+// at most (rows below the one being written, so the reads never see a row of
+// this sweep): their round trip passes behind the eight rows before.  Bound by
+// the latency of the 2 k dependent steps: k = 500 66 us (88 with a round trip
+// per eight rows and lanes that started at their own rows).
 struct TriF {
   C64 lm, u0i, u1, u2;
 };
@@ -121,15 +286,18 @@ __device__ __forceinline__ void tri_inv_col(int j, int k, const TriF* sf, const 
                                             gp<const int> Sw, gp<const C64> U0i, gp<const C64> U1,
                                             gp<const C64> U2, gp<C64> B) {
   const C64 z = mk(0.0, 0.0);
-  const int i0 = j > 0 ? j - 1 : 0;
+  // rows in step over the wave, from its first column's first nonzero row (the others hold zeros until theirs)
+  const int i0 = max((int)(blockIdx.x * 64) - 1, 0);
   for (int i = 0; i < i0; ++i) stg(B + (size_t)i * k + j, z);
-  C64 fc = (j == 0) ? mk(1.0, 0.0) : z;
-  for (int i = i0; i + 1 < k; ++i) {
-    const C64 fn = (i + 1 == j) ? mk(1.0, 0.0) : z;
+  C64 fc = mk(j == 0 ? 1.0 : 0.0, 0.0);
+#pragma unroll 8
+  for (int i = i0; i < k - 1; ++i) {
+    const C64 fn = mk(i + 1 == j ? 1.0 : 0.0, 0.0);
     const int sw = LDS ? ssw[i] : Sw[i];
-    const C64 piv = sw ? fn : fc, oth = sw ? fc : fn;
+    const C64 lm = LDS ? sf[i].lm : ldg(Lm + i);
+    const C64 piv = csel(sw, fn, fc), oth = csel(sw, fc, fn);
     stg(B + (size_t)i * k + j, piv);
-    fc = oth - cmul(LDS ? sf[i].lm : ldg(Lm + i), piv);
+    fc = oth - cmul(lm, piv);
   }
   stg(B + (size_t)(k - 1) * k + j, fc);
   C64 x1 = z, x2 = z;
@@ -141,30 +309,40 @@ __device__ __forceinline__ void tri_inv_col(int j, int k, const TriF* sf, const 
     x1 = xi;
   };
   int i = k - 1;
-  for (; i >= 7; i -= 8) {
-    C64 y[8];
+  C64 y[8], yn[8];
+  auto fetch = [&](C64(&v)[8], int i0) {  // rows i0 .. i0 - 7 (row 0 in the place of rows before it)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) y[u] = ldg(B + (size_t)(i - u) * k + j);
+    for (int u = 0; u < 8; ++u) v[u] = ldg(B + (size_t)max(i0 - u, 0) * k + j);
+  };
+  if (i >= 7) fetch(y, i);
+  for (; i >= 7; i -= 8) {
+    fetch(yn, i - 8);
 #pragma unroll
     for (int u = 0; u < 8; ++u) step(i - u, y[u]);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) y[u] = yn[u];
   }
   for (; i >= 0; --i) step(i, ldg(B + (size_t)i * k + j));
 }
 
-__global__ void __launch_bounds__(64) k_tri_inv(int k, const C64* __restrict__ Lm, const int* __restrict__ Sw,
-                                                const C64* __restrict__ U0i, const C64* __restrict__ U1,
-                                                const C64* __restrict__ U2, const C64* __restrict__ alpha,
-                                                const C64* __restrict__ beta, const C64* __restrict__ delta,
-                                                C64* __restrict__ B) {
+__global__ void __launch_bounds__(64) k_tri_inv(const Inner s0, const Inner* __restrict__ SS) {
   extern __shared__ TriF sf[];
+  const Inner& s = SS ? SS[blockIdx.z] : s0;
+  const int k = s.k;
+  if ((int)(blockIdx.x * blockDim.x) >= k) return;
+  gp<const C64> Lm = as_global((const C64*)s.Lm), U0i = as_global((const C64*)s.U0i),
+                U1 = as_global((const C64*)s.U1), U2 = as_global((const C64*)s.U2);
+  gp<const C64> alpha = as_global(s.al), beta = as_global(s.be), delta = as_global(s.de);
+  gp<const int> Sw = as_global((const int*)s.Sw);
+  gp<C64> B = as_global(s.B);
   int* ssw = reinterpret_cast<int*>(sf + (k <= TRI_INV_LDS_MAX ? k : 0));
   const bool lds = k <= TRI_INV_LDS_MAX;
   if (lds) {
     for (int i = threadIdx.x; i < k; i += blockDim.x) {
-      sf[i].lm = Lm[i];
-      sf[i].u0i = U0i[i];
-      sf[i].u1 = U1[i];
-      sf[i].u2 = U2[i];
+      sf[i].lm = ldg(Lm + i);
+      sf[i].u0i = ldg(U0i + i);
+      sf[i].u1 = ldg(U1 + i);
+      sf[i].u2 = ldg(U2 + i);
       ssw[i] = Sw[i];
     }
     __syncthreads();
@@ -172,28 +350,34 @@ __global__ void __launch_bounds__(64) k_tri_inv(int k, const C64* __restrict__ L
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= k) return;
   if (lds)
-    tri_inv_col<true>(j, k, sf, ssw, as_global(Lm), as_global(Sw), as_global(U0i), as_global(U1), as_global(U2),
-                      as_global(B));
+    tri_inv_col<true>(j, k, sf, ssw, Lm, Sw, U0i, U1, U2, B);
   else
-    tri_inv_col<false>(j, k, sf, ssw, as_global(Lm), as_global(Sw), as_global(U0i), as_global(U1), as_global(U2),
-                       as_global(B));
-  B[(size_t)j * k + j] = B[(size_t)j * k + j] + alpha[j];
-  if (j > 0) B[(size_t)(j - 1) * k + j] = B[(size_t)(j - 1) * k + j] + beta[j - 1];
-  if (j + 1 < k) B[(size_t)(j + 1) * k + j] = B[(size_t)(j + 1) * k + j] + delta[j];
+    tri_inv_col<false>(j, k, sf, ssw, Lm, Sw, U0i, U1, U2, B);
+  auto add = [&](int i, C64 h) {
+    gp<C64> o = B + (size_t)i * k + j;
+    stg(o, ldg(o) + h);
+  };
+  add(j, ldg(alpha + j));
+  if (j > 0) add(j - 1, ldg(beta + j - 1));
+  if (j + 1 < k) add(j + 1, ldg(delta + j));
 }
 
 // BH = B^dag (tiled transpose through LDS)
-__global__ void k_adjoint(int k, const C64* __restrict__ B, C64* __restrict__ BH) {
+__global__ void k_adjoint(const Inner s0, const Inner* __restrict__ SS) {
   __shared__ C64 t[32][33];
+  const Inner& s = SS ? SS[blockIdx.z] : s0;
+  const int k = s.k;
+  gp<const C64> B = as_global((const C64*)s.B);
+  gp<C64> BH = as_global(s.BH);
   const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
   for (int yy = threadIdx.y; yy < 32; yy += 8) {
     const int r = by + yy, c = bx + threadIdx.x;
-    if (r < k && c < k) t[yy][threadIdx.x] = B[(size_t)r * k + c];
+    if (r < k && c < k) t[yy][threadIdx.x] = ldg(B + (size_t)r * k + c);
   }
   __syncthreads();
   for (int yy = threadIdx.y; yy < 32; yy += 8) {
     const int r = bx + yy, c = by + threadIdx.x;
-    if (r < k && c < k) BH[(size_t)r * k + c] = conj(t[threadIdx.x][yy]);
+    if (r < k && c < k) stg(BH + (size_t)r * k + c, conj(t[threadIdx.x][yy]));
   }
 }
 
@@ -225,28 +409,7 @@ __global__ void k_tri_dense(int k, const C64* __restrict__ alpha, const C64* __r
 // Arnoldi: the one-sided form on a general B, with every projection
 // coefficient kept (column i of the Hessenberg H_l, both passes summed).
 constexpr int GR = 16;  // rows per k_in_gemv block (one wave each, 1024 threads)
-constexpr int LMAX = 512;  // largest inner size (LDS of k_in_sub)
 constexpr int SR = 32;  // rows per k_in_sub block (eight lanes each)
-
-struct Inner {
-  int k, herm, lmax;
-  const C64* B;
-  const C64* BH;
-  C64* V;
-  C64* W;
-  C64* uraw[2];  // ping-pong raw vectors (u side)
-  C64* qraw[2];  // (q side)
-  C64* part1;    // [2][nb1][lmax] partial projections from k_in_gemv
-  C64* part2;    // [2][nb2][lmax] second-pass partial projections
-  double* part3; // [4][nb2] normalisation partial sums
-  int nb1, nb2;
-  C64* a;
-  C64* b;
-  C64* d;
-  int* flags;
-  C64* hcol;     // [lmax][lmax] Arnoldi: column i of H_l at i * lmax (both passes summed)
-  int arnoldi;   // 1: one-sided recurrence on a general B, every coefficient kept
-};
 
 // the descriptor with its buffers seen as global memory (see as_global)
 struct InnerG {
@@ -288,11 +451,11 @@ __device__ __forceinline__ InnerG inner_view(const Inner& s) {
 
 // The descriptor of this block's problem: a kernel argument (read straight
 // from the kernel-argument segment, one round trip less) for a single
-// problem, entry blockIdx.z of a device array for a batch.
+// problem, entry z of a device array for a batch.
 template <bool BATCH>
-__device__ __forceinline__ const Inner& inner_desc(const Inner& s0, const Inner* SS) {
+__device__ __forceinline__ const Inner& inner_desc(const Inner& s0, const Inner* SS, int z) {
   if constexpr (BATCH)
-    return SS[blockIdx.z];
+    return SS[z];
   else
     return s0;
 }
@@ -312,54 +475,52 @@ __device__ __forceinline__ gp<C64> rawv(const InnerG& g, int q, int h) {
   return pick(q != 0, pick(h != 0, g.q1, g.q0), pick(h != 0, g.u1, g.u0));
 }
 
+// the sums of nb partial sums, thread t holding partial t (and t + NTH, ..):
+// the waves' sums in a fixed order; when only the first wave holds any
+// (nb <= 64), that wave alone reduces and shares them, which gives the same
+// sums (the other waves would add zeros)
 template <int NTH>
-__device__ __forceinline__ void bsum(double (&v)[4]) {
+__device__ __forceinline__ void bsum_first(double (&v)[4], int nb) {
   __shared__ double sh[4][NTH / 64];
+  const int nw = nb > 64 ? NTH / 64 : 1;
+  if (threadIdx.x < 64 * nw)
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) sh[q][threadIdx.x >> 6] = v[q];
+    for (int q = 0; q < 4; ++q) {
+      v[q] = wave_xsum(v[q]);
+      if ((threadIdx.x & 63) == 0) sh[q][threadIdx.x >> 6] = v[q];
+    }
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < NTH / 64; ++w) t += sh[q][w];
+    for (int w = 0; w < nw; ++w) t += sh[q][w];
     v[q] = t;
   }
 }
 
-// bsum when only the first wave holds nonzero terms (nb <= 64 partial sums,
-// thread t holding partial t): that wave alone reduces and shares the sums,
-// which equal bsum's (the other waves would add zeros)
-template <int NTH>
-__device__ __forceinline__ void bsum_first(double (&v)[4], int nb) {
-  if (nb > 64) {
-    bsum<NTH>(v);
-    return;
+// workgroup -> (problem, workgroup of the problem).  A batch of eight or more
+// deals its problems to the eight XCDs (workgroups go round the XCDs in launch
+// order), so that what the workgroups of a problem share, and its B from one
+// step to the next, sits in one L2.
+template <bool BATCH>
+__device__ __forceinline__ void inner_place(int r, int nbmax, int* z, int* x) {
+  if (!BATCH) {
+    *z = 0;
+    *x = blockIdx.x;
+  } else if (r < 8) {
+    *z = blockIdx.x / nbmax;
+    *x = blockIdx.x % nbmax;
+  } else {
+    const int slot = blockIdx.x >> 3;
+    *z = (blockIdx.x & 7) + 8 * (slot / nbmax);
+    *x = slot % nbmax;
   }
-  __shared__ double sh1[4];
-  if (threadIdx.x < 64) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
-    if (threadIdx.x == 0)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sh1[q] = v[q];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = sh1[q];
 }
+static int inner_grid(int r, int nbmax) { return r < 8 ? r * nbmax : 8 * nbmax * ((r + 7) / 8); }
 
-// Every inner kernel serves a batch of independent problems: problem
-// blockIdx.z is SS[blockIdx.z]; the grid is sized for the largest, and a
-// workgroup beyond its own problem's size or steps returns at once.
+// Every inner kernel serves a batch of independent problems: problem z is
+// SS[z]; the grid is sized for the largest, and a workgroup beyond its own
+// problem's size or steps returns at once.
 // Everything a block loads except the normalisation scale is known at launch
 // (the row of B, the previous raw vector, the old basis entry and the
 // projection columns), so it is all issued before the partial sums of the
@@ -370,17 +531,22 @@ __device__ __forceinline__ void bsum_first(double (&v)[4], int nb) {
 constexpr int GP = 2;  // projection columns per lane loaded at launch (j < 128)
 
 template <bool BATCH>
-__global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner* __restrict__ SS, int i) {
+__global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner* __restrict__ SS, int nprob,
+                                                     int nbmax, int i) {
   extern __shared__ C64 s_p[];  // [GR][i + 1] per-row projection products
-  const Inner& S = inner_desc<BATCH>(s0, SS);
+  int z, blk;
+  inner_place<BATCH>(nprob, nbmax, &z, &blk);
+  if (BATCH && z >= nprob) return;
+  const Inner& S = inner_desc<BATCH>(s0, SS, z);
   const InnerG s = inner_view(S);
+  const int side = BATCH ? blk >= s.nb1 : blockIdx.y;  // 0: u = B v, 1: q = B^dag w
+  if (BATCH) blk -= side ? s.nb1 : 0;
   // a batch launch covers the largest problem; a single problem is launched
   // for exactly its own steps and blocks
-  if (BATCH && (i >= s.lmax || (int)blockIdx.x >= s.nb1)) return;
+  if (BATCH && (i >= s.lmax || blk >= s.nb1 || (side && s.herm))) return;
   const int k = s.k;
-  const int side = blockIdx.y;  // 0: u = B v, 1: q = B^dag w
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = blockIdx.x * GR + wave;
+  const int r = blk * GR + wave;
   const bool live = r < k;
   const int rs = live ? r : 0;  // rows past k load row 0 and discard it
   // the side-dependent pointers come straight from the descriptor: selected
@@ -428,18 +594,18 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
   if (i > 0) {
     bsum_first<GR * 64>(v, s.nb2);
     const C64 sd = s.herm ? mk(v[2], 0.0) : mk(v[0], v[1]);
-    const double sabs = sqrt(norm2(sd));
+    const double sabs = sqrt(fma(sd.re, sd.re, sd.im * sd.im));  // (rounded in this order in every build)
     if (!(sabs > 1e-14 * sqrt(v[2] * (s.herm ? v[2] : v[3])))) {
-      if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) s.flags[0] = i;
+      if (blk == 0 && side == 0 && threadIdx.x == 0) s.flags[0] = i;
       return;
     }
     const double delta = sqrt(sabs);
     const C64 beta = (1.0 / delta) * sd;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    if (blk == 0 && side == 0 && threadIdx.x == 0) {
       stg(s.b + (i - 1), beta);
       stg(s.d + (i - 1), mk(delta, 0.0));
     }
-    const C64 sv = mk(1.0 / delta, 0.0), sw = (1.0 / norm2(beta)) * beta;  // v = u / delta, w = q / conj(beta)
+    const C64 sv = mk(1.0 / delta, 0.0), sw = (1.0 / fma(beta.re, beta.re, beta.im * beta.im)) * beta;  // v = u / delta, w = q / conj(beta)
     scal = side ? sw : sv;
     scal_o = side ? sv : sw;
     sub = side ? mk(delta, 0.0) : beta;
@@ -468,11 +634,7 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
     madd(c0);
   }
   C64 acc = (ac[0] + ac[1]) + (ac[2] + ac[3]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    acc.re += __shfl_xor(acc.re, o, 64);
-    acc.im += __shfl_xor(acc.im, o, 64);
-  }
+  acc = mk(wave_xsum(acc.re), wave_xsum(acc.im));
   const C64 xr = (i > 0) ? cmul(scal, xr_raw) : mk(r == 0 ? 1.0 : 0.0, 0.0);  // v_i (or w_i) at row r
   if (i > 0) acc = acc - cmul(sub, vold);
   if (live && lane == 0) {
@@ -497,12 +659,12 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
     }
   }
   __syncthreads();
-  gp<C64> out = s.part1 + ((size_t)side * s.nb1 + blockIdx.x) * s.lmax;
+  gp<C64> out = s.part1 + ((size_t)side * s.nb1 + blk) * s.lmax;
   for (int j = threadIdx.x; j < ncol; j += GR * 64) {
     C64 t = mk(0.0, 0.0);
 #pragma unroll
     for (int w = 0; w < GR; ++w)
-      if (blockIdx.x * GR + w < k) t = t + s_p[w * ncol + j];
+      if (blk * GR + w < k) t = t + s_p[w * ncol + j];
     stg(out + j, t);
   }
 }
@@ -513,16 +675,26 @@ static size_t gemv_lds(int i) { return (size_t)GR * (i + 1) * sizeof(C64); }
 
 // pass 1 (last == 0): reduce part1, subtract, emit part2;
 // pass 2 (last == 1): reduce part2, subtract, emit the normalisation sums.
-// Every phase issues its loads in one batch per thread: the partial-sum and
-// projection phases give each (side, column) four consecutive lanes that
-// split the terms and meet by shuffles; the subtraction handles both sides
-// in the same batch.
+// The partial-sum and projection phases give each (side, column) four
+// consecutive lanes that split the terms and meet by DPP; the subtraction has
+// a half of the workgroup per side, eight lanes per row.  What the three
+// phases load of the partial sums and the bases (up to 64 columns) is known at
+// launch and issued together: one memory round trip instead of three.
+// Bound by the launch and that round trip: 5.2 us at k = 500 (6.5 when each
+// phase loaded for itself), 6.2 us for 16 problems of k = 300 (8.9).
+constexpr int ST = 512;
 constexpr int TPJ = 4;  // lanes per (side, column) in the reduction phases
 
 template <bool BATCH>
-__global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __restrict__ SS, int i, int last) {
-  const InnerG s = inner_view(inner_desc<BATCH>(s0, SS));
-  if (BATCH && (i >= s.lmax || (last && i + 1 >= s.lmax) || (int)blockIdx.x >= s.nb2)) return;
+__global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __restrict__ SS, int nprob, int nbmax,
+                                               int i, int last) {
+  int z, blk;
+  inner_place<BATCH>(nprob, nbmax, &z, &blk);
+  if (BATCH && z >= nprob) return;
+  const Inner& S = inner_desc<BATCH>(s0, SS, z);
+  const InnerG s = inner_view(S);
+  const bool report = blk == 0 && threadIdx.x == 0 && !last && i + 1 >= s.lmax;  // the problem's last launch
+  if (BATCH && (i >= s.lmax || (last && i + 1 >= s.lmax) || blk >= s.nb2)) return;
   const int k = s.k;
   const int sides = s.herm ? 1 : 2;
   __shared__ C64 s_c[2][LMAX];
@@ -531,20 +703,62 @@ __global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __re
   const int nbin = pick(last != 0, s.nb2, s.nb1);
   const int ncol = i + 1;
   const int l4 = threadIdx.x & (TPJ - 1);
-  // reduce the partial projections: item = (side, j), TPJ lanes each
-  for (int it0 = 0; it0 < sides * ncol; it0 += ST / TPJ) {
-    const int item = it0 + (int)threadIdx.x / TPJ;
-    const bool ok = item < sides * ncol;
-    const int side = ok ? item / ncol : 0, j = ok ? item % ncol : 0;
+  constexpr int NIT = ST / TPJ;  // items per sweep over the workgroup
+  const int it1 = (int)threadIdx.x / TPJ;
+  // item -> (side, column); past the end: (0, 0)
+  auto item = [&](int it, int* side, int* j) {
+    const bool ok = it < sides * ncol;
+    *side = ok && it >= ncol ? 1 : 0;
+    *j = ok ? it - *side * ncol : 0;
+    return ok;
+  };
+  // this thread's side, row and columns in the subtraction
+  const int side2 = (int)threadIdx.x / (ST / 2), rl = ((int)threadIdx.x & (ST / 2 - 1)) >> 3, jl = threadIdx.x & 7;
+  const int r = blk * SR + rl, rs = r < k ? r : 0;
+  const bool mine = side2 < sides;
+  const int nr = min(SR, k - blk * SR);  // rows of this block (s_u is zero past them)
+  // --- loads known at launch: the first sweep's partial sums, the first 64
+  // columns of the subtraction, the first sweep's columns of the projections
+  C64 pv[8], bv[8], qv[8];
+  int side1, j1;
+  const bool ok1 = item(it1, &side1, &j1);
+  auto load_part = [&](int side, int j, int bb0) {
     gp<const C64> pp = pin + (size_t)side * nbin * s.lmax + j;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int bb = bb0 + u * TPJ;
+      pv[u] = ldg(pp + (size_t)(bb < nbin ? bb : 0) * s.lmax);
+    }
+  };
+  gp<const C64> basis = side2 ? s.W : s.V;
+  auto load_basis = [&](int j0) {
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int j = j0 + 8 * m;
+      bv[m] = ldg(basis + (size_t)(j <= i ? j : 0) * k + rs);
+    }
+  };
+  auto load_proj = [&](int side, int j) {
+    gp<const C64> pj = (s.herm || side ? s.V : s.W) + (size_t)j * k + blk * SR;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int w = l4 + m * TPJ;
+      qv[m] = ldg(pj + (w < nr ? w : 0));
+    }
+  };
+  static_assert(SR == 8 * TPJ, "one batch of loads covers the block's rows");
+  load_part(side1, j1, l4);
+  load_basis(jl);
+  gp<C64> x = rawv(s, side2, (i + 1) & 1);
+  const C64 xr = ldg(x + rs);
+  if (!last) load_proj(side1, j1);
+  // reduce the partial projections: item = (side, j), TPJ lanes each
+  for (int it0 = 0; it0 < sides * ncol; it0 += NIT) {
+    int side, j;
+    const bool ok = it0 == 0 ? (side = side1, j = j1, ok1) : item(it0 + it1, &side, &j);
     C64 t0 = mk(0.0, 0.0), t1 = t0;
     for (int bb0 = l4; bb0 < nbin; bb0 += 8 * TPJ) {
-      C64 pv[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int bb = bb0 + u * TPJ;
-        pv[u] = ldg(pp + (size_t)(bb < nbin ? bb : 0) * s.lmax);
-      }
+      if (it0 > 0 || bb0 > l4) load_part(side, j, bb0);
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         if (bb0 + u * TPJ < nbin) {
@@ -555,108 +769,71 @@ __global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __re
         }
     }
     C64 t = t0 + t1;
-#pragma unroll
-    for (int o = 1; o < TPJ; o <<= 1) {
-      t.re += __shfl_xor(t.re, o, 64);
-      t.im += __shfl_xor(t.im, o, 64);
-    }
+    t = mk(quad_xsum(t.re), quad_xsum(t.im));
     if (ok && l4 == 0) s_c[side][j] = t;
   }
   // a breakdown flagged at this or an earlier step ends the iteration; the
   // flag is read only now so that its latency overlaps the loads above (all
   // in bounds)
+  if (report) {
+    gp<int> o = as_global(S.out);
+    o[0] = s.flags[0];
+    o[1] = s.flags[1];
+  }
   if (s.flags[0]) return;
   __syncthreads();
-  if (!last && blockIdx.x == 0 && threadIdx.x == 0) stg(s.a + i, s.herm ? mk(s_c[0][i].re, 0.0) : s_c[0][i]);
-  if (s.arnoldi && blockIdx.x == 0)  // column i of H_l: the first pass stores, the second adds
+  if (!last && blk == 0 && threadIdx.x == 0) stg(s.a + i, s.herm ? mk(s_c[0][i].re, 0.0) : s_c[0][i]);
+  if (s.arnoldi && blk == 0)  // column i of H_l: the first pass stores, the second adds
     for (int j = threadIdx.x; j <= i; j += ST) {
       gp<C64> h = s.hcol + (size_t)i * s.lmax + j;
       stg(h, last ? ldg(h) + s_c[0][j] : s_c[0][j]);
     }
-  // u -= V c, q -= W d: eight lanes per row, columns jl, jl + 8, ... of both
-  // sides in one batch of loads
-  const int rl = threadIdx.x >> 3, jl = threadIdx.x & 7;
-  const int r = blockIdx.x * SR + rl;
-  gp<C64> u = rawv(s, 0, (i + 1) & 1);
-  gp<C64> q = rawv(s, 1, (i + 1) & 1);
-  C64 acc[2][2] = {{mk(0.0, 0.0), mk(0.0, 0.0)}, {mk(0.0, 0.0), mk(0.0, 0.0)}};
-  if (r < k) {
+  // u -= V c, q -= W d: eight lanes per row, columns jl, jl + 8, ...
+  C64 acc[2] = {mk(0.0, 0.0), mk(0.0, 0.0)};
+  if (mine && r < k)
     for (int j0 = jl; j0 <= i; j0 += 8 * 8) {
-      C64 bv[2][8];
+      if (j0 > jl) load_basis(j0);
 #pragma unroll
-      for (int side = 0; side < 2; ++side) {
-        gp<const C64> basis = side ? s.W : s.V;
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const int j = j0 + 8 * m;
-          bv[side][m] = (side < sides) ? ldg(basis + (size_t)(j <= i ? j : 0) * k + r) : mk(0.0, 0.0);
-        }
+      for (int m = 0; m < 8; ++m) {
+        const int j = j0 + 8 * m;
+        if (j <= i) acc[m & 1] = acc[m & 1] + cmul(bv[m], s_c[side2][j]);
       }
-#pragma unroll
-      for (int side = 0; side < 2; ++side)
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const int j = j0 + 8 * m;
-          if (side < sides && j <= i) acc[side][m & 1] = acc[side][m & 1] + cmul(bv[side][m], s_c[side][j]);
-        }
     }
-  }
-  for (int side = 0; side < sides; ++side) {
-    C64 a = acc[side][0] + acc[side][1];
-#pragma unroll
-    for (int o = 4; o > 0; o >>= 1) {
-      a.re += __shfl_xor(a.re, o, 64);
-      a.im += __shfl_xor(a.im, o, 64);
+  C64 a = acc[0] + acc[1];
+  a = mk(oct_xsum(a.re), oct_xsum(a.im));
+  if (mine && jl == 0) {
+    C64 nv = mk(0.0, 0.0);
+    if (r < k) {
+      nv = xr - a;
+      stg(x + r, nv);
     }
-    if (jl == 0) {
-      C64 nv = mk(0.0, 0.0);
-      if (r < k) {
-        gp<C64> x = side ? q : u;
-        nv = ldg(x + r) - a;
-        stg(x + r, nv);
-      }
-      s_u[side][rl] = nv;
-    }
+    s_u[side2][rl] = nv;
   }
   __syncthreads();
   if (!last) {
     // second-pass partial projections over this block's rows: item = (side, j)
-    const int nr = min(SR, k - blockIdx.x * SR);  // rows of this block (s_u is zero past them)
-    for (int it0 = 0; it0 < sides * ncol; it0 += ST / TPJ) {
-      const int item = it0 + (int)threadIdx.x / TPJ;
-      const bool ok = item < sides * ncol;
-      const int side = ok ? item / ncol : 0, j = ok ? item % ncol : 0;
-      gp<const C64> proj = pick(s.herm || side, s.V, s.W);
-      gp<const C64> pj = proj + (size_t)j * k + blockIdx.x * SR;
+    for (int it0 = 0; it0 < sides * ncol; it0 += NIT) {
+      int side, j;
+      const bool ok = it0 == 0 ? (side = side1, j = j1, ok1) : item(it0 + it1, &side, &j);
+      if (it0 > 0) load_proj(side, j);
       C64 t0 = mk(0.0, 0.0), t1 = t0;
-      for (int w0 = l4; w0 < nr; w0 += 8 * TPJ) {
-        C64 pv[8];
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const int w = w0 + m * TPJ;
-          pv[m] = ldg(pj + (w < nr ? w : 0));
-        }
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const int w = w0 + m * TPJ;
-          if (w < nr) {
-            if (m & 1)
-              t1 = t1 + cmulc(pv[m], s_u[side][w]);
-            else
-              t0 = t0 + cmulc(pv[m], s_u[side][w]);
-          }
+      for (int m = 0; m < 8; ++m) {
+        const int w = l4 + m * TPJ;
+        if (w < nr) {
+          if (m & 1)
+            t1 = t1 + cmulc(qv[m], s_u[side][w]);
+          else
+            t0 = t0 + cmulc(qv[m], s_u[side][w]);
         }
       }
       C64 t = t0 + t1;
-#pragma unroll
-      for (int o = 1; o < TPJ; o <<= 1) {
-        t.re += __shfl_xor(t.re, o, 64);
-        t.im += __shfl_xor(t.im, o, 64);
-      }
-      if (ok && l4 == 0) stg(s.part2 + ((size_t)side * s.nb2 + blockIdx.x) * s.lmax + j, t);
+      t = mk(quad_xsum(t.re), quad_xsum(t.im));
+      if (ok && l4 == 0) stg(s.part2 + ((size_t)side * s.nb2 + blk) * s.lmax + j, t);
     }
     return;
   }
+  if (threadIdx.x >= 64) return;
   double v[4] = {0, 0, 0, 0};
   if (threadIdx.x < SR) {
     const C64 un = s_u[0][threadIdx.x];
@@ -667,10 +844,11 @@ __global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __re
     v[2] = norm2(un);
     v[3] = norm2(qn);
   }
-  bsum<ST>(v);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = wave_xsum(v[q]);
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq) s.part3[qq * s.nb2 + blockIdx.x] = v[qq];
+    for (int q = 0; q < 4; ++q) s.part3[q * s.nb2 + blk] = v[q];
 }
 
 // dense upper Hessenberg H_l (ld = l, row-major) of the Arnoldi option.
@@ -691,14 +869,51 @@ __global__ void k_hess_dense(int l, int lmax, const C64* __restrict__ hcol, cons
   }
 }
 
-// z = V y (k rows, l columns)
-__global__ void k_in_lift(int k, int l, const C64* __restrict__ V, const C64* __restrict__ S, int lds,
-                          C64* __restrict__ z) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= k) return;
+// z = V y, y the first column of S (leading dimension ldy): 16 rows and 16
+// groups of columns per workgroup, every load of 256 B, eight in flight (one
+// thread per row waited for its l columns one after another)
+constexpr int LT = 256, LR = 16;
+__device__ __forceinline__ void lift_rows(int k, int l, const C64* __restrict__ V, const C64* __restrict__ y, int ldy,
+                                          C64* __restrict__ z) {
+  __shared__ C64 s_r[LT / 64][LR];
+  const int t = threadIdx.x, rr = t & 15, grp = t >> 4, r = blockIdx.x * LR + rr, rs = min(r, k - 1);
   C64 acc = mk(0.0, 0.0);
-  for (int j = 0; j < l; ++j) acc = acc + cmul(V[(size_t)j * k + r], S[(size_t)j * lds]);
-  z[r] = acc;
+  for (int j0 = grp; j0 < l; j0 += 8 * (LT / LR)) {
+    C64 v[8], c[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int j = min(j0 + m * (LT / LR), l - 1);
+      v[m] = V[(size_t)j * k + rs];
+      c[m] = y[(size_t)j * ldy];
+    }
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+      if (j0 + m * (LT / LR) < l) acc = acc + cmul(v[m], c[m]);
+  }
+#pragma unroll
+  for (int o = 16; o <= 32; o <<= 1) {
+    acc.re += __shfl_xor(acc.re, o, 64);
+    acc.im += __shfl_xor(acc.im, o, 64);
+  }
+  if ((t & 63) < LR) s_r[t >> 6][rr] = acc;
+  __syncthreads();
+  if (t < LR && r < k) z[r] = (s_r[0][rr] + s_r[1][rr]) + (s_r[2][rr] + s_r[3][rr]);
+}
+
+__global__ void __launch_bounds__(LT) k_in_lift(int k, int l, const C64* __restrict__ V, const C64* __restrict__ S,
+                                                int lds, C64* __restrict__ z) {
+  lift_rows(k, l, V, S, lds, z);
+}
+
+// the same for source blockIdx.y of a batch: order kv[s], lv[s] columns, its
+// basis, matrix and result at multiples of vstride, ld * ld and zstride
+__global__ void __launch_bounds__(LT) k_in_lift_batch(const int* __restrict__ kv, const int* __restrict__ lv,
+                                                      const C64* __restrict__ V, size_t vstride,
+                                                      const C64* __restrict__ S, int ld, C64* __restrict__ z,
+                                                      int zstride) {
+  const int s = blockIdx.y, k = kv[s];
+  if ((int)blockIdx.x * LR >= k) return;
+  lift_rows(k, lv[s], V + s * vstride, S + (size_t)s * ld * ld, ld, z + (size_t)s * zstride);
 }
 
 // z = column 0 of S (ld = k)
@@ -713,15 +928,11 @@ DevBuf g_small, g_batch;
 HostBuf g_small_pin;  // pinned readback of the inner iteration's flags
 }
 
-// device pointers of the tridiagonal factorisation of H_k
-struct TriWork {
-  C64 *Lm, *U0i, *U1, *U2;
-  int* Sw;
-};
-
 // workspace of one inner problem of order k with ell steps, carved from base
-// (base == nullptr: only the size); fills s and tw
-static size_t inner_layout(int k, int ell, int hermitian, char* base, Inner* s, TriWork* tw) {
+// (base == nullptr: only the size); fills s.  The basis V and H_l may live
+// elsewhere (vl, hl: diagonal, super- and sub-diagonal ldh apart).
+static size_t inner_layout(int k, int ell, int hermitian, char* base, Inner* s, C64* vl = nullptr, C64* hl = nullptr,
+                           int ldh = 0) {
   const int nb1 = (k + GR - 1) / GR, nb2 = (k + SR - 1) / SR;
   const size_t kk = (size_t)k * k;
   size_t bytes = 0;
@@ -732,10 +943,10 @@ static size_t inner_layout(int k, int ell, int hermitian, char* base, Inner* s, 
   };
   const size_t oB = take(kk * sizeof(C64));
   const size_t oBH = take(hermitian ? 0 : kk * sizeof(C64));
-  const size_t oV = take((size_t)k * ell * sizeof(C64));
+  const size_t oV = take(vl ? 0 : (size_t)k * ell * sizeof(C64));
   const size_t oW = take(hermitian ? 0 : (size_t)k * ell * sizeof(C64));
   const size_t oR = take((size_t)4 * k * sizeof(C64));
-  const size_t oF = take((size_t)5 * k * sizeof(C64) + (size_t)k * sizeof(int));
+  const size_t oF = take((size_t)4 * k * sizeof(C64) + (size_t)k * sizeof(int));
   const size_t oC = take((size_t)3 * ell * sizeof(C64));
   const size_t oP1 = take((size_t)2 * nb1 * ell * sizeof(C64));
   const size_t oP2 = take((size_t)2 * nb2 * ell * sizeof(C64));
@@ -748,7 +959,7 @@ static size_t inner_layout(int k, int ell, int hermitian, char* base, Inner* s, 
   s->lmax = ell;
   s->B = (C64*)(base + oB);
   s->BH = hermitian ? s->B : (C64*)(base + oBH);
-  s->V = (C64*)(base + oV);
+  s->V = vl ? vl : (C64*)(base + oV);
   s->W = hermitian ? s->V : (C64*)(base + oW);
   C64* R = (C64*)(base + oR);
   s->uraw[0] = R;
@@ -756,15 +967,18 @@ static size_t inner_layout(int k, int ell, int hermitian, char* base, Inner* s, 
   s->qraw[0] = R + 2 * k;
   s->qraw[1] = R + 3 * k;
   C64* F = (C64*)(base + oF);
-  tw->Lm = F;
-  tw->U0i = F + k;
-  tw->U1 = F + 2 * k;
-  tw->U2 = F + 3 * k;
-  tw->Sw = (int*)(F + 5 * k);
-  C64* Cc = (C64*)(base + oC);
-  s->a = Cc;
-  s->b = Cc + ell;
-  s->d = Cc + 2 * ell;
+  s->Lm = F;
+  s->U0i = F + k;
+  s->U1 = F + 2 * k;
+  s->U2 = F + 3 * k;
+  s->Sw = (int*)(F + 4 * k);
+  if (!hl) {
+    hl = (C64*)(base + oC);
+    ldh = ell;
+  }
+  s->a = hl;
+  s->b = hl + ldh;
+  s->d = hl + 2 * ldh;
   s->part1 = (C64*)(base + oP1);
   s->part2 = (C64*)(base + oP2);
   s->part3 = (double*)(base + oP3);
@@ -776,21 +990,24 @@ static size_t inner_layout(int k, int ell, int hermitian, char* base, Inner* s, 
   return bytes;
 }
 
-// B = H_k + H_k^{-1} (and B^dag) of one problem; clears its flags and b
-static int inner_prepare(int k, int hermitian, const C64* alpha, const C64* beta, const C64* delta, const Inner& s,
-                         const TriWork& tw, hipStream_t st) {
-  NK_HIP(hipMemsetAsync(s.flags, 0, 8 * sizeof(int), st));
-  NK_HIP(hipMemsetAsync(s.b, 0, 2 * s.lmax * sizeof(C64), st));
-  const size_t lds_lu = k <= TRI_LDS_MAX ? (size_t)3 * k * sizeof(C64) : 0;
-  const size_t lds_inv = k <= TRI_INV_LDS_MAX ? (size_t)k * (sizeof(TriF) + sizeof(int)) : 0;
-  hipLaunchKernelGGL(k_tri_lu, dim3(1), dim3(256), lds_lu, st, k, alpha, beta, delta, tw.Lm, tw.Sw, tw.U0i, tw.U1,
-                     tw.U2, s.flags + 1);
-  hipLaunchKernelGGL(k_tri_inv, dim3((k + 63) / 64), dim3(64), lds_inv, st, k, tw.Lm, tw.Sw, tw.U0i, tw.U1, tw.U2,
-                     alpha, beta, delta, (C64*)s.B);
-  if (!hermitian)
-    hipLaunchKernelGGL(k_adjoint, dim3((k + 31) / 32, (k + 31) / 32), dim3(32, 8), 0, st, k, s.B, (C64*)s.BH);
-  NK_HIP(hipGetLastError());
-  return NK_OK;
+// B = H_k + H_k^{-1} (and B^dag), then the inner iteration of r problems (one:
+// by value in s0; more: descriptors in device memory) of order up to kmax
+// with up to lmax steps: one launch per kernel and step serves all of them
+template <bool BATCH>
+static void inner_launch(int r, const Inner& s0, const Inner* SS, int oneside, int kmax, int lmax, hipStream_t st) {
+  const int kl = std::min(kmax, TRI_INV_LDS_MAX), kt = (kmax + 31) / 32;
+  hipLaunchKernelGGL(k_tri_lu, dim3(r), dim3(256), tri_lu_lds(kmax), st, s0, SS);
+  hipLaunchKernelGGL(k_tri_inv, dim3((kmax + 63) / 64, 1, r), dim3(64), (size_t)kl * (sizeof(TriF) + sizeof(int)), st,
+                     s0, SS);
+  if (!oneside) hipLaunchKernelGGL(k_adjoint, dim3(kt, kt, r), dim3(32, 8), 0, st, s0, SS);
+  const int sides = oneside ? 1 : 2, nb1 = (kmax + GR - 1) / GR, nb2 = (kmax + SR - 1) / SR;
+  const dim3 g1 = BATCH ? dim3(inner_grid(r, sides * nb1)) : dim3(nb1, sides);
+  const dim3 g2 = BATCH ? dim3(inner_grid(r, nb2)) : dim3(nb2);
+  for (int i = 0; i < lmax; ++i) {
+    hipLaunchKernelGGL(k_in_gemv<BATCH>, g1, dim3(GR * 64), gemv_lds(i), st, s0, SS, r, sides * nb1, i);
+    hipLaunchKernelGGL(k_in_sub<BATCH>, g2, dim3(ST), 0, st, s0, SS, r, nb2, i, 0);
+    if (i + 1 < lmax) hipLaunchKernelGGL(k_in_sub<BATCH>, g2, dim3(ST), 0, st, s0, SS, r, nb2, i, 1);
+  }
 }
 
 int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* beta, const C64* delta,
@@ -830,32 +1047,27 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
     set_error("inner Krylov size %d exceeds %d", ell, LMAX);
     return NK_EINVAL;
   }
-  const size_t lay = inner_layout(k, ell, oneside, nullptr, nullptr, nullptr);
-  const size_t oS = (lay + 255) & ~(size_t)255;
-  const size_t oD = oS + (((size_t)ell * ell * sizeof(C64) + 255) & ~(size_t)255);
-  if (g_small.ensure(oD) || g_small_pin.ensure(2 * sizeof(int))) return NK_ENOMEM;
+  const size_t lay = inner_layout(k, ell, oneside, nullptr, nullptr);
+  if (g_small.ensure(lay + (size_t)ell * ell * sizeof(C64)) || g_small_pin.ensure(2 * sizeof(int))) return NK_ENOMEM;
   char* base = g_small.as<char>();
-  Inner s;
-  TriWork tw;
-  inner_layout(k, ell, oneside, base, &s, &tw);
+  Inner s{};
+  inner_layout(k, ell, oneside, base, &s);
   s.arnoldi = arnoldi;
-  C64* Hl = (C64*)(base + oS);
-  if (int e = inner_prepare(k, oneside, alpha, beta, delta, s, tw, st)) return e;
-  const int sides = oneside ? 1 : 2;
-  for (int i = 0; i < ell; ++i) {
-    hipLaunchKernelGGL(k_in_gemv<false>, dim3(s.nb1, sides, 1), dim3(GR * 64), gemv_lds(i), st, s, nullptr, i);
-    hipLaunchKernelGGL(k_in_sub<false>, dim3(s.nb2, 1, 1), dim3(ST), 0, st, s, nullptr, i, 0);
-    if (i + 1 < ell) hipLaunchKernelGGL(k_in_sub<false>, dim3(s.nb2, 1, 1), dim3(ST), 0, st, s, nullptr, i, 1);
-  }
+  s.al = alpha;
+  s.be = beta;
+  s.de = delta;
+  s.out = g_small_pin.dev<int>();
+  C64* Hl = reinterpret_cast<C64*>(base + lay);
+  inner_launch<false>(1, s, nullptr, oneside, k, ell, st);
   NK_HIP(hipGetLastError());
-  int* fl = g_small_pin.host<int>();
-  NK_HIP(hipMemcpyAsync(fl, s.flags, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
   NK_HIP(hipStreamSynchronize(st));
+  const int* fl = g_small_pin.host<int>();
+  const int brk = fl[0];
   if (fl[1]) {
     set_error("nested small problem: H_k is singular");
     return NK_WARN_NOTCONV;
   }
-  const int lu = fl[0] ? fl[0] : ell;
+  const int lu = brk ? brk : ell;
   if (out && out->hl_host) {
     NK_HIP(hipMemcpyAsync(out->hl_host, s.a, lu * sizeof(C64), hipMemcpyDeviceToHost, st));
     NK_HIP(hipMemcpyAsync(out->hl_host + lu, s.b, lu * sizeof(C64), hipMemcpyDeviceToHost, st));
@@ -866,7 +1078,7 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
     NK_HIP(hipMemcpyAsync(out->vl_dev, s.V, (size_t)k * lu * sizeof(C64), hipMemcpyDeviceToDevice, st));
   if (out && out->inner_only) {
     out->ell_used = lu;
-    return fl[0] ? NK_WARN_BREAKDOWN : NK_OK;
+    return brk ? NK_WARN_BREAKDOWN : NK_OK;
   }
   if (arnoldi)
     hipLaunchKernelGGL(k_hess_dense, dim3(256), dim3(256), 0, st, lu, ell, s.hcol, s.b, s.d, Hl);
@@ -878,56 +1090,56 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
   const TriIn tri{s.a, s.b, s.d, 0};
   int e = rh_sign_batched(1, lu, &lu, Hl, rh_scaling, rh_maxit, rh_tol, &it, &res, st, arnoldi ? nullptr : &tri);
   if (e < 0) return e;
-  hipLaunchKernelGGL(k_in_lift, dim3((k + 255) / 256), dim3(256), 0, st, k, lu, s.V, Hl, lu, z);
+  hipLaunchKernelGGL(k_in_lift, dim3((k + LR - 1) / LR), dim3(LT), 0, st, k, lu, s.V, Hl, lu, z);
   NK_HIP(hipGetLastError());
   if (out) {
     out->rh_iters = it;
     out->ell_used = lu;
     out->rh_residual = res;
   }
-  return e ? e : (fl[0] ? NK_WARN_BREAKDOWN : NK_OK);
+  return e ? e : (brk ? NK_WARN_BREAKDOWN : NK_OK);
 }
 
 // The inner projections of r problems at once: one launch per kernel and
-// step serves all of them (grid z = problem).  Problem s has order k[s] and
-// ell[s] steps; its H_ell (diagonal, super-, sub-diagonal) goes to
-// hl_host + s * 3 * ldh (rows of ldh) and its basis V_ell (column j at
+// step serves all of them.  Problem s has order k[s] and ell[s] steps; its
+// H_ell (diagonal, super-, sub-diagonal, zero from its last step on) goes to
+// hl_dev + s * 3 * ldh (rows of ldh) and its basis V_ell (column j at
 // j * k[s]) to vl_dev + s * vl_stride; ell_used[s] < ell[s] after an
 // invariant subspace or a breakdown.
-int small_inner_batch(int r, const int* k, const int* ell, int hermitian, const C64* const* alpha,
-                      const C64* const* beta, const C64* const* delta, C64* hl_host, int ldh, C64* vl_dev,
-                      size_t vl_stride, int* ell_used, hipStream_t st) {
+int small_inner_batch(int r, const int* k, const int* ell, int hermitian, const C64* alpha, const C64* beta,
+                      const C64* delta, size_t cstride, C64* hl_dev, int ldh, C64* vl_dev, size_t vl_stride,
+                      int* ell_used, hipStream_t st) {
   std::vector<size_t> off(r + 1, 0);
   for (int s = 0; s < r; ++s) {
     if (ell[s] < 1 || ell[s] > LMAX || ell[s] > k[s] || ell[s] > ldh) {
       set_error("inner problem %d: ell = %d outside [1, min(k = %d, %d)]", s, ell[s], k[s], LMAX);
       return NK_EINVAL;
     }
-    off[s + 1] = off[s] + ((inner_layout(k[s], ell[s], hermitian, nullptr, nullptr, nullptr) + 255) & ~(size_t)255);
+    off[s + 1] = off[s] + inner_layout(k[s], ell[s], hermitian, nullptr, nullptr, vl_dev);
   }
-  if (g_batch.ensure(off[r] + (size_t)r * sizeof(Inner) + 256)) return NK_ENOMEM;
+  // descriptors: written to pinned memory, read by the kernels from the device's copy
+  const size_t dbytes = (size_t)r * sizeof(Inner);
+  if (g_batch.ensure(off[r] + dbytes) || g_small_pin.ensure(dbytes + (size_t)2 * r * sizeof(int))) return NK_ENOMEM;
   char* base = g_batch.as<char>();
-  std::vector<Inner> S(r);
-  std::vector<TriWork> tw(r);
-  int lmax = 0, nb1 = 0, nb2 = 0;
+  Inner* S = g_small_pin.host<Inner>();
+  int* fl = reinterpret_cast<int*>(g_small_pin.host<char>() + dbytes);
+  int* fl_dev = reinterpret_cast<int*>(g_small_pin.dev<char>() + dbytes);
+  int lmax = 0, kmax = 0;
   for (int s = 0; s < r; ++s) {
-    inner_layout(k[s], ell[s], hermitian, base + off[s], &S[s], &tw[s]);
-    if (int e = inner_prepare(k[s], hermitian, alpha[s], beta[s], delta[s], S[s], tw[s], st)) return e;
+    Inner in{};
+    inner_layout(k[s], ell[s], hermitian, base + off[s], &in, vl_dev + s * vl_stride, hl_dev + (size_t)s * 3 * ldh, ldh);
+    in.al = alpha + s * cstride;
+    in.be = beta + s * cstride;
+    in.de = delta + s * cstride;
+    in.out = fl_dev + 2 * s;
+    S[s] = in;
     lmax = std::max(lmax, ell[s]);
-    nb1 = std::max(nb1, S[s].nb1);
-    nb2 = std::max(nb2, S[s].nb2);
+    kmax = std::max(kmax, k[s]);
   }
-  Inner* sdev = (Inner*)(base + off[r]);
-  NK_HIP(hipMemcpyAsync(sdev, S.data(), r * sizeof(Inner), hipMemcpyHostToDevice, st));
-  const int sides = hermitian ? 1 : 2;
-  for (int i = 0; i < lmax; ++i) {
-    hipLaunchKernelGGL(k_in_gemv<true>, dim3(nb1, sides, r), dim3(GR * 64), gemv_lds(i), st, Inner{}, sdev, i);
-    hipLaunchKernelGGL(k_in_sub<true>, dim3(nb2, 1, r), dim3(ST), 0, st, Inner{}, sdev, i, 0);
-    if (i + 1 < lmax) hipLaunchKernelGGL(k_in_sub<true>, dim3(nb2, 1, r), dim3(ST), 0, st, Inner{}, sdev, i, 1);
-  }
+  Inner* sdev = reinterpret_cast<Inner*>(base + off[r]);
+  NK_HIP(hipMemcpyAsync(sdev, S, dbytes, hipMemcpyHostToDevice, st));
+  inner_launch<true>(r, Inner{}, sdev, hermitian, kmax, lmax, st);
   NK_HIP(hipGetLastError());
-  std::vector<int> fl((size_t)2 * r);
-  for (int s = 0; s < r; ++s) NK_HIP(hipMemcpyAsync(&fl[2 * s], S[s].flags, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
   NK_HIP(hipStreamSynchronize(st));
   int warn = NK_OK;
   for (int s = 0; s < r; ++s) {
@@ -935,18 +1147,16 @@ int small_inner_batch(int r, const int* k, const int* ell, int hermitian, const 
       set_error("nested small problem %d: H_k is singular", s);
       return NK_WARN_NOTCONV;
     }
-    const int lu = fl[2 * s] ? fl[2 * s] : ell[s];
+    ell_used[s] = fl[2 * s] ? fl[2 * s] : ell[s];
     if (fl[2 * s]) warn = NK_WARN_BREAKDOWN;
-    ell_used[s] = lu;
-    C64* h = hl_host + (size_t)s * 3 * ldh;
-    NK_HIP(hipMemcpyAsync(h, S[s].a, lu * sizeof(C64), hipMemcpyDeviceToHost, st));
-    NK_HIP(hipMemcpyAsync(h + ldh, S[s].b, lu * sizeof(C64), hipMemcpyDeviceToHost, st));
-    NK_HIP(hipMemcpyAsync(h + 2 * ldh, S[s].d, lu * sizeof(C64), hipMemcpyDeviceToHost, st));
-    NK_HIP(hipMemcpyAsync(vl_dev + (size_t)s * vl_stride, S[s].V, (size_t)k[s] * lu * sizeof(C64),
-                          hipMemcpyDeviceToDevice, st));
   }
-  NK_HIP(hipStreamSynchronize(st));
   return warn;
+}
+
+void small_lift_batch(int r, int kmax, const int* kv, const int* lv, const C64* V, size_t vstride, const C64* S,
+                      int ld, C64* z, int zstride, hipStream_t st) {
+  hipLaunchKernelGGL(k_in_lift_batch, dim3((kmax + LR - 1) / LR, r), dim3(LT), 0, st, kv, lv, V, vstride, S, ld, z,
+                     zstride);
 }
 
 }  // namespace nk

@@ -30,4 +30,41 @@ __device__ __forceinline__ double wave_sum(double v) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// The butterfly sums v += v of lane ^ o, for o = 32 .. 1 (wave_xsum), 4 .. 1
+// (oct_xsum, over 8 lanes) and 1, 2 (quad_xsum, over 4 lanes): the same bits
+// as with shuffles, on DPP and the row swaps instead of LDS permutes.  After a
+// step, lanes l and l ^ o agree, so a rotation within the row of 16 that meets
+// either of them does for the next one.
+__device__ __forceinline__ double pair_sum(double v, bool rows32) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
+  const auto l = rows32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                        : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h = rows32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                        : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+}
+__device__ __forceinline__ double wave_xsum(double v) {
+  v = pair_sum(v, true);
+  v = pair_sum(v, false);
+  v += dpp_take<0x128, 0xf>(v);  // row_ror:8
+  v += dpp_take<0x124, 0xf>(v);  // row_ror:4
+  v += dpp_take<0x122, 0xf>(v);  // row_ror:2
+  v += dpp_take<0x121, 0xf>(v);  // row_ror:1
+  return v;
+}
+__device__ __forceinline__ double quad_xsum(double v) {
+  v += dpp_take<0xb1, 0xf>(v);  // quad_perm 1, 0, 3, 2
+  v += dpp_take<0x4e, 0xf>(v);  // quad_perm 2, 3, 0, 1
+  return v;
+}
+__device__ __forceinline__ double oct_xsum(double v) {
+  const double up = dpp_take<0x104, 0xf>(v), dn = dpp_take<0x114, 0xf>(v);  // row_shl:4: lane + 4, row_shr:4: lane - 4
+  v += (threadIdx.x & 4) ? dn : up;
+  v += dpp_take<0x4e, 0xf>(v);  // quad_perm 2, 3, 0, 1
+  v += dpp_take<0xb1, 0xf>(v);  // quad_perm 1, 0, 3, 2
+  return v;
+}
+
 }  // namespace nk

@@ -174,3 +174,51 @@ def test_tridiagonal_sign_nan_is_reported():
     a[30] = np.nan
     _, _, rc = b.nk_small_sign(70, 0, True, a, be, de)
     assert rc == b.NK_WARN_NOTCONV
+
+
+def _two_sided(B, ell):
+    """Diagonal, super- and sub-diagonal of H_ell of K_ell(B, e_1), two-sided, each projection twice."""
+    k = len(B)
+    V, Wd = np.zeros((k, ell), complex), np.zeros((k, ell), complex)
+    V[0, 0] = Wd[0, 0] = 1.0
+    a, be, de = np.zeros(ell, complex), np.zeros(ell - 1, complex), np.zeros(ell - 1, complex)
+    for i in range(ell):
+        u, q = B @ V[:, i], B.conj().T @ Wd[:, i]
+        a[i] = np.vdot(Wd[:, i], u)
+        for _ in range(2):
+            u, q = u - V[:, :i + 1] @ (Wd[:, :i + 1].conj().T @ u), q - Wd[:, :i + 1] @ (V[:, :i + 1].conj().T @ q)
+        if i + 1 < ell:
+            s = np.vdot(q, u)
+            de[i] = np.sqrt(abs(s))
+            be[i] = s / de[i]
+            V[:, i + 1], Wd[:, i + 1] = u / de[i], q / np.conj(be[i])
+    return a, be, de
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 17, 959, 960, 961, 1365, 1366])
+@pytest.mark.parametrize("diag", [0.3, 3.0])
+@pytest.mark.parametrize("e", [0, 230, -230])
+def test_inner_projection_of_every_elimination(k, diag, e):
+    """H_ell around the sizes at which the elimination of H_k changes its
+    storage, with rows exchanged (a small diagonal) and not, and with pivots
+    beyond the range of its unscaled reciprocal (H_k 2^230: B = H_k to the last
+    bit, 2^-230: B = H_k^{-1}).  Five steps in FP64, condition below 100: 1e-10."""
+    b = nk()
+    rng = np.random.default_rng(1000 + k)
+    c = lambda n: rng.standard_normal(n) + 1j * rng.standard_normal(n)
+    al, be, de = diag * np.exp(0.3j * rng.standard_normal(k)) + 0.05 * c(k), 1.0 + 0.1 * c(k), 1.1 + 0.1 * c(k)
+    if diag < 1.0:  # weakly coupled pairs
+        be[1::2], de[1::2] = 0.2 * be[1::2], 0.2 * de[1::2]
+    H = np.diag(al) + np.diag(be[:k - 1], 1) + np.diag(de[:k - 1], -1)
+    assert np.linalg.cond(H) < 100
+    ell = min(5, k - 1) if k > 1 else 1
+    B = H + np.linalg.inv(H) if e == 0 else H if e > 0 else np.linalg.inv(H)
+    ref = _two_sided(B, ell)
+    banner(f"inner projection k={k} diagonal {diag} scale 2^{e}")
+    f = 2.0 ** e
+    got = b.nk_inner_matrix(k, ell, False, f * al, f * be, f * de)
+    assert got[3] == ell and got[4] == 0
+    g = 2.0 ** -abs(e)
+    for x, y in zip(got[:3], ref):
+        x = g * x[:len(y)]
+        assert np.linalg.norm(x - y) <= 1e-10 * max(1.0, np.linalg.norm(ref[0]))
