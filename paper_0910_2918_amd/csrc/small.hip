@@ -527,13 +527,18 @@ static int inner_grid(int r, int nbmax) { return r < 8 ? r * nbmax : 8 * nbmax *
 // previous step are reduced: one memory round trip instead of four.  Each
 // wave multiplies its own row's new entry into the projection columns and
 // leaves the products in LDS; they are summed over the block's rows in row
-// order, as a single thread summing them would.
+// order, as a single thread summing them would.  The new vector is scaled once
+// per workgroup, into LDS (by every wave for itself it cost as many loads as
+// the matrix): k = 500 7.1 us (8.9), 16 problems of k = 300 19 us (22).  The
+// products are rounded in a fixed order, as in the elimination.
+constexpr int XC = 512;  // columns of B staged at a time, eight per lane
 constexpr int GP = 2;  // projection columns per lane loaded at launch (j < 128)
 
 template <bool BATCH>
 __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner* __restrict__ SS, int nprob,
                                                      int nbmax, int i) {
   extern __shared__ C64 s_p[];  // [GR][i + 1] per-row projection products
+  __shared__ C64 s_x[XC];       // v_i (or w_i), a stretch of it
   int z, blk;
   inner_place<BATCH>(nprob, nbmax, &z, &blk);
   if (BATCH && z >= nprob) return;
@@ -561,16 +566,20 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
   const bool other = !s.herm;
   gp<const C64> proj = as_global((const C64*)(s.herm ? S.V : (side ? S.V : S.W)));
   gp<const C64> osrc = as_global((const C64*)(side ? (h ? S.uraw[1] : S.uraw[0]) : (h ? S.qraw[1] : S.qraw[0])));
-  // loads issued at launch: eight columns of the row and of the raw vector
-  // per lane (clamped to column 0 past the end), this row's raw entries, the
-  // old basis entry and up to GP projection columns per lane
-  C64 mv[8], xv[8];
+  // loads issued at launch: eight columns of the row per lane (clamped to
+  // column 0 past the end), an entry of the raw vector per thread, this row's
+  // raw entries, the old basis entry and up to GP projection columns per lane
+  C64 mv[8], xs;
+  auto fetch = [&](int c0) {
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int c = lane + 64 * u, cc = c < k ? c : 0;
-    mv[u] = ldg(M + (size_t)rs * k + cc);
-    xv[u] = ldg(src + cc);
-  }
+    for (int u = 0; u < 8; ++u) {
+      const int c = c0 + lane + 64 * u, cc = c < k ? c : 0;
+      mv[u] = ldg(M + (size_t)rs * k + cc);
+    }
+    const int c = c0 + (int)threadIdx.x;
+    xs = ldg(src + (c < k ? c : 0));
+  };
+  fetch(0);
   const C64 xr_raw = ldg(src + rs);
   const C64 xo_raw = ldg(osrc + rs);
   const C64 vold = ldg(basis + (size_t)(i > 0 ? i - 1 : 0) * k + rs);
@@ -610,33 +619,24 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
     scal_o = side ? sv : sw;
     sub = side ? mk(delta, 0.0) : beta;
   }
-  // u_r = (B v_i)_r - sub * v_{i-1, r}: the batch loaded at launch, then
-  // (k > 512) the rest of the row eight columns per lane at a time
+  // u_r = (B v_i)_r - sub * v_{i-1, r}, XC columns at a time: the workgroup
+  // scales them once, into LDS, for all its rows
   C64 ac[4] = {mk(0.0, 0.0), mk(0.0, 0.0), mk(0.0, 0.0), mk(0.0, 0.0)};
-  auto madd = [&](int c0) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = c0 + 64 * u;
-      if (c < k) {
-        const C64 x = (i > 0) ? cmul(scal, xv[u]) : mk(c == 0 ? 1.0 : 0.0, 0.0);
-        ac[u & 3] = ac[u & 3] + cmul(mv[u], x);
-      }
+  for (int c0 = 0; c0 < k; c0 += XC) {
+    if (c0 > 0) {
+      fetch(c0);
+      __syncthreads();
     }
-  };
-  madd(lane);
-  for (int c0 = lane + 8 * 64; c0 < k; c0 += 8 * 64) {
+    if (threadIdx.x < XC) s_x[threadIdx.x] = (i > 0) ? cmul_a(scal, xs) : mk(c0 + threadIdx.x == 0 ? 1.0 : 0.0, 0.0);
+    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = c0 + 64 * u, cc = c < k ? c : 0;
-      mv[u] = ldg(M + (size_t)rs * k + cc);
-      xv[u] = ldg(src + cc);
-    }
-    madd(c0);
+    for (int u = 0; u < 8; ++u)
+      if (c0 + lane + 64 * u < k) ac[u & 3] = ac[u & 3] + cmul_b(mv[u], s_x[lane + 64 * u]);
   }
   C64 acc = (ac[0] + ac[1]) + (ac[2] + ac[3]);
   acc = mk(wave_xsum(acc.re), wave_xsum(acc.im));
-  const C64 xr = (i > 0) ? cmul(scal, xr_raw) : mk(r == 0 ? 1.0 : 0.0, 0.0);  // v_i (or w_i) at row r
-  if (i > 0) acc = acc - cmul(sub, vold);
+  const C64 xr = (i > 0) ? cmul_a(scal, xr_raw) : mk(r == 0 ? 1.0 : 0.0, 0.0);  // v_i (or w_i) at row r
+  if (i > 0) acc = acc - cmul_b(sub, vold);
   if (live && lane == 0) {
     stg(basis + (size_t)i * k + r, xr);
     stg(dst + r, acc);
@@ -652,19 +652,20 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
       const int j = lane + 64 * (m0 + m);
       if (j < ncol) {
         C64 pv;
-        if (j == i) pv = other ? ((i > 0) ? cmul(scal_o, xo_raw) : mk(r == 0 ? 1.0 : 0.0, 0.0)) : xr;
+        if (j == i) pv = other ? ((i > 0) ? cmul_b(scal_o, xo_raw) : mk(r == 0 ? 1.0 : 0.0, 0.0)) : xr;
         else pv = (m0 == 0) ? pj[m] : ldg(proj + (size_t)j * k + rs);
-        s_p[wave * ncol + j] = cmulc(pv, acc);
+        s_p[wave * ncol + j] = mk(fma(pv.im, acc.im, pv.re * acc.re), fma(pv.re, acc.im, -(pv.im * acc.re)));
       }
     }
   }
   __syncthreads();
   gp<C64> out = s.part1 + ((size_t)side * s.nb1 + blk) * s.lmax;
   for (int j = threadIdx.x; j < ncol; j += GR * 64) {
-    C64 t = mk(0.0, 0.0);
+    C64 t = mk(0.0, 0.0), pw[GR];
 #pragma unroll
-    for (int w = 0; w < GR; ++w)
-      if (blk * GR + w < k) t = t + s_p[w * ncol + j];
+    for (int w = 0; w < GR; ++w) pw[w] = s_p[w * ncol + j];
+#pragma unroll
+    for (int w = 0; w < GR; ++w) t = csel(blk * GR + w < k, t + pw[w], t);
     stg(out + j, t);
   }
 }
