@@ -432,18 +432,12 @@ int nk_apply_dw_device(nk_lattice* lat, double m_w, double mu, int32_t gamma5, c
     set_error("no gauge field set on the lattice handle");
     return NK_ENOGAUGE;
   }
-  const Geom& g = lat->g;
-  const size_t n = (size_t)12 * g.V;
-  if (lat->tmp.ensure(2 * n * sizeof(C64))) return NK_ENOMEM;
-  C64* a = lat->tmp.as<C64>();
-  C64* b = a + n;
-  hipStream_t st = (hipStream_t)stream;
-  for (int r = 0; r < nrhs; ++r) {
-    if (int e = pack_spinor<double>(g, (const C64*)x + r * n, a, st)) return e;
-    if (int e = apply_dw_dev(lat, m_w, mu, gamma5 ? 1 : 0, a, b, st)) return e;
-    if (int e = unpack_spinor<double>(g, b, (C64*)y + r * n, st)) return e;
-  }
-  return NK_OK;
+  auto tmp = [](nk_lattice* l, C64** p) -> int {
+    if (l->tmp.ensure((size_t)12 * l->g.V * sizeof(C64))) return NK_ENOMEM;
+    *p = l->tmp.as<C64>();
+    return NK_OK;
+  };
+  return apply_canon_dev(lat, m_w, mu, gamma5 ? 1 : 0, (const C64*)x, (C64*)y, nrhs, tmp, (hipStream_t)stream);
 }
 
 int nk_apply_dw(nk_lattice* lat, double m_w, double mu, int32_t gamma5, const double* x, double* y, int32_t nrhs) {

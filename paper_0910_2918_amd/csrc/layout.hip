@@ -42,22 +42,59 @@ __global__ void k_pack_gauge(Geom g, const C64* __restrict__ canon, C64* __restr
   }
 }
 
-template <class R>
-__global__ void k_pack_spinor(Geom g, const C64* __restrict__ canon, Cx<R>* __restrict__ dev) {
-  const int sc = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sc >= g.V) return;
-  const int s = dev_site(g, sc);
+// Spinor layouts, 64 device sites per workgroup, through LDS: both sides of the
+// exchange are then read and written in whole lines (a canonical site's 12
+// components lie together, and device sites run along x lines; a lane per
+// site on the canonical side touched 64 lines per instruction).  Bound by
+// memory (65536 sites: 25 MB, 6.8 us to pack and 8.0 to unpack by a lane per site).
+constexpr int PS = 64, PLD = 13;  // sites per workgroup; padded sites in LDS
+
+__device__ __forceinline__ int canon_of(const Geom& g, int s) {
+  int l = s & ((1 << g.lts) - 1), T = s >> g.lts, r = 0;
 #pragma unroll
-  for (int c = 0; c < 12; ++c) dev[sidx<R>(g.V, c, s)] = narrow<R>(canon[(size_t)sc * 12 + c]);
+  for (int d = 0; d < 4; ++d) {
+    const int ct = d < 3 ? T % g.nt[d] : T;
+    r += (ct * g.b[d] + (l & (g.b[d] - 1))) * g.stride[d];
+    l >>= g.lb[d];
+    T /= g.nt[d];
+  }
+  return r;
 }
 
-template <class R>
-__global__ void k_unpack_spinor(Geom g, const Cx<R>* __restrict__ dev, C64* __restrict__ canon) {
-  const int sc = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sc >= g.V) return;
-  const int s = dev_site(g, sc);
+template <class R, bool PACK>
+__global__ void __launch_bounds__(256) k_layout(Geom g, C64* __restrict__ canon, Cx<R>* __restrict__ dev) {
+  __shared__ C64 sh[PS][PLD];
+  __shared__ int s_can[PS];
+  const int s0 = blockIdx.x * PS, t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int ns = min(PS, g.V - s0);
+  if (t < PS) s_can[t] = canon_of(g, s0 + min(t, ns - 1));
+  __syncthreads();
+  C64 v[3];
+  if (PACK) {
 #pragma unroll
-  for (int c = 0; c < 12; ++c) canon[(size_t)sc * 12 + c] = widen(dev[sidx<R>(g.V, c, s)]);
+    for (int m = 0; m < 3; ++m) {
+      const int e = t + 256 * m, q = e / 12, c = e % 12;
+      v[m] = canon[(size_t)s_can[q] * 12 + c];
+    }
+#pragma unroll
+    for (int m = 0; m < 3; ++m) sh[(t + 256 * m) / 12][(t + 256 * m) % 12] = v[m];
+    __syncthreads();
+    if (lane < ns)
+#pragma unroll
+      for (int m = 0; m < 3; ++m) dev[sidx<R>(g.V, w + 4 * m, s0 + lane)] = narrow<R>(sh[lane][w + 4 * m]);
+  } else {
+    const int s = s0 + min(lane, ns - 1);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) v[m] = widen(dev[sidx<R>(g.V, w + 4 * m, s)]);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) sh[lane][w + 4 * m] = v[m];
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      const int e = t + 256 * m, q = e / 12, c = e % 12;
+      if (q < ns) canon[(size_t)s_can[q] * 12 + c] = sh[q][c];
+    }
+  }
 }
 
 void geom_init(Geom& g, const int dims[4]) {
@@ -111,14 +148,14 @@ int pack_gauge(nk_lattice* lat, const C64* canon, hipStream_t st) {
 
 template <class R>
 int pack_spinor(const Geom& g, const C64* canon, Cx<R>* dev, hipStream_t st) {
-  hipLaunchKernelGGL(k_pack_spinor<R>, dim3((g.V + 255) / 256), dim3(256), 0, st, g, canon, dev);
+  hipLaunchKernelGGL((k_layout<R, true>), dim3((g.V + PS - 1) / PS), dim3(256), 0, st, g, const_cast<C64*>(canon), dev);
   NK_HIP(hipGetLastError());
   return NK_OK;
 }
 
 template <class R>
 int unpack_spinor(const Geom& g, const Cx<R>* dev, C64* canon, hipStream_t st) {
-  hipLaunchKernelGGL(k_unpack_spinor<R>, dim3((g.V + 255) / 256), dim3(256), 0, st, g, dev, canon);
+  hipLaunchKernelGGL((k_layout<R, false>), dim3((g.V + PS - 1) / PS), dim3(256), 0, st, g, canon, const_cast<Cx<R>*>(dev));
   NK_HIP(hipGetLastError());
   return NK_OK;
 }

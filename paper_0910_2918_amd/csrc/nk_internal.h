@@ -273,6 +273,8 @@ template <class R>
 int unpack_spinor(const Geom& g, const Cx<R>* dev, C64* canon, hipStream_t st);
 
 // wilson.hip
+int apply_canon_dev(nk_lattice* lat, double m_w, double mu, int g5, const C64* x, C64* y, int nrhs,
+                    int (*tmp)(nk_lattice*, C64**), hipStream_t st);
 int apply_dw_dev(nk_lattice* lat, double m_w, double mu, int g5, const C64* x, C64* y, hipStream_t st);
 int apply_pair_dev(nk_lattice* lat, double m_w, double mu, const C64* v, const C64* w, C64* av, C64* adw,
                    hipStream_t st);

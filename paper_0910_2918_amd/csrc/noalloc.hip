@@ -1,6 +1,7 @@
 // nk_apply_dw_noalloc_device: the operator of Sec. 1 on canonical device
-// vectors, as nk_apply_dw_device computes it, with its two layout
-// temporaries in a fixed device array instead of the handle's allocation.
+// vectors, as nk_apply_dw_device computes it, with the packed vector that
+// overlapping inputs need in a fixed device array instead of the handle's
+// allocation.
 // For callers that cannot allocate device memory (HIP graph capture, tight
 // serving loops).
 #include <mutex>
@@ -9,10 +10,10 @@
 
 namespace nk {
 
-// two packed FP64 spinor fields of at most NK_NOALLOC_MAX_SITES sites: the
-// packed source and the packed result.  Each device the library runs on
-// holds its own copy until the process ends.
-constexpr size_t kScratchElems = (size_t)2 * 12 * NK_NOALLOC_MAX_SITES;
+// one packed FP64 spinor field of at most NK_NOALLOC_MAX_SITES sites, the
+// packed source.  Each device the library runs on holds its own copy until
+// the process ends.
+constexpr size_t kScratchElems = (size_t)12 * NK_NOALLOC_MAX_SITES;
 static __device__ __align__(256) C64 scratch[kScratchElems];
 
 namespace {
@@ -23,7 +24,7 @@ void* g_scratch_ptr[kMaxDevices] = {};
 
 // the device address of `scratch` on the current device, looked up once per
 // device (the host-side name of the array is not a device address)
-static int scratch_ptr(C64** out) {
+static int scratch_ptr(nk_lattice*, C64** out) {
   int dev = 0;
   NK_HIP(hipGetDevice(&dev));
   if (dev < 0 || dev >= kMaxDevices) {
@@ -64,17 +65,8 @@ extern "C" int nk_apply_dw_noalloc_device(nk_lattice* lat, double m_w, double mu
               NK_NOALLOC_MAX_SITES);
     return NK_EINVAL;
   }
-  C64* a = nullptr;
-  if (int e = scratch_ptr(&a)) return e;
-  const size_t n = (size_t)12 * g.V;
-  C64* b = a + (size_t)12 * NK_NOALLOC_MAX_SITES;
-  hipStream_t st = (hipStream_t)stream;
-  // pack writes every entry of a, the stencil every entry of b: nothing from
-  // an earlier call is read, so nothing needs clearing
-  for (int r = 0; r < nrhs; ++r) {
-    if (int e = pack_spinor<double>(g, (const C64*)x + r * n, a, st)) return e;
-    if (int e = apply_dw_dev(lat, m_w, mu, gamma5 ? 1 : 0, a, b, st)) return e;
-    if (int e = unpack_spinor<double>(g, b, (C64*)y + r * n, st)) return e;
-  }
-  return NK_OK;
+  // (where the scratch is used, every entry is written first: nothing from an
+  // earlier call is read, so nothing needs clearing)
+  return apply_canon_dev(lat, m_w, mu, gamma5 ? 1 : 0, (const C64*)x, (C64*)y, nrhs, scratch_ptr,
+                         (hipStream_t)stream);
 }

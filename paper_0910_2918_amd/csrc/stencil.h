@@ -219,12 +219,38 @@ __device__ __forceinline__ void hop_fence() {
 #endif
 }
 
+// canonical index of a device site
+__device__ __forceinline__ int canon_site(const Geom& g, const SiteC& c) {
+  int s = 0;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) s += (c.ct[d] * g.b[d] + c.cl[d]) * g.stride[d];
+  return s;
+}
+
+// The field that a hop reads: a pointer to a device-layout field, or a
+// canonical FP64 field with the canonical index of the lane's own site.
+struct CanonField {
+  const C64* p;
+  int s;
+};
+// psi of the neighbour in direction NU, whose device index is sn
+template <int NU, bool FWD, class R>
+__device__ __forceinline__ void load_nbr(const Cx<R>* f, const Geom& g, int sn, bool, Cx<R> (&p)[12]) {
+  load_spinor(f, g.V, sn, p);
+}
+template <int NU, bool FWD>
+__device__ __forceinline__ void load_nbr(const CanonField& f, const Geom& g, int, bool wrap, C64 (&p)[12]) {
+  const int d = wrap ? (1 - g.L[NU]) * g.stride[NU] : g.stride[NU];
+  const C64* q = f.p + (size_t)(FWD ? f.s + d : f.s - d) * 12;
+#pragma unroll
+  for (int c = 0; c < 12; ++c) p[c] = q[c];
+}
+
 // forward hop in direction nu for NF fields: (1 - gamma) U_nu(x) psi(x + nu)
-template <int NU, class R, int NF, class LK>
-__device__ __forceinline__ void hop_fwd(const Geom& g, int s, const SiteC& sc0, const LK& lk,
-                                        const Cx<R>* const (&in)[NF], const R (&cf)[NF], Cx<R> (&acc)[NF][12]) {
+template <int NU, class R, int NF, class LK, class F>
+__device__ __forceinline__ void hop_fwd(const Geom& g, int s, const SiteC& sc0, const LK& lk, const F (&in)[NF],
+                                        const R (&cf)[NF], Cx<R> (&acc)[NF][12]) {
   using P = Proj<NU>;
-  const int V = g.V;
   bool wrap;
   const int sf = nbr_fwd<NU>(g, s, sc0, &wrap);
   const R bf = (NU == 3 && wrap) ? R(-1) : R(1);
@@ -235,7 +261,7 @@ __device__ __forceinline__ void hop_fwd(const Geom& g, int s, const SiteC& sc0, 
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     Cx<R> p[12];
-    load_spinor(in[f], V, sf, p);
+    load_nbr<NU, true>(in[f], g, sf, wrap, p);
     const R sc = bf * cf[f];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -259,11 +285,10 @@ __device__ __forceinline__ void hop_fwd(const Geom& g, int s, const SiteC& sc0, 
 }
 
 // backward hop in direction nu for NF fields: (1 + gamma) U_nu(x - nu)^dag psi(x - nu)
-template <int NU, class R, int NF, class LK>
-__device__ __forceinline__ void hop_bwd(const Geom& g, int s, const SiteC& sc0, const LK& lk,
-                                        const Cx<R>* const (&in)[NF], const R (&cb)[NF], Cx<R> (&acc)[NF][12]) {
+template <int NU, class R, int NF, class LK, class F>
+__device__ __forceinline__ void hop_bwd(const Geom& g, int s, const SiteC& sc0, const LK& lk, const F (&in)[NF],
+                                        const R (&cb)[NF], Cx<R> (&acc)[NF][12]) {
   using P = Proj<NU>;
-  const int V = g.V;
   bool wrap;
   const int sb = nbr_bwd<NU>(g, s, sc0, &wrap);
   const R bb = (NU == 3 && wrap) ? R(-1) : R(1);
@@ -274,7 +299,7 @@ __device__ __forceinline__ void hop_bwd(const Geom& g, int s, const SiteC& sc0, 
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     Cx<R> p[12];
-    load_spinor(in[f], V, sb, p);
+    load_nbr<NU, false>(in[f], g, sb, wrap, p);
     const R sc = bb * cb[f];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -354,10 +379,10 @@ __device__ __forceinline__ void xacc(XBuf<R, NG>& xb, int w, int lane, const Cx<
 
 // one hop (forward or backward in direction NU) of group GI, handed to the
 // exchange
-template <bool FWD, int NU, int NG, int GI, bool FIRST, class R, class LK>
-__device__ __forceinline__ void hop_x(const Geom& g, int s, const SiteC& x, const LK& lk, const Cx<R>* in, R tf,
+template <bool FWD, int NU, int NG, int GI, bool FIRST, class R, class LK, class F>
+__device__ __forceinline__ void hop_x(const Geom& g, int s, const SiteC& x, const LK& lk, const F& in, R tf,
                                       XBuf<R, NG>& xb, int w, int lane, Cx<R> (&mine)[12 / NG]) {
-  const Cx<R>* ins[1] = {in};
+  const F ins[1] = {in};
   const R f1[1] = {NU == 3 ? tf : R(1)};
   Cx<R> acc[1][12];
 #pragma unroll
@@ -372,8 +397,8 @@ __device__ __forceinline__ void hop_x(const Geom& g, int s, const SiteC& x, cons
 // hopping sum of direction group gi (wave-uniform) of one field at site s,
 // left in the exchange (LDS slots of wave w and mine[]); ef/eb are the
 // forward/backward temporal factors
-template <int NG, class R, class LK>
-__device__ __forceinline__ void hop_group(const Geom& g, int s, const LK& lk, const Cx<R>* in, int gi, R ef, R eb,
+template <int NG, class R, class LK, class F>
+__device__ __forceinline__ void hop_group(const Geom& g, int s, const LK& lk, const F& in, int gi, R ef, R eb,
                                           XBuf<R, NG>& xb, int w, int lane, Cx<R> (&mine)[12 / NG]) {
   const SiteC x = site_coords(g, s);
   if constexpr (NG == 4) {

@@ -1,5 +1,7 @@
 // Stand-alone applications of gamma5 Dw(mu): the single operator and the
 // fused pair (A v, A^dag w) of two-sided Lanczos (A^dag = A(-mu)).
+#include <algorithm>
+
 #include "stencil.h"
 
 namespace nk {
@@ -106,6 +108,64 @@ __global__ void __launch_bounds__(256) k_apply_block(Geom g, LinksPlain<double> 
   }
 }
 
+// The operator on canonical vectors, out of the stencil's epilogue into the
+// canonical layout: the 64 sites' results meet in LDS (over the exchange's
+// buffer) and go out as they lie in memory, 12 components of a site together
+// and whole x lines of sites behind each other.  CIN: the input is canonical
+// too, each lane reading its neighbours' 192 bytes where they lie (twelve loads
+// that share their lines; the L1 holds a wave's 12 KB of them); grid y =
+// vector.  That spares the packing launch and its pass over memory.
+template <int NG, bool CIN>
+__global__ void __launch_bounds__(256) k_apply_canon(Geom g, LinksPlain<double> lk, double diag, int g5, const C64* in,
+                                                     C64* out, double ef, double eb) {
+  constexpr int M = 12 / NG, NSB = (256 / 64) / NG, SITES = 64 * NSB, LD = 13;  // LD: padded sites in LDS
+  __shared__ union {
+    XBuf<double, NG> xb;
+    C64 y[SITES][LD];
+  } sh;
+  __shared__ int s_can[SITES];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gi = w % NG, sb = w / NG;
+  const int s0 = xcd_block() * SITES, s = s0 + sb * 64 + lane;
+  const size_t off = CIN ? (size_t)blockIdx.y * 12 * g.V : 0;
+  const C64* x = in + off;
+  C64* y = out + off;
+  const bool live = s < g.V;
+  const int sl = live ? s : 0;  // a lane past the end hops at site 0
+  const int sc = canon_site(g, site_coords(g, sl));
+  if (gi == 0) s_can[sb * 64 + lane] = sc;
+  C64 mine[M];
+  if constexpr (CIN)
+    hop_group<NG>(g, sl, lk, CanonField{x, sc}, gi, ef, eb, sh.xb, w, lane, mine);
+  else
+    hop_group<NG>(g, sl, lk, x, gi, ef, eb, sh.xb, w, lane, mine);
+  __builtin_amdgcn_sched_barrier(0);  // the stencil's registers are free before these loads
+  int se = CIN ? sc : sl;
+  asm volatile("" : "+v"(se));  // keeps the epilogue addresses out of the stencil's registers
+  C64 ein[M];
+#pragma unroll
+  for (int cl = 0; cl < M; ++cl) ein[cl] = CIN ? x[(size_t)se * 12 + gi * M + cl] : x[sidx<double>(g.V, gi * M + cl, se)];
+  __syncthreads();
+  C64 o[M];
+#pragma unroll
+  for (int cl = 0; cl < M; ++cl) {
+    const int cc = gi * M + cl;
+    const C64 hs = xsum<NG>(sh.xb, sb, gi, lane, cl, mine[cl]);
+    o[cl] = diag * ein[cl] - 0.5 * hs;
+    if (g5 && cc >= 6) o[cl] = mk(-o[cl].re, -o[cl].im);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int cl = 0; cl < M; ++cl) sh.y[sb * 64 + lane][gi * M + cl] = o[cl];
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < SITES * 12 / 256; ++m) {
+    const int e = threadIdx.x + 256 * m, q = e / 12, c = e % 12;
+    if (s0 + q < g.V) y[(size_t)s_can[q] * 12 + c] = sh.y[q][c];
+  }
+}
+
 // workgroups of k_apply for NF fields
 static int apply_blocks(const Geom& g, int nf) {
   const int spb = (64 / nf) * ((256 / 64) / NK_GROUPS);
@@ -129,6 +189,36 @@ int apply_dw_dev(nk_lattice* lat, double m_w, double mu, int g5, const C64* x, C
   LinksPlain<double> lk{lat->U64.as<C64>(), g.V};
   hipLaunchKernelGGL((k_apply<double, 1, LinksPlain<double>, NK_GROUPS>), dim3(apply_blocks(g, 1)), dim3(256), 0,
                      st, g, lk, 4.0 + m_w, g5, in, out, tf);
+  NK_HIP(hipGetLastError());
+  return NK_OK;
+}
+
+// y = [gamma5] Dw x for nrhs canonical vectors.  The one launch needs x and y
+// apart, since it writes y while it reads x; where they overlap, each x is
+// packed into tmp(), one vector, before its y is written, one vector after the
+// other.  Measured (one vector; through the packed layout with this epilogue;
+// pack, stencil and unpack): 4096 sites 7.4, 10.8, 12.6 us; 65536 18.8, 23.2,
+// 31.0; 331776 96, 114, 157.
+int apply_canon_dev(nk_lattice* lat, double m_w, double mu, int g5, const C64* x, C64* y, int nrhs,
+                    int (*tmp)(nk_lattice*, C64**), hipStream_t st) {
+  if (int e = check_gauge(lat)) return e;
+  const Geom& g = lat->g;
+  const size_t n = (size_t)12 * g.V;
+  LinksPlain<double> lk{lat->U64.as<C64>(), g.V};
+  const double ef = exp(mu), eb = exp(-mu);
+  if (x + n * nrhs <= y || y + n * nrhs <= x) {
+    for (int r = 0; r < nrhs; r += 65535)
+      hipLaunchKernelGGL((k_apply_canon<NK_GROUPS, true>), dim3(apply_blocks(g, 1), std::min(nrhs - r, 65535)),
+                         dim3(256), 0, st, g, lk, 4.0 + m_w, g5, x + r * n, y + r * n, ef, eb);
+  } else {
+    C64* p = nullptr;
+    if (int e = tmp(lat, &p)) return e;
+    for (int r = 0; r < nrhs; ++r) {
+      if (int e = pack_spinor<double>(g, x + r * n, p, st)) return e;
+      hipLaunchKernelGGL((k_apply_canon<NK_GROUPS, false>), dim3(apply_blocks(g, 1)), dim3(256), 0, st, g, lk,
+                         4.0 + m_w, g5, p, y + r * n, ef, eb);
+    }
+  }
   NK_HIP(hipGetLastError());
   return NK_OK;
 }

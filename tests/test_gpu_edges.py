@@ -222,3 +222,50 @@ def test_inner_projection_of_every_elimination(k, diag, e):
     for x, y in zip(got[:3], ref):
         x = g * x[:len(y)]
         assert np.linalg.norm(x - y) <= 1e-10 * max(1.0, np.linalg.norm(ref[0]))
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 2, 6, 2), (16, 4, 2, 2), (6, 4, 2, 10), (8, 8, 4, 6)])
+@pytest.mark.parametrize("shift", [None, 5, 12, -7, 0.5, 1.0, -1.0])
+def test_operator_on_apart_and_overlapping_vectors(dims, shift):
+    """Canonical vectors with x and y apart (one launch), and y anywhere over x:
+    then each x is read as the outputs before it left it.  Sites below, at and
+    above a wave's 64; a fixed sum of at most 8 x 2 x 9 products: 1e-13."""
+    b = nk()
+    torch = torch_cuda()
+    lat, u = make_lattice(dims, 0.8, seed=3)
+    nrhs = 3
+    x = latgen.random_sources(dims, nrhs, 4).reshape(nrhs, -1)
+    n = x.shape[1]
+    banner(f"operator dims={dims} shift={shift}")
+    buf = np.zeros(6 * n, complex)
+    ix = n if shift is not None and shift < 0 else 0
+    buf[ix:ix + 3 * n] = x.reshape(-1)
+    iy = 3 * n if shift is None else ix + (shift if isinstance(shift, int) else int(shift * n))
+    ref = buf.copy()
+    for r in range(nrhs):
+        src = ref[ix + r * n:ix + (r + 1) * n].reshape(latgen.random_sources(dims, 1, 0)[0].shape)
+        ref[iy + r * n:iy + (r + 1) * n] = np.asarray(W.dw_apply(u, src.copy(), M_W, 0.3, g5=True)).reshape(-1)
+    for call in (b.nk_apply_dw_device, b.nk_apply_dw_noalloc_device):
+        t = torch.from_numpy(buf.copy()).cuda()
+        call(lat.h, M_W, 0.3, True, t[ix:ix + 3 * n], t[iy:iy + 3 * n], nrhs)
+        got = to_host(t)
+        assert np.linalg.norm(got - ref) <= 1e-13 * np.linalg.norm(ref)
+    lat.close()
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 2, 6, 2), (16, 4, 2, 2), (6, 4, 2, 10)])
+def test_spinor_layouts_are_inverse(dims):
+    """Packing is a permutation (every entry once) and unpacking undoes it, on
+    site counts below, at and above a workgroup's 64."""
+    b = nk()
+    torch = torch_cuda()
+    lat, _ = make_lattice(dims, 0.8, seed=3)
+    n = 12 * int(np.prod(dims))
+    x = torch.arange(2 * n, dtype=torch.float64, device="cuda") + 0.5j
+    xp, back = torch.zeros_like(x), torch.zeros_like(x)
+    b.nk_spinor_pack_device(lat.h, x, xp, 2)
+    b.nk_spinor_unpack_device(lat.h, xp, back, 2)
+    assert torch.equal(back, x)
+    for r in range(2):
+        assert torch.equal(torch.sort(xp[r * n:(r + 1) * n].real).values, x[r * n:(r + 1) * n].real)
+    lat.close()
