@@ -235,11 +235,11 @@ struct CanonField {
 };
 // psi of the neighbour in direction NU, whose device index is sn
 template <int NU, bool FWD, class R>
-__device__ __forceinline__ void load_nbr(const Cx<R>* f, const Geom& g, int sn, bool, Cx<R> (&p)[12]) {
-  load_spinor(f, g.V, sn, p);
+__device__ __forceinline__ void load_nbr(const Cx<R>* f, const Geom&, int V, int sn, bool, Cx<R> (&p)[12]) {
+  load_spinor(f, V, sn, p);
 }
 template <int NU, bool FWD>
-__device__ __forceinline__ void load_nbr(const CanonField& f, const Geom& g, int, bool wrap, C64 (&p)[12]) {
+__device__ __forceinline__ void load_nbr(const CanonField& f, const Geom& g, int, int, bool wrap, C64 (&p)[12]) {
   const int d = wrap ? (1 - g.L[NU]) * g.stride[NU] : g.stride[NU];
   const C64* q = f.p + (size_t)(FWD ? f.s + d : f.s - d) * 12;
 #pragma unroll
@@ -251,6 +251,7 @@ template <int NU, class R, int NF, class LK, class F>
 __device__ __forceinline__ void hop_fwd(const Geom& g, int s, const SiteC& sc0, const LK& lk, const F (&in)[NF],
                                         const R (&cf)[NF], Cx<R> (&acc)[NF][12]) {
   using P = Proj<NU>;
+  const int V = g.V;
   bool wrap;
   const int sf = nbr_fwd<NU>(g, s, sc0, &wrap);
   const R bf = (NU == 3 && wrap) ? R(-1) : R(1);
@@ -261,7 +262,7 @@ __device__ __forceinline__ void hop_fwd(const Geom& g, int s, const SiteC& sc0, 
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     Cx<R> p[12];
-    load_nbr<NU, true>(in[f], g, sf, wrap, p);
+    load_nbr<NU, true>(in[f], g, V, sf, wrap, p);
     const R sc = bf * cf[f];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -289,6 +290,7 @@ template <int NU, class R, int NF, class LK, class F>
 __device__ __forceinline__ void hop_bwd(const Geom& g, int s, const SiteC& sc0, const LK& lk, const F (&in)[NF],
                                         const R (&cb)[NF], Cx<R> (&acc)[NF][12]) {
   using P = Proj<NU>;
+  const int V = g.V;
   bool wrap;
   const int sb = nbr_bwd<NU>(g, s, sc0, &wrap);
   const R bb = (NU == 3 && wrap) ? R(-1) : R(1);
@@ -299,7 +301,7 @@ __device__ __forceinline__ void hop_bwd(const Geom& g, int s, const SiteC& sc0, 
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     Cx<R> p[12];
-    load_nbr<NU, false>(in[f], g, sb, wrap, p);
+    load_nbr<NU, false>(in[f], g, V, sb, wrap, p);
     const R sc = bb * cb[f];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -380,7 +382,7 @@ __device__ __forceinline__ void xacc(XBuf<R, NG>& xb, int w, int lane, const Cx<
 // one hop (forward or backward in direction NU) of group GI, handed to the
 // exchange
 template <bool FWD, int NU, int NG, int GI, bool FIRST, class R, class LK, class F>
-__device__ __forceinline__ void hop_x(const Geom& g, int s, const SiteC& x, const LK& lk, const F& in, R tf,
+__device__ __forceinline__ void hop_x(const Geom& g, int s, const SiteC& x, const LK& lk, F in, R tf,
                                       XBuf<R, NG>& xb, int w, int lane, Cx<R> (&mine)[12 / NG]) {
   const F ins[1] = {in};
   const R f1[1] = {NU == 3 ? tf : R(1)};
@@ -398,7 +400,7 @@ __device__ __forceinline__ void hop_x(const Geom& g, int s, const SiteC& x, cons
 // left in the exchange (LDS slots of wave w and mine[]); ef/eb are the
 // forward/backward temporal factors
 template <int NG, class R, class LK, class F>
-__device__ __forceinline__ void hop_group(const Geom& g, int s, const LK& lk, const F& in, int gi, R ef, R eb,
+__device__ __forceinline__ void hop_group(const Geom& g, int s, const LK& lk, F in, int gi, R ef, R eb,
                                           XBuf<R, NG>& xb, int w, int lane, Cx<R> (&mine)[12 / NG]) {
   const SiteC x = site_coords(g, s);
   if constexpr (NG == 4) {
