@@ -1,13 +1,13 @@
 // Many sources in lockstep: the outer two-sided Lanczos basis of Sec. 2 for
 // r sources at once, the small problems of Eqs. (3)-(6) batched, and the lift.
 //
-// Each source keeps its own recurrence and coefficients.  A step is four
+// Each source keeps its own recurrence and coefficients.  A step is two
 // launches for all sources together:
-//   k_blk1  A v_j, A^dag w_j minus the previous vectors, partial w~^dag A v~
-//           (grid: site blocks x sources)
-//   k_bred1 alpha_j per source (fixed-order reduction)
-//   k_blk2  v_hat, w_hat (new unnormalised columns), partial s, |v|^2, |w|^2
-//   k_bred2 delta, beta, the scales and the breakdown test per source
+//   k_blk1  delta, beta, the scales and the breakdown test of the step before
+//           (fixed-order reduction); A v_j, A^dag w_j minus the previous
+//           vectors, partial w~^dag A v~ (grid: site blocks x sources)
+//   k_blk2  alpha_j (fixed-order reduction); v_hat, w_hat (new unnormalised
+//           columns), partial s, |v|^2, |w|^2
 // so launches and reductions are shared by the sources, and the small
 // problems run as one inner projection per source followed by one batched
 // Roberts-Higham call over the uneven ell of all sources.  The links are
@@ -113,53 +113,61 @@ __device__ __forceinline__ void reduce_src(const double* __restrict__ p, int nb,
   bsum<NQ>(v);
 }
 
-// finish step j - 1 of every source: s -> delta, beta, scales of column j,
-// breakdown test (at j = 0: the source norm)
+// what finishing step j - 1 of a source leaves: delta, beta and the scales of
+// column j
+struct Fin {
+  double delta, sv;
+  C64 beta, sw;
+};
+
+// finish step j - 1 from its sums [Re s, Im s, |v|^2, |w|^2] with the breakdown
+// test (at j = 0: the source norm).  Returns what to flag, 0 to go on.
+__device__ __forceinline__ int finish(const double (&red)[4], int j, Fin& f) {
+  const C64 sdot = mk(red[0], red[1]);
+  const double sabs = sqrt(norm2(sdot));
+  if (j == 0 && !(sabs > 0.0 && sabs < 1e300)) return -1;
+  if (j > 0 && !(sabs > 1e-14 * sqrt(red[2] * red[3]))) return j;
+  f.delta = sqrt(sabs);
+  f.beta = (1.0 / f.delta) * sdot;
+  f.sv = 1.0 / f.delta;
+  f.sw = (1.0 / norm2(f.beta)) * f.beta;  // 1 / conj(beta)
+  return 0;
+}
+__device__ __forceinline__ void store_fin(const BArgs& a, int s, int j, const Fin& f) {
+  a.sv[(size_t)s * (a.k + 1) + j] = f.sv;
+  a.sw[(size_t)s * (a.k + 1) + j] = f.sw;
+  if (j > 0) {
+    a.beta[(size_t)s * a.k + j - 1] = f.beta;
+    a.delta[(size_t)s * a.k + j - 1] = mk(f.delta, 0.0);
+  }
+}
+
+// finish step j - 1 of every source in a launch of its own, before a stencil
+// step for several sources per workgroup
 __global__ void __launch_bounds__(BT) k_bred2(BArgs a, int j) {
   const int s = blockIdx.x;
   if (a.flags[s]) return;
   double red[4];
   reduce_src<4>(a.part2 + (size_t)s * 4 * a.nb2, a.nb2, red);
   if (threadIdx.x != 0) return;
-  const C64 sdot = mk(red[0], red[1]);
-  const double sabs = sqrt(norm2(sdot));
-  if (j == 0 && !(sabs > 0.0 && sabs < 1e300)) {
-    a.flags[s] = -1;
-    return;
-  }
-  if (j > 0 && !(sabs > 1e-14 * sqrt(red[2] * red[3]))) {
-    a.flags[s] = j;
-    return;
-  }
-  const double delta = sqrt(sabs);
-  const C64 beta = (1.0 / delta) * sdot;
-  a.sv[(size_t)s * (a.k + 1) + j] = 1.0 / delta;
-  a.sw[(size_t)s * (a.k + 1) + j] = (1.0 / norm2(beta)) * beta;  // 1 / conj(beta)
-  if (j > 0) {
-    a.beta[(size_t)s * a.k + j - 1] = beta;
-    a.delta[(size_t)s * a.k + j - 1] = mk(delta, 0.0);
-  }
-}
-
-// alpha_j = conj(sw_j) sv_j (w~_j^dag A v~_j) of every running source
-__global__ void __launch_bounds__(BT) k_bred1(BArgs a, int j) {
-  const int s = blockIdx.x;
-  if (a.flags[s]) return;
-  double red[2];
-  reduce_src<2>(a.part1 + (size_t)s * 2 * a.nb1, a.nb1, red);
-  if (threadIdx.x != 0) return;
-  const double svj = a.sv[(size_t)s * (a.k + 1) + j];
-  const C64 swj = a.sw[(size_t)s * (a.k + 1) + j];
-  a.alpha[(size_t)s * a.k + j] = cmul(conj(swj), svj * mk(red[0], red[1]));
+  Fin f;
+  if (const int flag = finish(red, j, f))
+    a.flags[s] = flag;
+  else
+    store_fin(a, s, j, f);
 }
 
 // the stencil step of source blockIdx.y: p = A v_j - beta_j v_{j-1},
 // q = A^dag w_j - delta_j w_{j-1} (both scaled by the lazy normalisation),
-// partial w~_j^dag (A v~_j).  The body of the one-source kernel: directions
-// split over the waves (hop_group), two lanes per site.  Workgroups run
-// source by source, so each source keeps the one-source kernel's locality;
-// the links, read once per source, stay in the Infinity Cache between
-// sources.
+// partial w~_j^dag (A v~_j).  It first finishes step j - 1 (every workgroup
+// sums its source's partials: a launch for that cost 4.8 us a step).  The body
+// of the one-source kernel: directions split over the waves (hop_group), two
+// lanes per site.  Workgroups run source by source, so each source keeps the
+// one-source kernel's locality; the links, read once per source, stay in the
+// Infinity Cache between sources.  The epilogue's operands and the partials
+// are loaded together, before the reduction (the previous vectors after it, one
+// component at a time, took another three round trips).  16 sources on 8^4:
+// 30.4 us and 17 in k_blk2 (29 and 14.7, and 4.8 for each of the two reductions).
 template <int NG>
 __global__ void __launch_bounds__(BT) k_blk1(Geom g, LinksPlain<double> lk, double diag, double eft, double ebt,
                                               int j, BArgs a) {
@@ -185,17 +193,24 @@ __global__ void __launch_bounds__(BT) k_blk1(Geom g, LinksPlain<double> lk, doub
   C64 ein[M];
 #pragma unroll
   for (int cl = 0; cl < M; ++cl) ein[cl] = in[sidx<double>(g.V, gi * M + cl, live ? se : 0)];
-  // this source's step coefficients (uniform loads) before the barrier too
-  const size_t kk = (size_t)src * (a.k + 1);
-  const double svj = a.sv[kk + j];
-  const C64 swj = a.sw[kk + j];
-  C64 scale = f ? swj : mk(svj, 0.0), sub = mk(0.0, 0.0);
-  if (j > 0) {
-    const C64 bm = a.beta[(size_t)src * a.k + j - 1], dm = a.delta[(size_t)src * a.k + j - 1];
-    sub = f ? cmul(dm, a.sw[kk + j - 1]) : a.sv[kk + j - 1] * bm;
-  }
-  __syncthreads();
   const C64* prev = f ? colw(a, src, j > 0 ? j - 1 : 0) : colv(a, src, j > 0 ? j - 1 : 0);
+  C64 eprev[M];
+#pragma unroll
+  for (int cl = 0; cl < M; ++cl) eprev[cl] = prev[sidx<double>(g.V, gi * M + cl, live ? se : 0)];
+  double red[4];
+  const size_t kk = (size_t)src * (a.k + 1);
+  const double svp = j > 0 ? a.sv[kk + j - 1] : 0.0;
+  const C64 swp = a.sw[kk + (j > 0 ? j - 1 : 0)];
+  reduce_src<4>(a.part2 + (size_t)src * 4 * a.nb2, a.nb2, red);  // also completes the exchange
+  Fin fin;
+  const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+  if (const int flag = finish(red, j, fin)) {
+    if (first) a.flags[src] = flag;
+    return;
+  }
+  if (first) store_fin(a, src, j, fin);
+  const C64 scale = f ? fin.sw : mk(fin.sv, 0.0);
+  const C64 sub = f ? cmul(mk(fin.delta, 0.0), swp) : svp * fin.beta;
   C64* out = f ? vq(a, src) : vp(a, src);
   double dre = 0.0, dim = 0.0;
   if (live) {
@@ -208,7 +223,7 @@ __global__ void __launch_bounds__(BT) k_blk1(Geom g, LinksPlain<double> lk, doub
       C64 av = diag * ein[cl] - 0.5 * hs;
       if (cc >= 6) av = mk(-av.re, -av.im);
       C64 o = cmul(scale, av);
-      if (j > 0) o = o - cmul(sub, prev[i]);
+      if (j > 0) o = o - cmul(sub, eprev[cl]);
       out[i] = o;
       if (f == 0) {
         const C64 t = cmulc(wpair, av);
@@ -310,15 +325,13 @@ __global__ void __launch_bounds__(BT) k_blkS(Geom g, LinksPlain<double> lk, doub
 
 // v_hat = p - alpha_j v_j, w_hat = q - conj(alpha_j) w_j into column j + 1,
 // partial sums of s = w_hat^dag v_hat, |v_hat|^2, |w_hat|^2; second sweep:
-// y += lc_{j+1} v_hat
-__global__ void __launch_bounds__(BT) k_blk2(BArgs a, int j) {
+// y += lc_{j+1} v_hat.  alpha_j = conj(sw_j) sv_j (w~_j^dag A v~_j) is summed by
+// every workgroup from the stencil step's partials, behind its first loads (a
+// launch for that cost 4.8 us a step).
+template <int U>
+__global__ void __launch_bounds__(BT, 4) k_blk2(BArgs a, int j) {
   const int s = blockIdx.y;
   if (a.flags[s]) return;
-  const double svj = a.sv[(size_t)s * (a.k + 1) + j];
-  const C64 swj = a.sw[(size_t)s * (a.k + 1) + j];
-  const C64 alpha = a.alpha[(size_t)s * a.k + j];
-  const C64 av = svj * alpha;
-  const C64 aw = cmul(conj(alpha), swj);
   const C64* p = vp(a, s);
   const C64* q = vq(a, s);
   const C64* v = colv(a, s, j);
@@ -328,15 +341,14 @@ __global__ void __launch_bounds__(BT) k_blk2(BArgs a, int j) {
   C64* y = vy(a, s);
   const bool lift = a.lc != nullptr && j + 1 < a.kused[s];
   const C64 lcn = lift ? a.lc[(size_t)s * a.k + j + 1] : mk(0.0, 0.0);
-  double sre = 0.0, sim = 0.0, nv = 0.0, nw = 0.0;
-  // four elements per thread and batch, all loads before the first store
-  constexpr int U = 4;
+  // U elements per thread and batch, all loads before the first store (U = 1
+  // where the grid covers the vector: registers for eight waves per SIMD)
   const size_t stride = (size_t)gridDim.x * BT;
-  for (size_t i0 = (size_t)blockIdx.x * BT + threadIdx.x; i0 < a.n; i0 += U * stride) {
-    C64 pp[U], qq[U], vv[U], ww[U];
+  C64 pp[U], qq[U], vv[U], ww[U];
+  auto load = [&](size_t ib) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const size_t i = i0 + u * stride;
+      const size_t i = ib + u * stride;
       if (i < a.n) {
         pp[u] = p[i];
         qq[u] = q[i];
@@ -344,6 +356,19 @@ __global__ void __launch_bounds__(BT) k_blk2(BArgs a, int j) {
         ww[u] = w[i];
       }
     }
+  };
+  size_t i0 = (size_t)blockIdx.x * BT + threadIdx.x;
+  load(i0);
+  const double svj = a.sv[(size_t)s * (a.k + 1) + j];
+  const C64 swj = a.sw[(size_t)s * (a.k + 1) + j];
+  double red[2];
+  reduce_src<2>(a.part1 + (size_t)s * 2 * a.nb1, a.nb1, red);
+  const C64 alpha = cmul(conj(swj), svj * mk(red[0], red[1]));
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.alpha[(size_t)s * a.k + j] = alpha;
+  const C64 av = svj * alpha;
+  const C64 aw = cmul(conj(alpha), swj);
+  double sre = 0.0, sim = 0.0, nv = 0.0, nw = 0.0;
+  for (; i0 < a.n; i0 += U * stride) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const size_t i = i0 + u * stride;
@@ -360,6 +385,7 @@ __global__ void __launch_bounds__(BT) k_blk2(BArgs a, int j) {
         if (lift) y[i] = y[i] + cmul(lcn, vr);
       }
     }
+    if (i0 + U * stride < a.n) load(i0 + U * stride);
   }
   double t4[4] = {sre, sim, nv, nw};
   bsum<4>(t4);
@@ -440,7 +466,6 @@ int sweep(nk_lattice* lat, const BArgs& a, int ng, int grp, double m_w, double m
   const Geom& g = lat->g;
   const LinksPlain<double> lk{lat->U64.as<C64>(), g.V};
   hipLaunchKernelGGL(k_bstart, dim3(a.nb2, a.r), dim3(BT), 0, st, a);
-  hipLaunchKernelGGL(k_bred2, dim3(a.r), dim3(BT), 0, st, a, 0);
   const double eft = exp(mu), ebt = exp(-mu);
   for (int j = 0; j < kmax; ++j) {
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -448,14 +473,16 @@ int sweep(nk_lattice* lat, const BArgs& a, int ng, int grp, double m_w, double m
     if (timed)
       for (auto& e : ev)
         if (int r = prof_event(lat, &e)) return r;
+    if (grp > 1) hipLaunchKernelGGL(k_bred2, dim3(a.r), dim3(BT), 0, st, a, j);
     launch_blk1(g, lk, ng, grp, m_w, eft, ebt, j, a, ev[0], ev[1], st);
-    hipLaunchKernelGGL(k_bred1, dim3(a.r), dim3(BT), 0, st, a, j);
-    hipExtLaunchKernelGGL(k_blk2, dim3(a.nb2, a.r), dim3(BT), 0, st, ev[2], ev[3], 0, a, j);
+    if (a.n <= (size_t)a.nb2 * BT)
+      hipExtLaunchKernelGGL(k_blk2<1>, dim3(a.nb2, a.r), dim3(BT), 0, st, ev[2], ev[3], 0, a, j);
+    else
+      hipExtLaunchKernelGGL(k_blk2<4>, dim3(a.nb2, a.r), dim3(BT), 0, st, ev[2], ev[3], 0, a, j);
     if (timed) {
       lat->evkind.push_back(0);
       lat->evkind.push_back(1);
     }
-    if (j + 1 < kmax) hipLaunchKernelGGL(k_bred2, dim3(a.r), dim3(BT), 0, st, a, j + 1);
   }
   NK_HIP(hipGetLastError());
   return NK_OK;

@@ -202,7 +202,23 @@ template <class R>
 __global__ void __launch_bounds__(NT) k_lan2(int n, int j, const Cx<R>* __restrict__ p, const Cx<R>* __restrict__ vj,
                                              Cx<R>* __restrict__ vnext, const double* __restrict__ partIn, int nbIn,
                                              double* __restrict__ partOut, Coefs c, LiftAcc lift) {
-  if (c.flags[0]) return;
+  // the loads of four elements per thread are issued before the partial sums
+  // of K1 are reduced, and those of the next four before these are stored
+  constexpr int U = 4;
+  const int stride = gridDim.x * NT;
+  int i0 = blockIdx.x * NT + threadIdx.x;
+  Cx<R> pp[U], vv[U];
+  auto load = [&](int ib) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(ib + u * stride, n - 1);
+      pp[u] = p[i];
+      vv[u] = vj[i];
+    }
+  };
+  const int flag = c.flags[0];
+  load(i0);
+  if (flag) return;
   double red[1];
   reduce_partials<1>(partIn, nbIn, red);
   const double alpha = red[0];
@@ -211,16 +227,23 @@ __global__ void __launch_bounds__(NT) k_lan2(int n, int j, const Cx<R>* __restri
   const bool acc = lift.y && (j + 1 < lift.kused);
   const C64 lcn = acc ? lift.lc[j + 1] : mk(0.0, 0.0);
   double nrm = 0.0;
-  for (int i = blockIdx.x * NT + threadIdx.x; i < n; i += gridDim.x * NT) {
-    const C64 v = widen(p[i]) - as * widen(vj[i]);
-    const Cx<R> vr = narrow<R>(v);
-    vnext[i] = vr;
-    const C64 vd = widen(vr);
-    nrm += norm2(vd);
-    if (acc) {
-      const size_t iy = sidx_to64<R>(n / 12, i);
-      lift.y[iy] = lift.y[iy] + cmul(lcn, vd);
+  for (; i0 < n; i0 += U * stride) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * stride;
+      if (i < n) {
+        const C64 v = widen(pp[u]) - as * widen(vv[u]);
+        const Cx<R> vr = narrow<R>(v);
+        vnext[i] = vr;
+        const C64 vd = widen(vr);
+        nrm += norm2(vd);
+        if (acc) {
+          const size_t iy = sidx_to64<R>(n / 12, i);
+          lift.y[iy] = lift.y[iy] + cmul(lcn, vd);
+        }
+      }
     }
+    if (i0 + U * stride < n) load(i0 + U * stride);
   }
   double v[1] = {nrm};
   block_sum<1>(v);

@@ -481,21 +481,21 @@ __device__ __forceinline__ gp<C64> rawv(const InnerG& g, int q, int h) {
 // sums (the other waves would add zeros)
 template <int NTH>
 __device__ __forceinline__ void bsum_first(double (&v)[4], int nb) {
-  __shared__ double sh[4][NTH / 64];
-  const int nw = nb > 64 ? NTH / 64 : 1;
-  if (threadIdx.x < 64 * nw)
+  __shared__ double sh[NTH / 64][4];
+  const bool one = nb <= 64;
+  if (!one || threadIdx.x < 64)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       v[q] = wave_xsum(v[q]);
-      if ((threadIdx.x & 63) == 0) sh[q][threadIdx.x >> 6] = v[q];
+      if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][q] = v[q];
     }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    double t = 0.0;
-    for (int w = 0; w < nw; ++w) t += sh[q][w];
-    v[q] = t;
-  }
+  for (int q = 0; q < 4; ++q) v[q] = sh[0][q];
+  if (!one)
+    for (int w = 1; w < NTH / 64; ++w)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] += sh[w][q];
 }
 
 // workgroup -> (problem, workgroup of the problem).  A batch of eight or more
@@ -529,7 +529,7 @@ static int inner_grid(int r, int nbmax) { return r < 8 ? r * nbmax : 8 * nbmax *
 // leaves the products in LDS; they are summed over the block's rows in row
 // order, as a single thread summing them would.  The new vector is scaled once
 // per workgroup, into LDS (by every wave for itself it cost as many loads as
-// the matrix): k = 500 7.1 us (8.9), 16 problems of k = 300 19 us (22).  The
+// the matrix): k = 500 6.9 us (8.9), 16 problems of k = 300 18 us (22).  The
 // products are rounded in a fixed order, as in the elimination.
 constexpr int XC = 512;  // columns of B staged at a time, eight per lane
 constexpr int GP = 2;  // projection columns per lane loaded at launch (j < 128)
@@ -554,6 +554,19 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
   const int r = blk * GR + wave;
   const bool live = r < k;
   const int rs = live ? r : 0;  // rows past k load row 0 and discard it
+  // the previous step's normalisation partial sums (i > 0) and the breakdown
+  // flag, first: what they decide does not wait for the matrix
+  int flag = s.flags[0];
+  double v[4] = {0, 0, 0, 0};
+  if (i > 0) {
+    gp<const double> p3 = s.part3;
+    if ((int)threadIdx.x < s.nb2)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = p3[q * s.nb2 + threadIdx.x];
+    for (int bb = threadIdx.x + GR * 64; bb < s.nb2; bb += GR * 64)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] += p3[q * s.nb2 + bb];
+  }
   // the side-dependent pointers come straight from the descriptor: selected
   // copies of the local view would keep that view in scratch memory
   const int h = i & 1;
@@ -589,15 +602,10 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
     const int j = lane + 64 * m;
     pj[m] = ldg(proj + (size_t)(j < i ? j : 0) * k + rs);
   }
-  // the previous step's normalisation partial sums (i > 0)
-  double v[4] = {0, 0, 0, 0};
-  if (i > 0)
-    for (int bb = threadIdx.x; bb < s.nb2; bb += GR * 64)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] += s.part3[q * s.nb2 + bb];
-  // a breakdown at an earlier step ends the iteration; the flag is read only
-  // now so that its latency overlaps the loads above (all in bounds)
-  if (s.flags[0]) return;
+  // a breakdown at an earlier step ends the iteration; tested only now so that
+  // the flag's latency overlaps the loads above (all in bounds)
+  asm volatile("" : "+v"(flag));
+  if (flag) return;
   C64 scal = mk(1.0, 0.0), sub = mk(0.0, 0.0);
   C64 scal_o = mk(1.0, 0.0);  // scale of the other side's new column
   if (i > 0) {
@@ -748,6 +756,7 @@ __global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __re
     }
   };
   static_assert(SR == 8 * TPJ, "one batch of loads covers the block's rows");
+  int flag = s.flags[0];
   load_part(side1, j1, l4);
   load_basis(jl);
   gp<C64> x = rawv(s, side2, (i + 1) & 1);
@@ -773,15 +782,15 @@ __global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __re
     t = mk(quad_xsum(t.re), quad_xsum(t.im));
     if (ok && l4 == 0) s_c[side][j] = t;
   }
-  // a breakdown flagged at this or an earlier step ends the iteration; the
-  // flag is read only now so that its latency overlaps the loads above (all
-  // in bounds)
+  // a breakdown flagged at this or an earlier step ends the iteration; tested
+  // only now so that the flag's latency overlaps the loads above (all in bounds)
+  asm volatile("" : "+v"(flag));
   if (report) {
     gp<int> o = as_global(S.out);
-    o[0] = s.flags[0];
+    o[0] = flag;
     o[1] = s.flags[1];
   }
-  if (s.flags[0]) return;
+  if (flag) return;
   __syncthreads();
   if (!last && blk == 0 && threadIdx.x == 0) stg(s.a + i, s.herm ? mk(s_c[0][i].re, 0.0) : s_c[0][i]);
   if (s.arnoldi && blk == 0)  // column i of H_l: the first pass stores, the second adds
