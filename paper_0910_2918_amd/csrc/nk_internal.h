@@ -85,6 +85,15 @@ __host__ __device__ __forceinline__ Cx<R> narrow(Cx<double> a) { return mk<R>((R
 //   tile = ((TT n2 + TZ) n1 + TY) n0 + TX,
 // so that one workgroup's sites form a compact hypercube whose neighbours
 // mostly lie in the same tile (and in cache).
+// a store that does not keep its line in the L2: for results of a pass that
+// reads more than the caches hold
+template <class R>
+__device__ __forceinline__ void store_nt(Cx<R>* p, Cx<R> v) {
+  typedef R v2 __attribute__((ext_vector_type(2)));
+  const v2 t = {v.re, v.im};
+  __builtin_nontemporal_store(t, reinterpret_cast<v2*>(p));
+}
+
 struct Geom {
   int L[4];
   int stride[4];  // canonical strides 1, Lx, Lx Ly, Lx Ly Lz

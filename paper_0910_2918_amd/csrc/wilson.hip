@@ -8,7 +8,11 @@ namespace nk {
 
 // y_f = [gamma5] ((4 + m_w) x_f - 1/2 hop(x_f)) for NF fields, device layout.
 // Directions split over the waves of the workgroup (hop_group); NF lanes per
-// site, lane f on field f.
+// site, lane f on field f.  Bound by the caches: an XCD's 4 MB L2 holds about
+// eight tiles' links and spinors, so the spinors that cross a tile in z and t
+// are fetched again (573 MB read for 318 on 24^4).  The pair's results, which
+// would take a fifth of that L2, are stored past it: 24^4 150 -> 139 us, 16^4
+// 24.3 -> 23.7.
 template <class R, int NF, class LK, int NG>
 __global__ void __launch_bounds__(256) k_apply(Geom g, LK lk, R diag, int g5, FieldPtrs<R, NF> in,
                                                 FieldPtrsW<R, NF> out, TFac<R, NF> tf) {
@@ -45,7 +49,10 @@ __global__ void __launch_bounds__(256) k_apply(Geom g, LK lk, R diag, int g5, Fi
     const size_t i = sidx<R>(g.V, cc, se);
     Cx<R> o = diag * ein[cl] - R(0.5) * hs;
     if (g5 && cc >= 6) o = mk<R>(-o.re, -o.im);
-    y[i] = o;
+    if (NF == 2)
+      store_nt(&y[i], o);
+    else
+      y[i] = o;
   }
 }
 
@@ -114,7 +121,10 @@ __global__ void __launch_bounds__(256) k_apply_block(Geom g, LinksPlain<double> 
 // and whole x lines of sites behind each other.  CIN: the input is canonical
 // too, each lane reading its neighbours' 192 bytes where they lie (twelve loads
 // that share their lines; the L1 holds a wave's 12 KB of them); grid y =
-// vector.  That spares the packing launch and its pass over memory.
+// vector.  That spares the packing launch and its pass over memory.  The
+// results are stored past the L2, which the neighbours and links need: 24^4 96
+// -> 79 us, 16^4 18.8 -> 17.8 (y read back by the next application: 98.6 ->
+// 91.4, 19.0 -> 18.8).
 template <int NG, bool CIN>
 __global__ void __launch_bounds__(256) k_apply_canon(Geom g, LinksPlain<double> lk, double diag, int g5, const C64* in,
                                                      C64* out, double ef, double eb) {
@@ -162,7 +172,7 @@ __global__ void __launch_bounds__(256) k_apply_canon(Geom g, LinksPlain<double> 
 #pragma unroll
   for (int m = 0; m < SITES * 12 / 256; ++m) {
     const int e = threadIdx.x + 256 * m, q = e / 12, c = e % 12;
-    if (s0 + q < g.V) y[(size_t)s_can[q] * 12 + c] = sh.y[q][c];
+    if (s0 + q < g.V) store_nt(&y[(size_t)s_can[q] * 12 + c], sh.y[q][c]);
   }
 }
 
@@ -197,8 +207,8 @@ int apply_dw_dev(nk_lattice* lat, double m_w, double mu, int g5, const C64* x, C
 // apart, since it writes y while it reads x; where they overlap, each x is
 // packed into tmp(), one vector, before its y is written, one vector after the
 // other.  Measured (one vector; through the packed layout with this epilogue;
-// pack, stencil and unpack): 4096 sites 7.4, 10.8, 12.6 us; 65536 18.8, 23.2,
-// 31.0; 331776 96, 114, 157.
+// pack, stencil and unpack; the first two with results kept in the L2): 4096
+// sites 7.4, 10.8, 12.6 us; 65536 18.8, 23.2, 31.0; 331776 96, 114, 157.
 int apply_canon_dev(nk_lattice* lat, double m_w, double mu, int g5, const C64* x, C64* y, int nrhs,
                     int (*tmp)(nk_lattice*, C64**), hipStream_t st) {
   if (int e = check_gauge(lat)) return e;
