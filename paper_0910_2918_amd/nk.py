@@ -146,19 +146,21 @@ class nk_sign_info(C.Structure):
 
 
 _lib = None
+_torch = None  # set with _lib
 
 
 def library():
     """Load libnk.so (once); raise NKLibraryMissing if it is not built."""
-    global _lib
+    global _lib, _torch
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise NKLibraryMissing(f"{LIB_PATH} is not built; run python -m paper_0910_2918_amd.build")
     # torch ships its own HIP runtime; load it first so that libnk.so binds to
     # the same libamdhip64 instead of pulling a second runtime into the process
-    import torch  # noqa: F401
+    import torch
 
+    _torch = torch
     lib = C.CDLL(LIB_PATH)
     vp, i32, dbl = C.c_void_p, C.c_int32, C.c_double
     P = C.POINTER
@@ -222,20 +224,27 @@ def _check(rc: int) -> int:
 
 
 def _stream(stream):
+    """Handle of a stream (None: torch's current one), as an integer: ctypes turns it into the pointer argument."""
     if stream is None:
-        import torch
+        return _current_stream()
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)
+
+def _current_stream() -> int:
+    # torch.cuda.current_stream() builds a Stream object for each call (1 us
+    # of a small operator call's 7.6); its two lookups alone are enough once
+    # the device is initialised
+    c = _torch._C
+    if _torch.cuda.is_initialized() and hasattr(c, "_cuda_getCurrentRawStream"):
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return _torch.cuda.current_stream().cuda_stream
 
 
 def _dptr(t):
-    """Device pointer of a contiguous complex128 CUDA tensor."""
-    if not t.is_cuda or not t.is_contiguous() or str(t.dtype) != "torch.complex128":
+    """Device pointer of a contiguous complex128 CUDA tensor, as an integer."""
+    if not t.is_cuda or not t.is_contiguous() or t.dtype != _torch.complex128:
         raise ValueError("expected a contiguous complex128 CUDA tensor")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _hptr(a: np.ndarray):
@@ -422,9 +431,9 @@ def nk_inner_matrix(k: int, ell: int, hermitian: bool, alpha, beta, delta):
 
 def _fptr(t):
     """Device pointer of a contiguous float32 CUDA tensor."""
-    if not t.is_cuda or not t.is_contiguous() or str(t.dtype) != "torch.float32":
+    if not t.is_cuda or not t.is_contiguous() or t.dtype != _torch.float32:
         raise ValueError("expected a contiguous float32 CUDA tensor")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _iptr(t):
