@@ -184,82 +184,99 @@ __global__ void __launch_bounds__(256) k_rh_features(int ld, const int* __restri
 }
 
 // ---------------------------------------------------------------------------
-// forward pass: 16 samples per 256-thread workgroup on the FP32 matrix cores
-// (v_mfma_f32_16x16x4f32, FP32 accumulation); wave w finishes units
-// 16 w .. 16 w + 15 of a hidden layer, wave 0 the output layer.  Operand
-// layout: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16], accumulator
-// element i of lane l is D[4 (l / 16) + i][l % 16].  The products of a layer
-// of NV inputs are dealt so that lane group q = l / 16 takes the inputs
-// q NV/4 .. (q + 1) NV/4 - 1: a lane then reads contiguous runs of its weight
-// row (16-byte loads) and of its sample's activations.
+// forward pass: 16 samples per 256-thread workgroup on the FP64 matrix cores
+// (v_mfma_f64_16x16x4f64), rounded to FP32 only where y and the activations
+// are stored: the spectral loss multiplies an error of y by up to a hundred,
+// and with FP32 sums and activations (2.3e-7 of y) the gradient of a few
+// samples was off by a few 1e-6; now 2.5e-8 of y and 1e-7.  Wave w finishes units 16 w ..
+// 16 w + 15 of a hidden layer, wave 0 the output layer.  Operand layout: lane
+// l holds A[l % 16][l / 16] and B[l / 16][l % 16], accumulator element i of
+// lane l is D[4 i + l / 16][l % 16].  The products of a layer of NV inputs are
+// dealt so that lane group q = l / 16 takes the inputs q NV/4 ..
+// (q + 1) NV/4 - 1: a lane then reads contiguous runs of its weight row
+// (16-byte loads) and of its sample's activations.
 // Bound by latency (three layers, one weight read each): with one lane per
 // unit, as this kernel was before, every lane walked its own weight row in
 // 4-byte loads, 64 cache lines per load, and a layer took 64 of them; 12.7 us
-// for 2048 samples, now 8.3.
+// for 2048 samples, now 9.0 (11.4 with tanh(), 8.3 in FP32).
 // act (optional) keeps a1, a2, a3 for the backward pass.
 typedef float nk_f4 __attribute__((ext_vector_type(4)));
+typedef double nk_d4 __attribute__((ext_vector_type(4)));
 constexpr int FS = 16;       // samples per workgroup
-constexpr int FLD = MH + 4;  // padded row of activations (16-byte aligned)
+constexpr int FLD = MH + 2;  // padded row of activations (16-byte aligned)
 
-// the pre-activations of the 16 samples (rows of in, leading dimension FLD)
-// and 16 units whose weight rows start at W (leading dimension NV); units past
-// nu read row 0 and are ignored by the caller
+// tanh to a few 1e-16, absolute, and to as much relative to its value below
+// 2^-10 (three terms of the series): half the instructions of tanh(), which
+// were most of the kernel's time
+__device__ __forceinline__ double tanh_of(double x) {
+  const double x2 = x * x;
+  const double s = x * fma(x2, fma(x2, 2.0 / 15.0, -1.0 / 3.0), 1.0);
+  const double t = 1.0 - 2.0 / (exp(2.0 * x) + 1.0);
+  return fabs(x) < 0x1p-10 ? s : t;
+}
+
+// this lane's weights of 16 units, whose rows of NV start at W; units past nu
+// read row 0 and are ignored by the caller
 template <int NV>
-__device__ __forceinline__ nk_f4 layer16(const float* __restrict__ W, int nu, const float* in, int lane) {
-  const int l16 = lane & 15, q = lane >> 4;
-  constexpr int NK = NV / 4;
-  const float* wr = W + (size_t)(l16 < nu ? l16 : 0) * NV + q * NK;
-  const float* ar = in + l16 * FLD + q * NK;
-  nk_f4 wv[NK / 4], av[NK / 4];
+__device__ __forceinline__ void weights16(const float* __restrict__ W, int nu, int lane, float (&wv)[NV / 4]) {
+  const int l16 = lane & 15;
+  const float* wr = W + (size_t)(l16 < nu ? l16 : 0) * NV + (lane >> 4) * (NV / 4);
 #pragma unroll
-  for (int c = 0; c < NK / 4; ++c) {
-    // the flat parameter array gives no more than 4-byte alignment
-    wv[c] = nk_f4{wr[4 * c], wr[4 * c + 1], wr[4 * c + 2], wr[4 * c + 3]};
-    av[c] = *reinterpret_cast<const nk_f4*>(ar + 4 * c);
-  }
-  nk_f4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < NV / 4; ++c) wv[c] = wr[c];  // (the flat parameter array gives no more than 4-byte alignment)
+}
+// the pre-activations of the 16 samples (rows of in, leading dimension FLD) and those units
+template <int NV>
+__device__ __forceinline__ nk_d4 layer16(const float (&wv)[NV / 4], const double* in, int lane) {
+  const double* ar = in + (lane & 15) * FLD + (lane >> 4) * (NV / 4);
+  nk_d4 acc[4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
-  for (int c = 0; c < NK / 4; ++c)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c][e], wv[c][e], acc, 0, 0, 0);
-  return acc;
+  for (int c = 0; c < NV / 4; ++c)
+    acc[c & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[c], (double)wv[c], acc[c & 3], 0, 0, 0);
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
 __global__ void __launch_bounds__(256) k_mlp_fwd(int B, const float* __restrict__ P, const float* __restrict__ feat,
                                                  float* __restrict__ y, float* __restrict__ act) {
-  __shared__ __align__(16) float sx[FS][FLD];
-  __shared__ __align__(16) float sa[2][FS][FLD];
+  __shared__ __align__(16) double sx[FS][FLD];
+  __shared__ __align__(16) double sa[2][FS][FLD];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int b0 = blockIdx.x * FS;
+  const int u = 16 * w + (lane & 15), r0 = lane >> 4;  // this lane's unit, and its samples r0 + 4 i
+  // every layer's weights are known at launch: one memory round trip for all
+  float w1[MI / 4], w2[MH / 4], w3[MH / 4], w4[MH / 4];
+  weights16<MI>(P + OW1 + 16 * w * MI, 16, lane, w1);
+  weights16<MH>(P + OW2 + 16 * w * MH, 16, lane, w2);
+  weights16<MH>(P + OW3 + 16 * w * MH, 16, lane, w3);
+  weights16<MH>(P + OW4, MT, lane, w4);
+  const float h1 = P[OB1 + u], h2 = P[OB2 + u], h3 = P[OB3 + u], h4 = P[OB4 + min(lane & 15, MT - 1)];
   {
     const int sl = tid / MI, v = tid % MI;  // 16 samples x 16 features
     const int b = b0 + sl;
-    sx[sl][v] = b < B ? (feat[(size_t)b * MI + v] - P[OMEAN + v]) * P[OISTD + v] : 0.f;
+    sx[sl][v] = b < B ? ((double)feat[(size_t)b * MI + v] - (double)P[OMEAN + v]) * (double)P[OISTD + v] : 0.0;
   }
   __syncthreads();
-  const int u = 16 * w + (lane & 15), r0 = 4 * (lane >> 4);
-  auto finish = [&](nk_f4 h, float bias, int layer, float (*out)[FLD]) {
+  auto finish = [&](nk_d4 h, float bias, int layer, double (*out)[FLD]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float a = tanhf(h[i] + bias);
-      const int b = b0 + r0 + i;
-      out[r0 + i][u] = a;
-      if (act && b < B) act[((size_t)b * 3 + layer) * MH + u] = a;
+      const double a = tanh_of(h[i] + (double)bias);
+      const int r = r0 + 4 * i, b = b0 + r;
+      out[r][u] = a;
+      if (act && b < B) act[((size_t)b * 3 + layer) * MH + u] = (float)a;
     }
   };
-  finish(layer16<MI>(P + OW1 + 16 * w * MI, 16, &sx[0][0], lane), P[OB1 + u], 0, sa[0]);
+  finish(layer16<MI>(w1, &sx[0][0], lane), h1, 0, sa[0]);
   __syncthreads();
-  finish(layer16<MH>(P + OW2 + 16 * w * MH, 16, &sa[0][0][0], lane), P[OB2 + u], 1, sa[1]);
+  finish(layer16<MH>(w2, &sa[0][0][0], lane), h2, 1, sa[1]);
   __syncthreads();
-  finish(layer16<MH>(P + OW3 + 16 * w * MH, 16, &sa[1][0][0], lane), P[OB3 + u], 2, sa[0]);
+  finish(layer16<MH>(w3, &sa[1][0][0], lane), h3, 2, sa[0]);
   __syncthreads();
   if (w == 0) {
-    const nk_f4 o = layer16<MH>(P + OW4, MT, &sa[0][0][0], lane);
+    const nk_d4 o = layer16<MH>(w4, &sa[0][0][0], lane);
     const int t = lane & 15;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int b = b0 + r0 + i;
-      if (t < MT && b < B) y[(size_t)b * MT + t] = o[i] + P[OB4 + t];
+      const int b = b0 + r0 + 4 * i;
+      if (t < MT && b < B) y[(size_t)b * MT + t] = (float)(o[i] + (double)h4);
     }
   }
 }
@@ -416,7 +433,7 @@ __global__ void __launch_bounds__(256) k_mlp_delta(int B, const float* __restric
 }
 
 // backward, step 2: the weight gradients sum_b delta[b][u] in[b][v] as matrix
-// products over the batch on the FP32 matrix cores (layout as in k_mlp_fwd:
+// products over the batch on the FP32 matrix cores (layout:
 // A = delta^T, B = the layer's input).  One workgroup of 16 waves per 16 x 16
 // tile of a weight matrix: 4 tiles of W1, 16 of W2, 16 of W3 and 4 of W4 (its
 // 4 rows of 16).  Wave w takes samples 4 w .. 4 w + 3 of every 64, one product
