@@ -50,7 +50,7 @@
 //     the sums of the stopping test.
 // Measured for k = 500, nine steps (511 poles): 37 + 29 + 8 + 53 us, where the
 // blocked elimination and its Newton-Schulz tail took 5.2 ms; for k = 60, ten
-// steps 9 + 18 + 3 + 39 us (the one-workgroup elimination: 455 to 600).
+// steps 9 + 18 + 3 + 28 us (the one-workgroup elimination: 455 to 600).
 #include <algorithm>
 #include <cmath>
 
@@ -472,7 +472,7 @@ __global__ void __launch_bounds__(64) k_tri_between(TriWs w, const int* __restri
 }
 
 // S_1 .. S_L of one 16 x 16 tile (rows of block c, columns of block C), or of
-// one part of a tile on the diagonal.  Per step the four waves share the
+// one part of a tile on the diagonal.  Per step the waves share the
 // poles, on the matrix cores (layout: lane l holds A[l % 16][l / 16],
 // B[l / 16][l % 16] and D[4 i + l / 16][l % 16]); the partial sums meet in LDS, where
 // every thread owns one entry of the tile, takes it from S_n to S_{n+1} and
@@ -481,10 +481,10 @@ __global__ void __launch_bounds__(64) k_tri_between(TriWs w, const int* __restri
 // inverse goes through memory (kept as partial sums per 16 poles, in an
 // earlier form, they were 140 MB written and read at k = 500, 140 + 37 us).
 constexpr int TLMAX = 10;
-constexpr int RSLOTS = 8;  // partial tiles in LDS: of the first six steps, later two sets of four
 constexpr int TPARTS = 9;  // parts of a diagonal tile: halves of 16, 8, 4, 2 rows above, then below, then the diagonal
-__global__ void __launch_bounds__(256, 3) k_tri_tile(TriWs w, const int* __restrict__ nvec, int L, C64* S_b) {
-  __shared__ C64 red[RSLOTS][TB][TB + 1];
+template <int NW>
+__global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 4) k_tri_tile(TriWs w, const int* __restrict__ nvec, int L, C64* S_b) {
+  __shared__ C64 red[2 * NW][TB][TB + 1];  // partial tiles: of the first six steps, later two sets, one per wave
   __shared__ double sred[4][2 * TLMAX];
   const int b = blockIdx.z, n = nvec[b];
   // workgroups: the parts of the diagonal tiles, then the other tiles row by row
@@ -501,8 +501,8 @@ __global__ void __launch_bounds__(256, 3) k_tri_tile(TriWs w, const int* __restr
   }
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, lq = lane >> 4;
-  const int er = threadIdx.x >> 4, ec = threadIdx.x & 15;  // the entry this thread owns
-  bool own = c * TB + er < n && C * TB + ec < n;
+  const int er = (threadIdx.x >> 4) & 15, ec = threadIdx.x & 15;  // the entry this thread (of the first four waves) owns
+  bool own = wv < 4 && c * TB + er < n && C * TB + ec < n;
   const int ldp = w.nch * TB;
   const C64 *A, *B;
   const C64* R = nullptr;
@@ -598,27 +598,32 @@ __global__ void __launch_bounds__(256, 3) k_tri_tile(TriWs w, const int* __restr
     for (int m = 0; m < 6; ++m)
       if (m < L) update(m, red[m][er][ec]);
     __syncthreads();
-    // the others, a step's poles dealt to the four waves
+    // the others, a step's poles dealt to the waves
 #pragma unroll
     for (int m = 6; m < TLMAX; ++m) {
       if (m < L) {
         zero();
-        for (int g = (1 << m) + 16 * wv; g < 2 << m; g += 64) {
+        for (int g = (1 << m) + 16 * wv; g < 2 << m; g += 16 * NW) {
           const Ops o = load(g);
 #pragma unroll
           for (int u = 0; u < 4; ++u) mac(o.x[u], o.b[u]);
         }
-        const int s0 = 4 * (m & 1);  // two sets of slots: one barrier per step
+        const int s0 = NW * (m & 1);  // two sets of slots: one barrier per step
         put(s0 + wv);
         __syncthreads();
-        update(m, (red[s0][er][ec] + red[s0 + 1][er][ec]) + (red[s0 + 2][er][ec] + red[s0 + 3][er][ec]));
+        C64 T = mk(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < NW; q += 4)
+          if ((1 << m) > 16 * q)  // (waves past the step's poles leave zeros)
+            T = T + ((red[s0 + q][er][ec] + red[s0 + q + 1][er][ec]) + (red[s0 + q + 2][er][ec] + red[s0 + q + 3][er][ec]));
+        update(m, T);
       }
     }
     if (own) S_b[so] = s;
   }
 #pragma unroll
   for (int m = 0; m < TLMAX; ++m) {
-    if (m < L) {
+    if (m < L && wv < 4) {
       const double d = wave_sum(ds[m]), e = wave_sum(ns[m]);
       if (lane == 0) {
         sred[wv][2 * m] = d;
@@ -718,7 +723,15 @@ int tri_rh_run(int batch, int ld, int maxn, const int* nvec, const TriIn& h, C64
     hipLaunchKernelGGL(k_tri_chain_mu, dim3(1, 1, batch), dim3(512), 0, st, w, h, nvec, L, sched, nsched);
   hipLaunchKernelGGL(k_tri_mid, dim3(pb, 2 * y.nch, batch), dim3(64), 0, st, w, h, nvec);
   if (y.nch > 1) hipLaunchKernelGGL(k_tri_between, dim3(pb, 2 * y.nch, batch), dim3(64), 0, st, w, nvec);
-  hipLaunchKernelGGL(k_tri_tile, dim3(y.ntask, 1, batch), dim3(256), 0, st, w, nvec, L, S);
+  // At most one workgroup per CU: sixteen waves for a tile, a step's poles in a
+  // quarter of the turns.  More workgroups fill the chip themselves, three of
+  // four waves to a CU.  Sixteen waves against four: n = 60 (48 workgroups)
+  // 27 and 38 us, n = 190 (240) 21 and 26, n = 230 (345) 34 and 28, n = 500
+  // (1280) 94 and 54.
+  if (y.ntask * batch <= 256)
+    hipLaunchKernelGGL(k_tri_tile<16>, dim3(y.ntask, 1, batch), dim3(1024), 0, st, w, nvec, L, S);
+  else
+    hipLaunchKernelGGL(k_tri_tile<4>, dim3(y.ntask, 1, batch), dim3(256), 0, st, w, nvec, L, S);
   hipLaunchKernelGGL(k_tri_sums, dim3(2 * L, batch), dim3(64), 0, st, w, g_tri_pin.dev<double>());
   NK_HIP(hipGetLastError());
   *sums = g_tri_pin.host<double>();
