@@ -566,21 +566,14 @@ int nk_small_sign(int32_t k, int32_t ell, int32_t hermitian, const double* alpha
   nk_sign_params dp;
   nk_sign_params_default(&dp);
   if (!p) p = &dp;
-  ScopedBuf buf;
-  if (buf.ensure((size_t)4 * k * sizeof(C64))) return NK_ENOMEM;
-  C64* a = buf.as<C64>();
-  NK_HIP(hipMemcpy(a, alpha, k * sizeof(C64), hipMemcpyHostToDevice));
-  NK_HIP(hipMemcpy(a + k, beta, k * sizeof(C64), hipMemcpyHostToDevice));
-  NK_HIP(hipMemcpy(a + 2 * k, delta, k * sizeof(C64), hipMemcpyHostToDevice));
   SmallOut so;
   if (p->inner < 0 || p->inner > 1) {
     set_error("invalid inner basis %d", p->inner);
     return NK_EINVAL;
   }
-  int e = small_sign_dev(k, ell, hermitian, a, a + k, a + 2 * k, p->rh_scaling, p->rh_maxit, p->rh_tol, a + 3 * k,
-                         &so, nullptr, p->inner);
+  int e = small_sign_host(k, ell, hermitian, alpha, beta, delta, p->rh_scaling, p->rh_maxit, p->rh_tol, z, &so,
+                          p->inner);
   if (e < 0) return e;
-  NK_HIP(hipMemcpy(z, a + 3 * k, k * sizeof(C64), hipMemcpyDeviceToHost));
   if (info) {
     std::memset(info, 0, sizeof *info);
     info->k_used = k;

@@ -352,6 +352,10 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
                    int rh_scaling, int rh_maxit, double rh_tol, C64* z, SmallOut* out, hipStream_t st,
                    int inner = NK_INNER_SAME);
 
+// the same on host coefficients and result (k complex each)
+int small_sign_host(int k, int ell, int hermitian, const void* alpha, const void* beta, const void* delta,
+                    int rh_scaling, int rh_maxit, double rh_tol, void* z, SmallOut* out, int inner);
+
 // the inner projections of r problems at once: problem s has its H_k at
 // alpha/beta/delta + s * cstride (see small.hip)
 int small_inner_batch(int r, const int* k, const int* ell, int hermitian, const C64* alpha, const C64* beta,

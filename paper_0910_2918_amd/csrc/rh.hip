@@ -1001,21 +1001,30 @@ int rh_tile_choice(int maxn, int batch, int* nb, int* rm, int* pth, int* tile) {
   return 1;
 }
 
+// the orders of a batch from (mapped) host memory, and its flags cleared: one
+// launch in the place of a copy and a fill, which take a place in the stream
+// of some 10 us each
+__global__ void k_rh_begin(int batch, const int* __restrict__ n_host, int* __restrict__ nvec, int* __restrict__ sing,
+                           int* __restrict__ ones) {
+  for (int b = threadIdx.x; b < batch; b += blockDim.x) {
+    nvec[b] = n_host[b];
+    sing[b] = 0;
+    ones[b] = 1;
+  }
+}
+
 // |S^2 - I|_F / sqrt(n) of every matrix of the batch into resid_host: one
 // product S S on the matrix cores (k_ns_gemm<0>, which leaves 3 I - S^2 in the
 // scratch buffer G0 and the partial sums of |I - S^2|_F^2), then the sums,
 // written by k_rh_resid_sum straight into pinned host memory
-static int rh_residuals(int batch, int maxn, int ld, const int* nvec, const C64* S, double* resid_host,
-                        hipStream_t st) {  // waits for the stream
+static int rh_residuals(int batch, int maxn, int ld, const int* nvec, const int* all, const C64* S, double* resid_host,
+                        hipStream_t st) {  // all: ones; waits for the stream
   const int ntile = (maxn + 31) / 32;
   const size_t nsp = (size_t)batch * ntile * ntile * 2;
+  // (room for the large path's flags behind the sums, which it takes from the same buffer)
   if (g_nsp.ensure(nsp * sizeof(double) + (size_t)batch * sizeof(int))) return NK_ENOMEM;
-  if (g_pinr.ensure((size_t)batch * (sizeof(double) + sizeof(int)))) return NK_ENOMEM;
+  if (g_pinr.ensure((size_t)batch * sizeof(double))) return NK_ENOMEM;
   double* part = g_nsp.as<double>();
-  int* all = reinterpret_cast<int*>(part + nsp);
-  int* ones = reinterpret_cast<int*>(g_pinr.host<double>() + batch);
-  std::fill(ones, ones + batch, 1);
-  NK_HIP(hipMemcpyAsync(all, ones, batch * sizeof(int), hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(k_ns_gemm<0>, dim3(ntile, ntile, batch), dim3(256), 0, st, ld, nvec, all, S, S, g_G0.as<C64>(),
                      part);
   hipLaunchKernelGGL(k_rh_resid_sum, dim3(batch), dim3(256), 0, st, ntile * ntile, nvec, part, g_pinr.dev<double>());
@@ -1043,6 +1052,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
   int* sing = act + batch;
   int* rowof = sing + batch;
   int* posof = rowof + (size_t)batch * ld;
+  int* ones = posof + (size_t)batch * ld;
   double* logdet = g_dbl.as<double>();
   double* resid = logdet + batch;
   double* part = resid + batch;
@@ -1074,7 +1084,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
   for (int b = 0; b < batch; ++b) maxn = std::max(maxn, n_host[b]);
   std::copy(n_host, n_host + batch, pin_n);
   std::fill(pin_zero, pin_zero + batch, 0);
-  NK_HIP(hipMemcpyAsync(nvec, pin_n, batch * sizeof(int), hipMemcpyHostToDevice, st));
+  hipLaunchKernelGGL(k_rh_begin, dim3(1), dim3(256), 0, st, batch, g_pin.dev<int>(), nvec, sing, ones);
   // learned scaling: the installed model's factors for the first steps of
   // each matrix, predicted from S_0 (without a model: determinant scaling)
   const int mu_steps = NK_MLP_STEPS;
@@ -1093,11 +1103,11 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
   std::vector<double> change0(batch, INFINITY);
   if (const int L = tri ? tri_rh_steps(batch, ld, maxn, scaling, maxit) : 0) {
     const double* sums = nullptr;
-    const int e = tri_rh_run(batch, ld, maxn, nvec, *tri, S, scaling, mdev, mu_steps, L, &sums, st);
+    const int e = tri_rh_run(batch, ld, maxn, nvec, sing, *tri, S, scaling, mdev, mu_steps, L, &sums, st);
     if (e < 0) return e;
     if (e == 0) {  // (1: no memory for its workspace)
       if (resid_host) {
-        if (int e2 = rh_residuals(batch, maxn, ld, nvec, S, resid_host, st)) return e2;
+        if (int e2 = rh_residuals(batch, maxn, ld, nvec, ones, S, resid_host, st)) return e2;
       } else {
         NK_HIP(hipStreamSynchronize(st));
       }
@@ -1172,7 +1182,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
     NK_HIP(hipMemcpyAsync(pin_iters, act, batch * sizeof(int), hipMemcpyDeviceToHost, st));
     NK_HIP(hipMemcpyAsync(pin_state, sing, batch * sizeof(int), hipMemcpyDeviceToHost, st));
     if (resid_host)
-      if (int e = rh_residuals(batch, maxn, ld, nvec, S, resid_host, st)) return e;
+      if (int e = rh_residuals(batch, maxn, ld, nvec, ones, S, resid_host, st)) return e;
     NK_HIP(hipStreamSynchronize(st));
     for (int b = 0; b < batch; ++b)
       if (!done[b]) {
@@ -1316,7 +1326,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
   }
   NK_HIP(hipMemcpyAsync(pin_state, sing, batch * sizeof(int), hipMemcpyDeviceToHost, st));
   if (resid_host)
-    if (int e = rh_residuals(batch, maxn, ld, nvec, S, resid_host, st)) return e;
+    if (int e = rh_residuals(batch, maxn, ld, nvec, ones, S, resid_host, st)) return e;
   NK_HIP(hipStreamSynchronize(st));
   for (int b = 0; b < batch; ++b) {
     if (!done[b]) state[b] = pin_state[b];

@@ -668,8 +668,7 @@ Layout tri_layout(int batch, int ld, int maxn, int L) {
   y.ntask = y.nch * TPARTS + y.nch * (y.nch - 1);
   const size_t el = (2 * (TB + 2) + 13 * TB) * (size_t)y.nch * batch * y.np + (size_t)batch * y.nch * (2 + y.nch) * y.np;
   y.bytes = el * sizeof(C64) +
-            (2 * (size_t)batch * y.np + (size_t)batch * L + (size_t)batch * 2 * L * y.ntask) * sizeof(double) +
-            (size_t)batch * sizeof(int) + 256;
+            (2 * (size_t)batch * y.np + (size_t)batch * L + (size_t)batch * 2 * L * y.ntask) * sizeof(double) + 256;
   return y;
 }
 
@@ -689,8 +688,8 @@ int tri_rh_steps(int batch, int ld, int maxn, int scaling, int maxit) {
   return L >= std::min(5, maxit) ? L : 0;
 }
 
-int tri_rh_run(int batch, int ld, int maxn, const int* nvec, const TriIn& h, C64* S, int scaling, const double* sched,
-               int nsched, int L, const double** sums, hipStream_t st) {
+int tri_rh_run(int batch, int ld, int maxn, const int* nvec, int* sing, const TriIn& h, C64* S, int scaling,
+               const double* sched, int nsched, int L, const double** sums, hipStream_t st) {
   const Layout y = tri_layout(batch, ld, maxn, L);
   if (g_tri.ensure(y.bytes) || g_tri_pin.ensure((size_t)batch * (2 * L + 1) * sizeof(double))) return 1;
   TriWs w{};
@@ -714,8 +713,7 @@ int tri_rh_run(int batch, int ld, int maxn, const int* nvec, const TriIn& h, C64
   w.kap = w.rho + (size_t)batch * y.np;
   w.mu = w.kap + (size_t)batch * y.np;
   w.sums = w.mu + (size_t)batch * L;
-  w.sing = reinterpret_cast<int*>(w.sums + (size_t)batch * 2 * L * w.nsum);
-  NK_HIP(hipMemsetAsync(w.sing, 0, batch * sizeof(int), st));
+  w.sing = sing;
   const int pb = y.np / 64;
   if (scaling == NK_RH_NONE)
     hipLaunchKernelGGL(k_tri_chain, dim3(pb, 2, batch), dim3(64), 0, st, w, h, nvec, L);

@@ -14,6 +14,8 @@
 // over the whole GPU, instead of k-long sequential solves inside its loop.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "hostbuf.h"
@@ -936,6 +938,14 @@ __global__ void k_col0(int k, const C64* __restrict__ S, C64* __restrict__ z) {
 namespace {
 DevBuf g_small, g_batch;
 HostBuf g_small_pin;  // pinned readback of the inner iteration's flags
+std::mutex g_coef_mu;
+DevBuf g_coef;        // coefficients of small_sign_host, and
+HostBuf g_coef_pin;   // their pinned staging, with the result
+
+__global__ void k_upload(int n, const C64* __restrict__ host, C64* __restrict__ dev) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) dev[i] = host[i];
+}
 }
 
 // workspace of one inner problem of order k with ell steps, carved from base
@@ -1108,6 +1118,32 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
     out->rh_residual = res;
   }
   return e ? e : (brk ? NK_WARN_BREAKDOWN : NK_OK);
+}
+
+// The small problem on host coefficients, on the null stream.  The staging
+// (4 k entries) is kept between calls and the coefficients are read from it by
+// a kernel: an allocation, three copies of pageable memory and one back on
+// every call were 45 of the plain method's 260 us at k = 500.
+int small_sign_host(int k, int ell, int hermitian, const void* alpha, const void* beta, const void* delta,
+                    int rh_scaling, int rh_maxit, double rh_tol, void* z, SmallOut* out, int inner) {
+  std::lock_guard<std::mutex> lock(g_coef_mu);
+  const size_t b = (size_t)k * sizeof(C64);
+  if (g_coef.ensure(3 * b) || g_coef_pin.ensure(4 * b)) return NK_ENOMEM;
+  char* h = g_coef_pin.host<char>();
+  std::memcpy(h, alpha, b);
+  std::memcpy(h + b, beta, b);
+  std::memcpy(h + 2 * b, delta, b);
+  std::memset(h + 3 * b, 0, b);  // a warning without a result (a singular H_k) leaves zeros
+  C64* a = g_coef.as<C64>();
+  hipLaunchKernelGGL(k_upload, dim3((3 * k + 255) / 256), dim3(256), 0, nullptr, 3 * k, g_coef_pin.dev<C64>(), a);
+  const int e = small_sign_dev(k, ell, hermitian, a, a + k, a + 2 * k, rh_scaling, rh_maxit, rh_tol,
+                               g_coef_pin.dev<C64>() + 3 * (size_t)k, out, nullptr, inner);
+  // (also after a failure: nothing may still read the staging when the next call fills it)
+  const hipError_t es = hipStreamSynchronize(nullptr);
+  if (e < 0) return e;
+  NK_HIP(es);
+  std::memcpy(z, h + 3 * b, b);
+  return e;
 }
 
 // The inner projections of r problems at once: one launch per kernel and
