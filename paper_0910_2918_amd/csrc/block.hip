@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "stencil.h"
+#include "wave.h"
 
 namespace nk {
 
@@ -56,18 +57,25 @@ __device__ __forceinline__ C64* vq(const BArgs& a, int s) { return slot(a, s, a.
 __device__ __forceinline__ C64* vx(const BArgs& a, int s) { return slot(a, s, a.ncols + 4); }
 __device__ __forceinline__ C64* vy(const BArgs& a, int s) { return slot(a, s, a.ncols + 5); }
 
+// sums over the workgroup: within the waves, then over them through LDS.  The
+// steps within a wave serve four values at once, without LDS (shuffles, one
+// value at a time, took a fifth of k_blk2: 16.8 us with them, 13.3 without).
 template <int NQ>
 __device__ __forceinline__ void bsum(double (&v)[NQ]) {
+  static_assert(NQ < 3 || NQ % 4 == 0, "one value, two, or fours");
   __shared__ double sh[NQ][BT / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  constexpr int R = NQ < 4 ? 64 / NQ : 16;  // lanes that hold the sum of one value
+  double t[(NQ + 3) / 4];
+  if constexpr (NQ == 1) t[0] = wave_xsum(v[0]);
+  if constexpr (NQ == 2) t[0] = wave_xsum2(v[0], v[1]);
+  if constexpr (NQ >= 4)
 #pragma unroll
-  for (int q = 0; q < NQ; ++q)
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
+    for (int q = 0; q < NQ; q += 4) t[q / 4] = wave_xsum4(v[q], v[q + 1], v[q + 2], v[q + 3]);
   __syncthreads();
-  if (lane == 0)
+  if (lane % R == 0)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) sh[q][w] = v[q];
+    for (int q = 0; q < NQ; q += 4) sh[q + lane / R][w] = t[q / 4];
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < NQ; ++q) v[q] = (sh[q][0] + sh[q][1]) + (sh[q][2] + sh[q][3]);
@@ -167,7 +175,8 @@ __global__ void __launch_bounds__(BT) k_bred2(BArgs a, int j) {
 // Infinity Cache between sources.  The epilogue's operands and the partials
 // are loaded together, before the reduction (the previous vectors after it, one
 // component at a time, took another three round trips).  16 sources on 8^4:
-// 30.4 us and 17 in k_blk2 (29 and 14.7, and 4.8 for each of the two reductions).
+// 27.9 us and 13.3 in k_blk2 (29 and 14.7, and 4.8 for each of the two reductions).
+// The reduction's result computed by one wave for all four: no gain.
 template <int NG>
 __global__ void __launch_bounds__(BT) k_blk1(Geom g, LinksPlain<double> lk, double diag, double eft, double ebt,
                                               int j, BArgs a) {
@@ -328,8 +337,7 @@ __global__ void __launch_bounds__(BT) k_blkS(Geom g, LinksPlain<double> lk, doub
 // y += lc_{j+1} v_hat.  alpha_j = conj(sw_j) sv_j (w~_j^dag A v~_j) is summed by
 // every workgroup from the stencil step's partials, behind its first loads (a
 // launch for that cost 4.8 us a step).
-template <int U>
-__global__ void __launch_bounds__(BT, 4) k_blk2(BArgs a, int j) {
+__global__ void __launch_bounds__(BT, 8) k_blk2(BArgs a, int j) {
   const int s = blockIdx.y;
   if (a.flags[s]) return;
   const C64* p = vp(a, s);
@@ -341,24 +349,19 @@ __global__ void __launch_bounds__(BT, 4) k_blk2(BArgs a, int j) {
   C64* y = vy(a, s);
   const bool lift = a.lc != nullptr && j + 1 < a.kused[s];
   const C64 lcn = lift ? a.lc[(size_t)s * a.k + j + 1] : mk(0.0, 0.0);
-  // U elements per thread and batch, all loads before the first store (U = 1
-  // where the grid covers the vector: registers for eight waves per SIMD)
+  // one entry at a time: eight waves per SIMD hide the loads (the next entry's
+  // loads sent ahead: 4 sources on 16^4 51.1 us, as here 49.3; batches of four
+  // entries spill: 62.2)
   const size_t stride = (size_t)gridDim.x * BT;
-  C64 pp[U], qq[U], vv[U], ww[U];
-  auto load = [&](size_t ib) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t i = ib + u * stride;
-      if (i < a.n) {
-        pp[u] = p[i];
-        qq[u] = q[i];
-        vv[u] = v[i];
-        ww[u] = w[i];
-      }
-    }
+  size_t i = (size_t)blockIdx.x * BT + threadIdx.x;
+  C64 pp, qq, vv, ww;
+  auto load = [&](size_t at) {
+    pp = p[at];
+    qq = q[at];
+    vv = v[at];
+    ww = w[at];
   };
-  size_t i0 = (size_t)blockIdx.x * BT + threadIdx.x;
-  load(i0);
+  if (i < a.n) load(i);
   const double svj = a.sv[(size_t)s * (a.k + 1) + j];
   const C64 swj = a.sw[(size_t)s * (a.k + 1) + j];
   double red[2];
@@ -368,24 +371,18 @@ __global__ void __launch_bounds__(BT, 4) k_blk2(BArgs a, int j) {
   const C64 av = svj * alpha;
   const C64 aw = cmul(conj(alpha), swj);
   double sre = 0.0, sim = 0.0, nv = 0.0, nw = 0.0;
-  for (; i0 < a.n; i0 += U * stride) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t i = i0 + u * stride;
-      if (i < a.n) {
-        const C64 vr = pp[u] - cmul(av, vv[u]);
-        const C64 wr = qq[u] - cmul(aw, ww[u]);
-        vn[i] = vr;
-        wn[i] = wr;
-        const C64 t = cmulc(wr, vr);
-        sre += t.re;
-        sim += t.im;
-        nv += norm2(vr);
-        nw += norm2(wr);
-        if (lift) y[i] = y[i] + cmul(lcn, vr);
-      }
-    }
-    if (i0 + U * stride < a.n) load(i0 + U * stride);
+  for (; i < a.n; i += stride) {
+    const C64 vr = pp - cmul(av, vv);
+    const C64 wr = qq - cmul(aw, ww);
+    vn[i] = vr;
+    wn[i] = wr;
+    const C64 t = cmulc(wr, vr);
+    sre += t.re;
+    sim += t.im;
+    nv += norm2(vr);
+    nw += norm2(wr);
+    if (lift) y[i] = y[i] + cmul(lcn, vr);
+    if (i + stride < a.n) load(i + stride);
   }
   double t4[4] = {sre, sim, nv, nw};
   bsum<4>(t4);
@@ -475,10 +472,7 @@ int sweep(nk_lattice* lat, const BArgs& a, int ng, int grp, double m_w, double m
         if (int r = prof_event(lat, &e)) return r;
     if (grp > 1) hipLaunchKernelGGL(k_bred2, dim3(a.r), dim3(BT), 0, st, a, j);
     launch_blk1(g, lk, ng, grp, m_w, eft, ebt, j, a, ev[0], ev[1], st);
-    if (a.n <= (size_t)a.nb2 * BT)
-      hipExtLaunchKernelGGL(k_blk2<1>, dim3(a.nb2, a.r), dim3(BT), 0, st, ev[2], ev[3], 0, a, j);
-    else
-      hipExtLaunchKernelGGL(k_blk2<4>, dim3(a.nb2, a.r), dim3(BT), 0, st, ev[2], ev[3], 0, a, j);
+    hipExtLaunchKernelGGL(k_blk2, dim3(a.nb2, a.r), dim3(BT), 0, st, ev[2], ev[3], 0, a, j);
     if (timed) {
       lat->evkind.push_back(0);
       lat->evkind.push_back(1);

@@ -35,24 +35,34 @@ __device__ __forceinline__ double wave_sum(double v) {
 // as with shuffles, on DPP and the row swaps instead of LDS permutes.  After a
 // step, lanes l and l ^ o agree, so a rotation within the row of 16 that meets
 // either of them does for the next one.
-__device__ __forceinline__ double pair_sum(double v, bool rows32) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
-  const auto l = rows32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
-                        : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const auto h = rows32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
-                        : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+// (a step on a and b at once: the sums of a in the even, of b in the odd half or rows)
+__device__ __forceinline__ double pair_sum2(double a, double b, bool rows32) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(a);
+  const unsigned long long v = (unsigned long long)__double_as_longlong(b);
+  const auto l = rows32 ? __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)v, false, false)
+                        : __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)v, false, false);
+  const auto h = rows32 ? __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(v >> 32), false, false)
+                        : __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(v >> 32), false, false);
   return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
          __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
 }
-__device__ __forceinline__ double wave_xsum(double v) {
-  v = pair_sum(v, true);
-  v = pair_sum(v, false);
+__device__ __forceinline__ double pair_sum(double v, bool rows32) { return pair_sum2(v, v, rows32); }
+__device__ __forceinline__ double row_xsum(double v) {
   v += dpp_take<0x128, 0xf>(v);  // row_ror:8
   v += dpp_take<0x124, 0xf>(v);  // row_ror:4
   v += dpp_take<0x122, 0xf>(v);  // row_ror:2
   v += dpp_take<0x121, 0xf>(v);  // row_ror:1
   return v;
+}
+__device__ __forceinline__ double wave_xsum(double v) { return row_xsum(pair_sum(pair_sum(v, true), false)); }
+// the same sums of several values at once, in fewer instructions: the first
+// steps leave every value in a part of the wave, the later ones serve all.
+// Of two, lanes 0 to 31 get the first; of four, row q of 16 lanes gets vq.
+__device__ __forceinline__ double wave_xsum2(double v0, double v1) {
+  return row_xsum(pair_sum(pair_sum2(v0, v1, true), false));
+}
+__device__ __forceinline__ double wave_xsum4(double v0, double v1, double v2, double v3) {
+  return row_xsum(pair_sum2(pair_sum2(v0, v2, true), pair_sum2(v1, v3, true), false));
 }
 __device__ __forceinline__ double quad_xsum(double v) {
   v += dpp_take<0xb1, 0xf>(v);  // quad_perm 1, 0, 3, 2
