@@ -25,6 +25,7 @@
 #include <mutex>
 
 #include "nk_internal.h"
+#include "wave.h"
 
 namespace nk {
 
@@ -286,40 +287,42 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(int B, const float* __restrict_
 // gradient with respect to y, scaled by gscale; one workgroup per sample,
 // FP64 arithmetic.  Step t uses mu_t = exp(y_t - mean_i log|z_{i,t}|): the
 // determinant scale of the eigenvalues times the learned correction.
-// SPT eigenvalues per thread: 1 for spectra of up to 256, 4 up to 1024.  Each
-// launch of the pair takes the samples of its own class and returns at once on
-// the others (their sizes are on the device); slots and whole waves past a
+// SPT eigenvalues per thread: 1 for spectra of up to 256, 2 up to 512, in one
+// launch, and 4 up to 1024 in a second one.  Each launch takes the samples of
+// its own class and returns at once on the others (their sizes are on the
+// device); slots and whole waves past a
 // sample's spectrum are branched over.  Bound by FP64 issue: the logarithm,
 // exponential and division of every step and eigenvalue.  So a step divides
 // once, and the backward sweep reuses its 1/w: 1/w^2 = (1/w)^2 and
 // z/|z|^2 = conj(1/z) = mu conj(1/w).  With four slots for every sample, each
 // of them computed, and two more divisions and an exponential per step, as
-// before, 2048 samples of 16 to 300 eigenvalues took 52.6 us; now 23 + 19
-// (7 and 2 workgroups per compute unit at 72 and 200 registers).
+// before, 2048 samples of 16 to 300 eigenvalues took 52.6 us; as two launches
+// of one and of four slots 22 + 19 (the few large samples leave the chip half
+// empty), and now 26 + 4, FP64 issue busy for 16 of them.  Registers: 106 for
+// one and two slots together, 188 for four, which would hold every sample to two
+// workgroups per compute unit.
 
-// sum over the 256 threads of the workgroup, the same value in every thread
-__device__ __forceinline__ double block_sum256(double v, double* sh) {
-  v = wsum(v);
+// sum over the 256 threads of the workgroup, the same value in every thread;
+// on: whether this wave has a value at all.  The calls of a kernel take turns
+// of the two halves of sh, so one barrier a call is enough.
+__device__ __forceinline__ double block_sum256(double v, bool on, double* sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  __syncthreads();
+  if (on) v = wave_xsum(v);
   if (lane == 0) sh[w] = v;
   __syncthreads();
   return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
 template <int SPT>
-__global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, const C64* __restrict__ lam,
-                                                   const float* __restrict__ y, float gscale,
-                                                   float* __restrict__ loss, float* __restrict__ dy) {
-  __shared__ double sh[4];
-  const int b = blockIdx.x;
-  const int i0 = off[b], n = off[b + 1] - off[b];
-  if ((SPT == 1) != (n <= 256)) return;  // the other launch's sample
+__device__ __forceinline__ void spec_loss_of(int b, int i0, int n, const C64* __restrict__ lam,
+                                             const float* __restrict__ y, float gscale, float* __restrict__ loss,
+                                             float* __restrict__ dy, double* sh) {
   if (n <= 0) {  // no eigenvalues: nothing to learn from this sample
     if (threadIdx.x < MT) dy[(size_t)b * MT + threadIdx.x] = 0.f;
     if (threadIdx.x == 0) loss[b] = 0.f;
     return;
   }
+  const bool wave_on = __builtin_amdgcn_readfirstlane(threadIdx.x) < n;
   bool on[SPT];
   C64 z[SPT];                  // z_t of the current step
   C64 w[SPT][MT], iw[SPT][MT];  // w_t = mu_t z_t and 1 / w_t
@@ -338,7 +341,8 @@ __global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, 
 #pragma unroll
     for (int r = 0; r < SPT; ++r)
       if (on[r]) ls += 0.5 * log(norm2(z[r]));
-    mu[t] = exp((double)y[(size_t)b * MT + t] - block_sum256(ls, sh) / n);
+    const double lm = block_sum256(ls, wave_on, sh + 4 * (t & 1)) / n;
+    mu[t] = wave_on ? exp((double)y[(size_t)b * MT + t] - lm) : 1.0;
 #pragma unroll
     for (int r = 0; r < SPT; ++r)
       if (on[r]) {
@@ -355,11 +359,11 @@ __global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, 
       dl[r] = 0.5 * log(e[r] + FLOOR);
       dmax = fmax(dmax, dl[r]);
     }
-  dmax = wmax(dmax);
+  if (wave_on) dmax = wmax(dmax);
+  double* shm = sh + 4 * (MT & 1);
+  if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = dmax;
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = dmax;
-  __syncthreads();
-  const double m = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
+  const double m = fmax(fmax(shm[0], shm[1]), fmax(shm[2], shm[3]));
   double ex[SPT], se = 0.0;
 #pragma unroll
   for (int r = 0; r < SPT; ++r)
@@ -367,7 +371,7 @@ __global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, 
       ex[r] = exp(KAPPA * (dl[r] - m));
       se += ex[r];
     }
-  const double S = block_sum256(se, sh);
+  const double S = block_sum256(se, wave_on, sh + 4 * ((MT + 1) & 1));
   // backward: gradients as complex numbers dRe + i dIm
   C64 gz[SPT];
 #pragma unroll
@@ -384,7 +388,7 @@ __global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, 
         gz[r] = cmulc(mk(0.5 * (1.0 - q.re), -0.5 * q.im), gz[r]);  // conj(f'(w)) gz, through z_{t+1} = (w + 1/w) / 2
         pg += gz[r].re * w[r][t].re + gz[r].im * w[r][t].im;
       }
-    const double glm = block_sum256(pg, sh);  // dL/dlog mu_t = dL/dy_t
+    const double glm = block_sum256(pg, wave_on, sh + 4 * ((MT + 2 + MT - 1 - t) & 1));  // dL/dlog mu_t = dL/dy_t
     g[t] = glm;
     // through w = mu z_t, and through the determinant scale -mean log|z_t|
 #pragma unroll
@@ -396,6 +400,22 @@ __global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, 
 #pragma unroll
     for (int t = 0; t < MT; ++t) dy[(size_t)b * MT + t] = (float)(gscale * g[t]);
   }
+}
+
+template <bool LARGE>
+__global__ void __launch_bounds__(256) k_spec_loss(const int* __restrict__ off, const C64* __restrict__ lam,
+                                                   const float* __restrict__ y, float gscale,
+                                                   float* __restrict__ loss, float* __restrict__ dy) {
+  __shared__ double sh[8];
+  const int b = blockIdx.x;
+  const int i0 = off[b], n = off[b + 1] - off[b];
+  if (LARGE != (n > 512)) return;  // the other launch's sample
+  if constexpr (LARGE)
+    spec_loss_of<4>(b, i0, n, lam, y, gscale, loss, dy, sh);
+  else if (n <= 256)
+    spec_loss_of<1>(b, i0, n, lam, y, gscale, loss, dy, sh);
+  else
+    spec_loss_of<2>(b, i0, n, lam, y, gscale, loss, dy, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -559,8 +579,8 @@ int mlp_forward(int batch, const float* P, const float* feat, float* y, float* a
 int mlp_spectral_loss(int batch, const int* off, const C64* lam, const float* y, float gscale, float* loss,
                       float* dy, hipStream_t st) {
   if (batch <= 0) return NK_OK;
-  hipLaunchKernelGGL(k_spec_loss<1>, dim3(batch), dim3(256), 0, st, off, lam, y, gscale, loss, dy);
-  hipLaunchKernelGGL(k_spec_loss<4>, dim3(batch), dim3(256), 0, st, off, lam, y, gscale, loss, dy);
+  hipLaunchKernelGGL(k_spec_loss<false>, dim3(batch), dim3(256), 0, st, off, lam, y, gscale, loss, dy);
+  hipLaunchKernelGGL(k_spec_loss<true>, dim3(batch), dim3(256), 0, st, off, lam, y, gscale, loss, dy);
   NK_HIP(hipGetLastError());
   return NK_OK;
 }

@@ -45,6 +45,29 @@ def test_mlp_batch_remainders(B, shift):
     assert off(grad.cpu().numpy(), g) < 2e-5
 
 
+def test_spectral_loss_sizes():
+    """Spectra at the edges of the kernel's slots (256, 512 and 1024
+    eigenvalues) and of a wave, and an empty one, in one batch against the
+    oracle.  The arithmetic is FP64 (sums of n terms, conditions below 1e4:
+    1e-10), the results FP32: 6e-8 of each, with a margin."""
+    torch = torch_cuda()
+    b = nk()
+    rng = np.random.default_rng(9)
+    sizes = [1, 64, 65, 255, 256, 257, 0, 320, 511, 512, 513, 1024]
+    lams = [(rng.uniform(0.3, 6.0, n) * rng.choice([-1.0, 1.0], n) + 0.2j * rng.standard_normal(n)) for n in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    y = (0.4 * rng.standard_normal((len(sizes), L.T))).astype(np.float32)
+    banner(f"spectral loss, spectra of {sizes}")
+    loss = torch.full((len(sizes),), 7.0, dtype=torch.float32, device="cuda")
+    dy = torch.full((len(sizes), L.T), 7.0, dtype=torch.float32, device="cuda")
+    b.nk_rh_spectral_loss_device(torch.from_numpy(off).cuda(), torch.from_numpy(np.concatenate(lams)).cuda(),
+                                 torch.from_numpy(y).cuda(), 0.25, loss, dy)
+    for i, lam in enumerate(lams):
+        lr, gr = L.spectral_loss(lam, y[i].astype(np.float64)) if len(lam) else (0.0, np.zeros(L.T))
+        assert abs(loss[i].item() - lr) <= 1e-6 * max(1.0, abs(lr)), sizes[i]
+        assert np.allclose(dy[i].cpu().numpy(), 0.25 * gr, rtol=1e-6, atol=1e-8), sizes[i]
+
+
 @pytest.mark.parametrize("p", [4, 15, 16, 17, 32, 33, 48, 65, 81, 97, 112, 113, 128])
 @pytest.mark.parametrize("mu", [0.0, 0.3])
 def test_eigenpairs_block_sizes(p, mu):
