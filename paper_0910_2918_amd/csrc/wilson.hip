@@ -10,10 +10,9 @@ namespace nk {
 // Directions split over the waves of the workgroup (hop_group); NF lanes per
 // site, lane f on field f.  Bound by the caches: an XCD's 4 MB L2 holds about
 // eight tiles' links and spinors, so the spinors that cross a tile in z and t
-// are fetched again (573 MB read for 318 on 24^4).  The pair's results, which
-// would take a fifth of that L2, are stored past it: 24^4 150 -> 139 us, 16^4
-// 24.3 -> 23.7.
-template <class R, int NF, class LK, int NG>
+// are fetched again (573 MB read for 318 on 24^4).  PAST: results, a fifth of
+// what would share that L2, are stored past it (see apply_pair_dev).
+template <class R, int NF, class LK, int NG, bool PAST = false>
 __global__ void __launch_bounds__(256) k_apply(Geom g, LK lk, R diag, int g5, FieldPtrs<R, NF> in,
                                                 FieldPtrsW<R, NF> out, TFac<R, NF> tf) {
   constexpr int M = 12 / NG;
@@ -49,7 +48,7 @@ __global__ void __launch_bounds__(256) k_apply(Geom g, LK lk, R diag, int g5, Fi
     const size_t i = sidx<R>(g.V, cc, se);
     Cx<R> o = diag * ein[cl] - R(0.5) * hs;
     if (g5 && cc >= 6) o = mk<R>(-o.re, -o.im);
-    if (NF == 2)
+    if (PAST)
       store_nt(&y[i], o);
     else
       y[i] = o;
@@ -254,8 +253,15 @@ int apply_pair_dev(nk_lattice* lat, double m_w, double mu, const C64* v, const C
   FieldPtrsW<double, 2> out{{av, adw}};
   TFac<double, 2> tf{{exp(mu), exp(-mu)}, {exp(-mu), exp(mu)}};
   LinksPlain<double> lk{lat->U64.as<C64>(), g.V};
-  hipLaunchKernelGGL((k_apply<double, 2, LinksPlain<double>, NK_GROUPS>), dim3(apply_blocks(g, 2)), dim3(256), 0,
-                     st, g, lk, 4.0 + m_w, 1, in, out, tf);
+  // Links and fields beyond the 256 MB Infinity Cache: nobody finds the results
+  // there anyway, and stored past the L2 they leave it to the neighbours.  With
+  // the results in the caches and past the L2, read back by the next call:
+  // 160000 sites 57.8, 68.8 us; 221184 86.2, 80.1; 331776 154.9, 150.0 (not read
+  // back: 58.3, 57.4; 83.6, 66.9; 152.5, 143.0).
+  const size_t bytes = ((size_t)4 * 9 + 4 * 12) * g.V * sizeof(C64);
+  auto* const k = bytes > (size_t)256 << 20 ? k_apply<double, 2, LinksPlain<double>, NK_GROUPS, true>
+                                            : k_apply<double, 2, LinksPlain<double>, NK_GROUPS>;
+  hipLaunchKernelGGL(k, dim3(apply_blocks(g, 2)), dim3(256), 0, st, g, lk, 4.0 + m_w, 1, in, out, tf);
   NK_HIP(hipGetLastError());
   return NK_OK;
 }

@@ -292,3 +292,25 @@ def test_spinor_layouts_are_inverse(dims):
     for r in range(2):
         assert torch.equal(torch.sort(xp[r * n:(r + 1) * n].real).values, x[r * n:(r + 1) * n].real)
     lat.close()
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 28, 28), (24, 24, 18, 20)])
+def test_pair_on_both_sides_of_the_cache_size(dims):
+    """The fused pair against two single applications where its links and
+    fields just fill the 256 MB cache (200704 sites are above 199728, 207360
+    further; the smaller lattices of the other tests are below): the same sum of
+    8 x 2 x 3 products per entry, 1e-14."""
+    b = nk()
+    torch = torch_cuda()
+    lat, _ = make_lattice(dims, 0.8, seed=3)
+    n = 12 * int(np.prod(dims))
+    banner(f"pair dims={dims}")
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    v, w = (torch.randn(n, dtype=torch.complex128, device="cuda", generator=gen) for _ in range(2))
+    av, aw, rv, rw = (torch.zeros_like(v) for _ in range(4))
+    b.nk_apply_pair_packed_device(lat.h, M_W, 0.3, v, w, av, aw)
+    b.nk_apply_dw_packed_device(lat.h, M_W, 0.3, True, v, rv)
+    b.nk_apply_dw_packed_device(lat.h, M_W, -0.3, True, w, rw)
+    for got, ref in ((av, rv), (aw, rw)):
+        assert torch.linalg.vector_norm(got - ref) <= 1e-14 * torch.linalg.vector_norm(ref)
+    lat.close()
