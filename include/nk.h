@@ -480,9 +480,9 @@ int nk_stream_device(int32_t kind, int64_t n, const void* a, const void* b, void
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * y = [gamma5] Dw(mu) x as nk_apply_dw_device, bit for bit, on nrhs canonical
- * device vectors, asynchronous on `stream`, with the two layout temporaries
- * (the packed source and the packed result) in a fixed device array of
- * 2 x 12 x NK_NOALLOC_MAX_SITES complex128 (24 MiB) that each device holds
+ * device vectors, asynchronous on `stream`, with the layout temporary that
+ * overlapping x and y need (the packed source) in a fixed device array of
+ * 12 x NK_NOALLOC_MAX_SITES complex128 (12 MiB) that each device holds
  * from its first use until the process ends.  The call allocates and frees
  * nothing.  Lattices of more than NK_NOALLOC_MAX_SITES sites are NK_EINVAL;
  * other errors as nk_apply_dw_device.  Every call on one device shares that
