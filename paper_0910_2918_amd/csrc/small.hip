@@ -500,25 +500,15 @@ __device__ __forceinline__ void bsum_first(double (&v)[4], int nb) {
       for (int q = 0; q < 4; ++q) v[q] += sh[w][q];
 }
 
-// workgroup -> (problem, workgroup of the problem).  A batch of eight or more
-// deals its problems to the eight XCDs (workgroups go round the XCDs in launch
-// order), so that what the workgroups of a problem share, and its B from one
-// step to the next, sits in one L2.
+// problem and workgroup within it: one problem's workgroups after the other,
+// dealt over the XCDs.  (From eight problems on, each kept on one XCD, whose
+// L2 then holds its B: 16 problems of k = 300 17.4 us a mat-vec, as here 15.8;
+// 12 of k = 600 35.6 and 27.2, 32 of k = 600 81 and 72.)
 template <bool BATCH>
-__device__ __forceinline__ void inner_place(int r, int nbmax, int* z, int* x) {
-  if (!BATCH) {
-    *z = 0;
-    *x = blockIdx.x;
-  } else if (r < 8) {
-    *z = blockIdx.x / nbmax;
-    *x = blockIdx.x % nbmax;
-  } else {
-    const int slot = blockIdx.x >> 3;
-    *z = (blockIdx.x & 7) + 8 * (slot / nbmax);
-    *x = slot % nbmax;
-  }
+__device__ __forceinline__ void inner_place(int nbmax, int* z, int* x) {
+  *z = BATCH ? blockIdx.x / nbmax : 0;
+  *x = BATCH ? blockIdx.x % nbmax : blockIdx.x;
 }
-static int inner_grid(int r, int nbmax) { return r < 8 ? r * nbmax : 8 * nbmax * ((r + 7) / 8); }
 
 // Every inner kernel serves a batch of independent problems: problem z is
 // SS[z]; the grid is sized for the largest, and a workgroup beyond its own
@@ -531,19 +521,17 @@ static int inner_grid(int r, int nbmax) { return r < 8 ? r * nbmax : 8 * nbmax *
 // leaves the products in LDS; they are summed over the block's rows in row
 // order, as a single thread summing them would.  The new vector is scaled once
 // per workgroup, into LDS (by every wave for itself it cost as many loads as
-// the matrix): k = 500 6.9 us (8.9), 16 problems of k = 300 18 us (22).  The
+// the matrix): k = 500 6.9 us (8.9), 16 problems of k = 300 15.8 us (22).  The
 // products are rounded in a fixed order, as in the elimination.
 constexpr int XC = 512;  // columns of B staged at a time, eight per lane
 constexpr int GP = 2;  // projection columns per lane loaded at launch (j < 128)
 
 template <bool BATCH>
-__global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner* __restrict__ SS, int nprob,
-                                                     int nbmax, int i) {
+__global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner* __restrict__ SS, int nbmax, int i) {
   extern __shared__ C64 s_p[];  // [GR][i + 1] per-row projection products
   __shared__ C64 s_x[XC];       // v_i (or w_i), a stretch of it
   int z, blk;
-  inner_place<BATCH>(nprob, nbmax, &z, &blk);
-  if (BATCH && z >= nprob) return;
+  inner_place<BATCH>(nbmax, &z, &blk);
   const Inner& S = inner_desc<BATCH>(s0, SS, z);
   const InnerG s = inner_view(S);
   const int side = BATCH ? blk >= s.nb1 : blockIdx.y;  // 0: u = B v, 1: q = B^dag w
@@ -697,11 +685,10 @@ constexpr int ST = 512;
 constexpr int TPJ = 4;  // lanes per (side, column) in the reduction phases
 
 template <bool BATCH>
-__global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __restrict__ SS, int nprob, int nbmax,
+__global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __restrict__ SS, int nbmax,
                                                int i, int last) {
   int z, blk;
-  inner_place<BATCH>(nprob, nbmax, &z, &blk);
-  if (BATCH && z >= nprob) return;
+  inner_place<BATCH>(nbmax, &z, &blk);
   const Inner& S = inner_desc<BATCH>(s0, SS, z);
   const InnerG s = inner_view(S);
   const bool report = blk == 0 && threadIdx.x == 0 && !last && i + 1 >= s.lmax;  // the problem's last launch
@@ -1021,12 +1008,12 @@ static void inner_launch(int r, const Inner& s0, const Inner* SS, int oneside, i
                      s0, SS);
   if (!oneside) hipLaunchKernelGGL(k_adjoint, dim3(kt, kt, r), dim3(32, 8), 0, st, s0, SS);
   const int sides = oneside ? 1 : 2, nb1 = (kmax + GR - 1) / GR, nb2 = (kmax + SR - 1) / SR;
-  const dim3 g1 = BATCH ? dim3(inner_grid(r, sides * nb1)) : dim3(nb1, sides);
-  const dim3 g2 = BATCH ? dim3(inner_grid(r, nb2)) : dim3(nb2);
+  const dim3 g1 = BATCH ? dim3(r * sides * nb1) : dim3(nb1, sides);
+  const dim3 g2 = BATCH ? dim3(r * nb2) : dim3(nb2);
   for (int i = 0; i < lmax; ++i) {
-    hipLaunchKernelGGL(k_in_gemv<BATCH>, g1, dim3(GR * 64), gemv_lds(i), st, s0, SS, r, sides * nb1, i);
-    hipLaunchKernelGGL(k_in_sub<BATCH>, g2, dim3(ST), 0, st, s0, SS, r, nb2, i, 0);
-    if (i + 1 < lmax) hipLaunchKernelGGL(k_in_sub<BATCH>, g2, dim3(ST), 0, st, s0, SS, r, nb2, i, 1);
+    hipLaunchKernelGGL(k_in_gemv<BATCH>, g1, dim3(GR * 64), gemv_lds(i), st, s0, SS, sides * nb1, i);
+    hipLaunchKernelGGL(k_in_sub<BATCH>, g2, dim3(ST), 0, st, s0, SS, nb2, i, 0);
+    if (i + 1 < lmax) hipLaunchKernelGGL(k_in_sub<BATCH>, g2, dim3(ST), 0, st, s0, SS, nb2, i, 1);
   }
 }
 
