@@ -679,9 +679,10 @@ Layout tri_layout(int batch, int ld, int maxn, int L) {
 // further step doubles the poles), nine when scaled (one workgroup's 512
 // threads), never more than the cap; fewer when the workspace would pass
 // 512 MB.  Fewer than five are not worth the detour: 0, and the caller
-// iterates with explicit inverses from the start.
+// iterates with explicit inverses from the start; so it does for a cap below
+// one, under which no step is taken.
 int tri_rh_steps(int batch, int ld, int maxn, int scaling, int maxit) {
-  if (maxn < 1) return 0;
+  if (maxn < 1 || maxit < 1) return 0;
   int L = scaling == NK_RH_NONE && maxn <= 128 ? TLMAX : 9;
   L = std::min(L, maxit);
   while (L > 0 && tri_layout(batch, ld, maxn, L).bytes > (size_t)512 << 20) --L;
