@@ -1097,8 +1097,10 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
   }
   // the steps of a tridiagonal start matrix in closed form, with Eq. (4)'s
   // stopping test on every step; what has not converged by then goes on below
-  // from there (step it0 + 1)
+  // from there (step it0 + 1).  A matrix that the closed form does not cover
+  // starts below from S_0, and so then do the others that have not converged.
   int it0 = 0;
+  bool any_done = false;
   std::vector<int> done(batch, 0), state(batch, 0);
   std::vector<double> change0(batch, INFINITY);
   if (const int L = tri ? tri_rh_steps(batch, ld, maxn, scaling, maxit) : 0) {
@@ -1112,7 +1114,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
         NK_HIP(hipStreamSynchronize(st));
       }
       it0 = L;
-      bool all = true;
+      bool all = true, redo = false;
       for (int b = 0; b < batch; ++b) {
         const double* v = sums + (size_t)b * (2 * L + 1);
         iters_host[b] = 0;
@@ -1120,33 +1122,44 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
           done[b] = 1;
           continue;
         }
+        bool covered = v[2 * L] == 0.0;
+        for (int m = 0; m < L; ++m) covered = covered && std::isfinite(v[2 * m] / v[2 * m + 1]);
+        if (!covered) {
+          redo = true;
+          continue;
+        }
         double prev = INFINITY;
         for (int m = 0; m < L && !done[b]; ++m) {
           const double change = std::sqrt(v[2 * m] / v[2 * m + 1]);
           iters_host[b] = m + 1;
           if (!(change > tol) || (change < 1e-6 && change > 0.5 * prev)) done[b] = 1;
-          if (!std::isfinite(change)) state[b] = 1;
           prev = change;
         }
         change0[b] = prev;
-        if (v[2 * L] != 0.0) {
-          state[b] = 1;
-          done[b] = 1;
-        }
         if (!done[b] && L >= maxit) {
           state[b] = 2;  // the cap ended the iteration before the stopping test held
           done[b] = 1;
         }
         all = all && done[b];
       }
-      if (all) return rh_outcome(batch, state.data(), maxit);
+      if (redo) {
+        it0 = 0;
+        std::fill(change0.begin(), change0.end(), INFINITY);
+        for (int b = 0; b < batch; ++b) pin_gj[b] = !done[b];
+        NK_HIP(hipMemcpyAsync(rowof, pin_gj, batch * sizeof(int), hipMemcpyHostToDevice, st));
+        if (int e2 = tri_rh_restart(batch, ld, nvec, rowof, *tri, S, st)) return e2;
+        NK_HIP(hipStreamSynchronize(st));  // (the staging and the flags' slot are free again)
+      } else if (all) {
+        return rh_outcome(batch, state.data(), maxit);
+      }
+      for (int b = 0; b < batch; ++b) any_done = any_done || done[b];
     }
   }
   if (maxn <= SMAX) {
     NK_HIP(hipMemcpyAsync(sing, pin_zero, batch * sizeof(int), hipMemcpyHostToDevice, st));
     const int* start = nullptr;
     const double* prev0 = nullptr;
-    if (it0 > 0) {  // in the slots of the large path's flags and stopping sums
+    if (it0 > 0 || any_done) {  // in the slots of the large path's flags and stopping sums
       double* ph = const_cast<double*>(sums_h);
       for (int b = 0; b < batch; ++b) {
         pin_gj[b] = done[b] ? -1 : it0;
@@ -1195,7 +1208,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
   for (int b = 0; b < batch; ++b) {
     maxn = std::max(maxn, n_host[b]);
     act_h[b] = n_host[b] > 0 && !done[b] ? 1 : 0;
-    if (it0 == 0) iters_host[b] = 0;
+    if (it0 == 0 && !done[b]) iters_host[b] = 0;
   }
   std::copy(act_h.begin(), act_h.end(), pin_act0);
   NK_HIP(hipMemcpyAsync(act, pin_act0, batch * sizeof(int), hipMemcpyHostToDevice, st));

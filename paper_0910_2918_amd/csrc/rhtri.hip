@@ -27,8 +27,7 @@
 //   (M^{-1})_ij = (M^{-1})_{i+1,j} u_i,  u_i = -b_i / D_i      for i < j,
 //   (M^{-1})_ij = (M^{-1})_{i-1,j} l_i,  l_i = -d_{i-1} / E_i  for i > j
 // (b, d the super- and sub-diagonal).  An exactly zero pivot is replaced by
-// 1e-30 of the matrix's size (the matrix is singular, and reported so, only
-// when the last pivot vanishes).  Between two different blocks of 16 rows the
+// 1e-30 of the matrix's size.  Between two different blocks of 16 rows the
 // inverse therefore has rank one per pole: for a block of rows c before the
 // block of columns C,
 //   rho (M^{-1})_ij = [u_i .. u_end(c)] [all u of the blocks between] [rho / g_j u_start(C) .. u_{j-1}],
@@ -40,6 +39,17 @@
 // Against the oracle the result is as accurate as the iteration with explicit
 // inverses or more (k = 300, condition 1.4e4: 1.2e-13 from the spectral sign
 // against 4.2e-13).
+//
+// Where it does not apply, a matrix is flagged and goes back to the iteration
+// with explicit inverses from S_0: when a last pivot vanishes (an iterate is
+// singular), when a row is more than 2^50 below the largest entry (a pivot
+// below 1e-30 could then be the true one), or when the minors leave 2^-900
+// within a block of rows (the next one could underflow).  Entries of up to
+// 2^50 of their neighbours are taken: the reciprocals are formed of operands
+// scaled by a power of two, since the minors of small rows fall by that factor
+// row after row (order 64, diagonal +-2 with one entry of 1e12: 2e-16 of S_9 e_1
+// from the explicit inverses; squares of unscaled minors underflowed from
+// 1e10 on).
 //
 // Kernels, over a batch (grid z):
 //   k_tri_chain (k_tri_chain_mu when scaled): the minors, one lane per pole and
@@ -65,20 +75,29 @@ namespace {
 
 constexpr int TB = 16;  // rows of a block, and poles of a step on the matrix cores
 constexpr double TINYPIV = 1e-30, SINGPIV = 1e-28;
+constexpr double ROWLOW = 0x1p-50;  // rows below this part of the matrix's largest entry: flagged
+constexpr int MINLOW = -900;        // exponent of the minors of a block below which: flagged
 
 typedef double nk_d4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double abs1(C64 a) { return fabs(a.re) + fabs(a.im); }
 
-// 1 / a: one reciprocal with two Newton steps (the operands here are matrix
-// entries and pivots, far from the ends of the exponent range)
-__device__ __forceinline__ C64 recip(C64 a, double* n2) {
-  const double n = fma(a.im, a.im, a.re * a.re);
+// the exponent of a's larger component (2^e is above it)
+__device__ __forceinline__ int expo(C64 a) {
+  int e;
+  (void)frexp(fmax(fabs(a.re), fabs(a.im)), &e);
+  return e;
+}
+// 1 / a: one reciprocal with two Newton steps, of |a|^2 scaled by a power of
+// two (exact), so that minors anywhere in the exponent range will do
+__device__ __forceinline__ C64 recip(C64 a) {
+  const int e = expo(a);
+  const double re = ldexp(a.re, -e), im = ldexp(a.im, -e);
+  const double n = fma(im, im, re * re);
   double y = __builtin_amdgcn_rcp(n);
   y = fma(y, fma(-n, y, 1.0), y);
   y = fma(y, fma(-n, y, 1.0), y);
-  *n2 = n;
-  return mk(a.re * y, -a.im * y);
+  return mk(ldexp(re * y, -e), ldexp(-im * y, -e));
 }
 
 // the zero with index q = 2^n + j of S_n and its residue (mu == nullptr: unscaled)
@@ -141,24 +160,33 @@ struct Rows {
 // Bound by the latency of its k dependent steps (two dependent products each;
 // carrying the pivots themselves, with a reciprocal per step, took 158 ns a
 // step, this 74 ns at k = 500).  A minor may vanish: the recurrence does not divide.
-// DIR 0 flags a vanishing last pivot and (LD) leaves log|det(H - i t)| in *ld.
+// DIR 0 flags what the closed form does not cover (see above) and (LD) leaves
+// log|det(H - i t)| in *ld; with rows, its rows are looked at too (one wave's
+// work for the whole matrix).
 template <bool LD, int DIR>
 __device__ __forceinline__ void chain(const TriWs& w, const TriIn& h, int b, int n, int q, double t, Rows& sh,
-                                      double* ld) {
+                                      double* ld, bool rows = false) {
   const C64* a = h.a + b * h.stride;
   const C64* be = h.b + b * h.stride;
   const C64* de = h.d + b * h.stride;
   const int lane = threadIdx.x & 63;
   const int nblk = (n + TB - 1) / TB, nld = (n + 63) / 64;
-  double sc = 0.0;  // the matrix's largest entry
+  double sc = 0.0, low = INFINITY;  // the matrix's largest entry, and the least over the rows of a row's largest
 #pragma unroll 8
   for (int k = 0; k < nld; ++k) {
-    const int i = min(64 * k + lane, n - 1), j = min(i, max(n - 2, 0));
-    const double so = n > 1 ? fmax(abs1(be[j]), abs1(de[j])) : 0.0;
-    sc = fmax(sc, fmax(abs1(a[i]), so));
+    const int i = min(64 * k + lane, n - 1), j = min(i, max(n - 2, 0)), j1 = max(i - 1, 0);
+    const double sb = n > 1 ? abs1(be[j]) : 0.0, sd = n > 1 ? abs1(de[j]) : 0.0, sa = abs1(a[i]);
+    sc = fmax(sc, fmax(sa, fmax(sb, sd)));
+    if (DIR == 0 && rows) {
+      const double s1 = i > 0 ? abs1(de[j1]) : 0.0;
+      low = fmin(low, fmax(sa, fmax(i + 1 < n ? sb : 0.0, s1)));
+    }
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sc = fmax(sc, __shfl_xor(sc, o, 64));
+  for (int o = 32; o > 0; o >>= 1) {
+    sc = fmax(sc, __shfl_xor(sc, o, 64));
+    if (DIR == 0 && rows) low = fmin(low, __shfl_xor(low, o, 64));
+  }
   int ke;
   (void)frexp(sc + fabs(t), &ke);
   const double kap = ldexp(1.0, -ke), kap2 = kap * kap, kt = kap * t;
@@ -175,7 +203,7 @@ __device__ __forceinline__ void chain(const TriWs& w, const TriIn& h, int b, int
   };
   fetch(DIR == 0 ? 0 : nld - 1);
   C64 x = mk(1.0, 0.0), y = mk(0.0, 0.0);  // the minor before this row, and the one before that
-  int ex = 0;
+  int ex = 0, least = 0;
   C64* out = DIR == 0 ? w.N : w.M;
   for (int kk = 0; kk < nld; ++kk) {
     const int k = DIR == 0 ? kk : nld - 1 - kk;
@@ -191,6 +219,7 @@ __device__ __forceinline__ void chain(const TriWs& w, const TriIn& h, int b, int
       // the pair's power of two
       int e;
       (void)frexp(fmax(fmax(fabs(x.re), fabs(x.im)), fmax(fabs(y.re), fabs(y.im))), &e);
+      least = min(least, e);
       x = mk(ldexp(x.re, -e), ldexp(x.im, -e));
       y = mk(ldexp(y.re, -e), ldexp(y.im, -e));
       if (LD) ex += e;
@@ -215,8 +244,14 @@ __device__ __forceinline__ void chain(const TriWs& w, const TriIn& h, int b, int
       }
     }
   }
-  if (DIR == 0 && q > 0 && !(abs1(x) > SINGPIV * abs1(y))) w.sing[b] = 1;
-  if (LD) *ld = abs1(x) > 0.0 ? 0.5 * log(norm2(x)) + (ex + (double)n * ke) * 0.69314718055994530942 : -1e300;
+  least = min(least, max(expo(x), expo(y)));
+  if (q > 0 && least < MINLOW) w.sing[b] = 1;
+  if (DIR == 0 && q > 0 && !(abs1(x) > SINGPIV * abs1(y) && low >= ROWLOW * sc)) w.sing[b] = 1;
+  if (LD) {
+    const int e = expo(x);
+    const C64 s = mk(ldexp(x.re, -e), ldexp(x.im, -e));
+    *ld = abs1(x) > 0.0 ? 0.5 * log(norm2(s)) + (ex + e + (double)n * ke) * 0.69314718055994530942 : -1e300;
+  }
 }
 
 // unscaled: every pole's zero is known beforehand; one wave per 64 poles and direction
@@ -231,7 +266,7 @@ __global__ void __launch_bounds__(64) k_tri_chain(TriWs w, TriIn h, const int* _
   zero_of(q, nullptr, &t, &rho);
   if (blockIdx.y == 0) w.rho[(size_t)b * w.np + q] = q < (1 << L) ? rho : 0.0;
   if (blockIdx.y == 0)
-    chain<false, 0>(w, h, b, n, q, t, sh, nullptr);
+    chain<false, 0>(w, h, b, n, q, t, sh, nullptr, blockIdx.x == 0);
   else
     chain<false, 1>(w, h, b, n, q, t, sh, nullptr);
 }
@@ -259,7 +294,7 @@ __global__ void __launch_bounds__(512) k_tri_chain_mu(TriWs w, TriIn h, const in
       zero_of(q, s_mu, &t, &rho);
       if (dir == 0) w.rho[(size_t)b * w.np + q] = rho;
       if (dir == 0)
-        chain<true, 0>(w, h, b, n, q, t, sh[wv], &ld);
+        chain<true, 0>(w, h, b, n, q, t, sh[wv], &ld, s == 0);
       else
         chain<false, 1>(w, h, b, n, q, t, sh[wv], nullptr);
       if (dir == 0 && live) v = ld;
@@ -300,8 +335,7 @@ __global__ void __launch_bounds__(512) k_tri_chain_mu(TriWs w, TriIn h, const in
 }
 
 __device__ __forceinline__ C64 quot(C64 a, C64 b) {
-  double n2;
-  return cmul(a, recip(b, &n2));
+  return cmul(a, recip(b));
 }
 // rho / g and the products within a block of 16 rows: a lane per pole, a wave
 // per block and direction (y = 2 block + direction); every load is known at
@@ -364,8 +398,7 @@ __global__ void __launch_bounds__(64) k_tri_mid(TriWs w, TriIn h, const int* __r
         const C64 bj = be[j + 1 < n ? j : 0];
         C64 gj = D;
         if (j + 1 < n) gj = gj + cmul(mk(kap * bj.re, kap * bj.im), ln);
-        double n2;
-        const C64 r = recip(gj, &n2);
+        const C64 r = recip(gj);
         const double f0 = rho * kap;
         g[k] = mk(rho != 0.0 ? f0 * r.re : 0.0, rho != 0.0 ? f0 * r.im : 0.0);  // (rho = 0: padding)
         const C64 dj = de[j > 0 ? j - 1 : 0];
@@ -638,7 +671,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 4) k_tri_tile(TriWs w, 
 }
 
 // the sums over the tiles, in a fixed order, into host memory: per matrix 2 L
-// sums (one wave each), then 1.0 if a zero pivot ended an elimination
+// sums (one wave each), then 1.0 if the closed form does not cover the matrix
 __global__ void __launch_bounds__(64) k_tri_sums(TriWs w, double* host) {
   const int b = blockIdx.y, m = blockIdx.x, n2 = gridDim.x;
   const double* p = w.sums + ((size_t)b * n2 + m) * w.nsum;
@@ -734,6 +767,28 @@ int tri_rh_run(int batch, int ld, int maxn, const int* nvec, int* sing, const Tr
   hipLaunchKernelGGL(k_tri_sums, dim3(2 * L, batch), dim3(64), 0, st, w, g_tri_pin.dev<double>());
   NK_HIP(hipGetLastError());
   *sums = g_tri_pin.host<double>();
+  return NK_OK;
+}
+
+__global__ void __launch_bounds__(256) k_tri_restart(int ld, const int* __restrict__ nvec,
+                                                     const int* __restrict__ redo, TriIn h, C64* __restrict__ S_b) {
+  const int b = blockIdx.y, n = nvec[b];
+  if (!redo[b]) return;
+  C64* S = S_b + (size_t)b * ld * ld;
+  const size_t nn = (size_t)max(n, 0) * n;
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < nn; e += (size_t)gridDim.x * 256) {
+    const int i = (int)(e / n), j = (int)(e % n);
+    C64 v = mk(0.0, 0.0);
+    if (i == j) v = h.a[b * h.stride + i];
+    if (j == i + 1) v = h.b[b * h.stride + i];
+    if (i == j + 1) v = h.d[b * h.stride + j];
+    S[(size_t)i * ld + j] = v;
+  }
+}
+
+int tri_rh_restart(int batch, int ld, const int* nvec, const int* redo, const TriIn& h, C64* S, hipStream_t st) {
+  hipLaunchKernelGGL(k_tri_restart, dim3(64, batch), dim3(256), 0, st, ld, nvec, redo, h, S);
+  NK_HIP(hipGetLastError());
   return NK_OK;
 }
 

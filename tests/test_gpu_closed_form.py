@@ -39,3 +39,58 @@ def test_cap_below_one_takes_no_step(n, ell, maxit):
             assert np.array_equal(z, T[:, 0])
         else:
             assert np.linalg.norm(z - (T + np.linalg.inv(T))[:, 0]) < 1e-12
+
+
+def _graded(kind, n, r):
+    """The intervals above with one diagonal entry of r, one coupled pair of r,
+    a coupling of r one way and 1 / r the other, or the lower half divided by r."""
+    a, b, d = _intervals(n, 7)
+    j = n // 3
+    if kind == "diagonal":
+        a[j] = r
+    elif kind == "pair":
+        b[j] = d[j] = r
+    elif kind == "one side":
+        b[j], d[j] = r, 1.0 / r
+    else:
+        a[n // 2:] /= r
+        b[n // 2 - 1:] /= r
+        d[n // 2 - 1:] /= r
+    return a, b, d
+
+
+@pytest.mark.parametrize("n", [6, 40, 128, 130])
+@pytest.mark.parametrize("kind", ["diagonal", "pair", "one side", "rows"])
+def test_badly_scaled_entries(kind, n):
+    """Entries of 1e8 to 1e22 times their neighbours: up to 2^50 (1e15) in
+    closed form, beyond it with explicit inverses.  The oracle's iteration is
+    within 6e-16 of the same one in long double on these matrices; the
+    tolerance of the capped iterates, 1e-11, is kept."""
+    from oracle import rh as R
+    b = nk()
+    for r in (1e8, 7e9, 1e10, 1e12, 1e15, 1e17, 1e22):
+        a, be, de = _graded(kind, n, r)
+        T = _dense(a, be, de)
+        for scaling, scale in ((b.NK_RH_NONE, None), (b.NK_RH_DET, R.determinant_scale)):
+            S, it, _ = R.roberts_higham(T, maxit=200, scale=scale)
+            banner(f"{kind} {r:g} n={n} scaling={scaling}")
+            p = b.nk_sign_params_default(rh_scaling=scaling, rh_maxit=200)
+            z, info, rc = b.nk_small_sign(n, 0, kind != "one side", a, be, de, p)
+            assert rc == 0 and abs(info.rh_iters - it) <= 2, (r, scaling, info.rh_iters, it, rc)
+            assert np.linalg.norm(z - S[:, 0]) <= 1e-11 * np.linalg.norm(S[:, 0]), (r, scaling)
+
+
+@pytest.mark.parametrize("n,ell", [(40, 20), (130, 60)])
+@pytest.mark.parametrize("r", [1e10, 1e12, 1e14])
+def test_badly_scaled_inner_problem(n, ell, r):
+    """Nested, with an entry of r in H_k and so in H_l (its off-diagonals then
+    spread from 1 / r to r; the inner recurrence amplifies rounding by as much, so
+    the entries of z are not determined): sgn(H_l) is unitary and V_l has
+    orthonormal columns, |z| = 1 to the 1e-13 that the spread leaves of it, held to 1e-10."""
+    b = nk()
+    a, be, de = _graded("diagonal", n, r)
+    banner(f"nested {n}/{ell} with an entry of {r:g}")
+    for scaling in (b.NK_RH_NONE, b.NK_RH_DET):
+        z, info, rc = b.nk_small_sign(n, ell, True, a, be, de, b.nk_sign_params_default(rh_scaling=scaling))
+        assert rc == 0 and info.ell_used == ell
+        assert abs(np.linalg.norm(z) - 1.0) < 1e-10
