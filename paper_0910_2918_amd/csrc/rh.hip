@@ -1114,10 +1114,10 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
         NK_HIP(hipStreamSynchronize(st));
       }
       it0 = L;
-      bool all = true, redo = false;
+      bool all = true, redo = false, retake = false;
       for (int b = 0; b < batch; ++b) {
         const double* v = sums + (size_t)b * (2 * L + 1);
-        iters_host[b] = 0;
+        iters_host[b] = pin_gj[b] = 0;
         if (n_host[b] <= 0) {
           done[b] = 1;
           continue;
@@ -1134,6 +1134,13 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
           iters_host[b] = m + 1;
           if (!(change > tol) || (change < 1e-6 && change > 0.5 * prev)) done[b] = 1;
           prev = change;
+          // A loose tolerance ends on an iterate that S_L has left behind.  Below
+          // 1e-9 the next changes are of its square, and S_L is that iterate to
+          // rounding (no tolerance up to 1e-9 comes here).
+          if (done[b] && m + 1 < L && !(change > tol) && change > 1e-9) {
+            pin_gj[b] = m + 1;
+            retake = true;
+          }
         }
         change0[b] = prev;
         if (!done[b] && L >= maxit) {
@@ -1145,13 +1152,19 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
       if (redo) {
         it0 = 0;
         std::fill(change0.begin(), change0.end(), INFINITY);
-        for (int b = 0; b < batch; ++b) pin_gj[b] = !done[b];
-        NK_HIP(hipMemcpyAsync(rowof, pin_gj, batch * sizeof(int), hipMemcpyHostToDevice, st));
-        if (int e2 = tri_rh_restart(batch, ld, nvec, rowof, *tri, S, st)) return e2;
-        NK_HIP(hipStreamSynchronize(st));  // (the staging and the flags' slot are free again)
-      } else if (all) {
-        return rh_outcome(batch, state.data(), maxit);
+        for (int b = 0; b < batch; ++b)
+          if (!done[b]) pin_gj[b] = -1;
       }
+      if (redo || retake) {
+        NK_HIP(hipMemcpyAsync(rowof, pin_gj, batch * sizeof(int), hipMemcpyHostToDevice, st));
+        if (int e2 = tri_rh_retake(batch, ld, maxn, nvec, rowof, *tri, S, L, st)) return e2;
+        if (resid_host && !redo && all) {
+          if (int e2 = rh_residuals(batch, maxn, ld, nvec, ones, S, resid_host, st)) return e2;
+        } else {
+          NK_HIP(hipStreamSynchronize(st));  // (the staging and the flags' slot are free again)
+        }
+      }
+      if (!redo && all) return rh_outcome(batch, state.data(), maxit);
       for (int b = 0; b < batch; ++b) any_done = any_done || done[b];
     }
   }

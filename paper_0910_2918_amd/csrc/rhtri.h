@@ -14,12 +14,14 @@ int tri_rh_steps(int batch, int ld, int maxn, int scaling, int maxit);
 // memory, valid once the stream has been waited for): per matrix the pairs
 // |S_{n+1} - mu_n S_n|^2, |S_{n+1}|^2 of the L steps, then nonzero if the
 // closed form does not cover the matrix (rhtri.hip); neither S nor the sums
-// then mean anything, and tri_rh_restart puts S_0 back.  Returns 1, with S
+// then mean anything, and tri_rh_retake puts S_0 back.  Returns 1, with S
 // unchanged, when there is no memory for the workspace.
 int tri_rh_run(int batch, int ld, int maxn, const int* nvec, int* sing, const TriIn& h, C64* S, int scaling,
                const double* sched, int nsched, int L, const double** sums, hipStream_t st);
 
-// S <- S_0 = H, from its diagonals, for the matrices with redo[b] != 0
-int tri_rh_restart(int batch, int ld, const int* nvec, const int* redo, const TriIn& h, C64* S, hipStream_t st);
+// After tri_rh_run with the same batch and L: S <- S_m, m = steps[b] (device
+// array) where it is positive, S_0 where it is negative, unchanged where zero.
+int tri_rh_retake(int batch, int ld, int maxn, const int* nvec, const int* steps, const TriIn& h, C64* S, int L,
+                  hipStream_t st);
 
 }  // namespace nk

@@ -513,13 +513,16 @@ __global__ void __launch_bounds__(64) k_tri_between(TriWs w, const int* __restri
 // matrix cores' FP64 rate and the loads of the factors from L2; nothing of an
 // inverse goes through memory (kept as partial sums per 16 poles, in an
 // earlier form, they were 140 MB written and read at k = 500, 140 + 37 us).
+// steps, if given: the steps of each matrix (at most Lw), none where it is not positive.
 constexpr int TLMAX = 10;
 constexpr int TPARTS = 9;  // parts of a diagonal tile: halves of 16, 8, 4, 2 rows above, then below, then the diagonal
 template <int NW>
-__global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 4) k_tri_tile(TriWs w, const int* __restrict__ nvec, int L, C64* S_b) {
+__global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 4) k_tri_tile(TriWs w, const int* __restrict__ nvec, int Lw,
+                                                                          const int* __restrict__ steps, C64* S_b) {
   __shared__ C64 red[2 * NW][TB][TB + 1];  // partial tiles: of the first six steps, later two sets, one per wave
   __shared__ double sred[4][2 * TLMAX];
-  const int b = blockIdx.z, n = nvec[b];
+  const int b = blockIdx.z, n = nvec[b], L = steps ? steps[b] : Lw;
+  if (L <= 0) return;
   // workgroups: the parts of the diagonal tiles, then the other tiles row by row
   const int nd = w.nch * TPARTS;
   int c, C, part = -1;
@@ -561,7 +564,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 4) k_tri_tile(TriWs w, 
   if (c * TB < n && C * TB < n) {
     const size_t so = (size_t)b * w.ld * w.ld + (size_t)(own ? c * TB + er : 0) * w.ld + (own ? C * TB + ec : 0);
     C64 s = S_b[so];
-    const double* mu = w.mu + (size_t)b * L;
+    const double* mu = w.mu + (size_t)b * Lw;
     // this lane's row of the left and column of the right factor
     A += (size_t)b * w.np * ldp + c * TB + l16;
     B += (size_t)b * w.np * ldp + C * TB + l16;
@@ -666,7 +669,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 4) k_tri_tile(TriWs w, 
   }
   __syncthreads();
   if (threadIdx.x < 2 * L)
-    w.sums[((size_t)b * 2 * L + threadIdx.x) * w.nsum + blockIdx.x] =
+    w.sums[((size_t)b * 2 * Lw + threadIdx.x) * w.nsum + blockIdx.x] =
         (sred[0][threadIdx.x] + sred[1][threadIdx.x]) + (sred[2][threadIdx.x] + sred[3][threadIdx.x]);
 }
 
@@ -705,27 +708,8 @@ Layout tri_layout(int batch, int ld, int maxn, int L) {
   return y;
 }
 
-}  // namespace
-
-// The steps to take in closed form: ten for orders up to 128 and nine above
-// (a spectrum between 0.3 and 6.5 in modulus converges in eight or nine; each
-// further step doubles the poles), nine when scaled (one workgroup's 512
-// threads), never more than the cap; fewer when the workspace would pass
-// 512 MB.  Fewer than five are not worth the detour: 0, and the caller
-// iterates with explicit inverses from the start; so it does for a cap below
-// one, under which no step is taken.
-int tri_rh_steps(int batch, int ld, int maxn, int scaling, int maxit) {
-  if (maxn < 1 || maxit < 1) return 0;
-  int L = scaling == NK_RH_NONE && maxn <= 128 ? TLMAX : 9;
-  L = std::min(L, maxit);
-  while (L > 0 && tri_layout(batch, ld, maxn, L).bytes > (size_t)512 << 20) --L;
-  return L >= std::min(5, maxit) ? L : 0;
-}
-
-int tri_rh_run(int batch, int ld, int maxn, const int* nvec, int* sing, const TriIn& h, C64* S, int scaling,
-               const double* sched, int nsched, int L, const double** sums, hipStream_t st) {
-  const Layout y = tri_layout(batch, ld, maxn, L);
-  if (g_tri.ensure(y.bytes) || g_tri_pin.ensure((size_t)batch * (2 * L + 1) * sizeof(double))) return 1;
+// the workspace of that layout, in g_tri
+TriWs tri_ws(const Layout& y, int batch, int ld, int L, int* sing) {
   TriWs w{};
   w.ld = ld;
   w.np = y.np;
@@ -748,6 +732,43 @@ int tri_rh_run(int batch, int ld, int maxn, const int* nvec, int* sing, const Tr
   w.mu = w.kap + (size_t)batch * y.np;
   w.sums = w.mu + (size_t)batch * L;
   w.sing = sing;
+  return w;
+}
+
+// S_0 -> S_1 .. of every tile.  At most one workgroup per CU: sixteen waves for
+// a tile, a step's poles in a quarter of the turns.  More workgroups fill the
+// chip themselves, three of four waves to a CU.  Sixteen waves against four:
+// n = 60 (48 workgroups) 27 and 38 us, n = 190 (240) 21 and 26, n = 230 (345)
+// 34 and 28, n = 500 (1280) 94 and 54.
+void tri_tiles(const TriWs& w, int batch, const int* nvec, int L, const int* steps, C64* S, hipStream_t st) {
+  if (w.nsum * batch <= 256)
+    hipLaunchKernelGGL(k_tri_tile<16>, dim3(w.nsum, 1, batch), dim3(1024), 0, st, w, nvec, L, steps, S);
+  else
+    hipLaunchKernelGGL(k_tri_tile<4>, dim3(w.nsum, 1, batch), dim3(256), 0, st, w, nvec, L, steps, S);
+}
+
+}  // namespace
+
+// The steps to take in closed form: ten for orders up to 128 and nine above
+// (a spectrum between 0.3 and 6.5 in modulus converges in eight or nine; each
+// further step doubles the poles), nine when scaled (one workgroup's 512
+// threads), never more than the cap; fewer when the workspace would pass
+// 512 MB.  Fewer than five are not worth the detour: 0, and the caller
+// iterates with explicit inverses from the start; so it does for a cap below
+// one, under which no step is taken.
+int tri_rh_steps(int batch, int ld, int maxn, int scaling, int maxit) {
+  if (maxn < 1 || maxit < 1) return 0;
+  int L = scaling == NK_RH_NONE && maxn <= 128 ? TLMAX : 9;
+  L = std::min(L, maxit);
+  while (L > 0 && tri_layout(batch, ld, maxn, L).bytes > (size_t)512 << 20) --L;
+  return L >= std::min(5, maxit) ? L : 0;
+}
+
+int tri_rh_run(int batch, int ld, int maxn, const int* nvec, int* sing, const TriIn& h, C64* S, int scaling,
+               const double* sched, int nsched, int L, const double** sums, hipStream_t st) {
+  const Layout y = tri_layout(batch, ld, maxn, L);
+  if (g_tri.ensure(y.bytes) || g_tri_pin.ensure((size_t)batch * (2 * L + 1) * sizeof(double))) return 1;
+  const TriWs w = tri_ws(y, batch, ld, L, sing);
   const int pb = y.np / 64;
   if (scaling == NK_RH_NONE)
     hipLaunchKernelGGL(k_tri_chain, dim3(pb, 2, batch), dim3(64), 0, st, w, h, nvec, L);
@@ -755,15 +776,7 @@ int tri_rh_run(int batch, int ld, int maxn, const int* nvec, int* sing, const Tr
     hipLaunchKernelGGL(k_tri_chain_mu, dim3(1, 1, batch), dim3(512), 0, st, w, h, nvec, L, sched, nsched);
   hipLaunchKernelGGL(k_tri_mid, dim3(pb, 2 * y.nch, batch), dim3(64), 0, st, w, h, nvec);
   if (y.nch > 1) hipLaunchKernelGGL(k_tri_between, dim3(pb, 2 * y.nch, batch), dim3(64), 0, st, w, nvec);
-  // At most one workgroup per CU: sixteen waves for a tile, a step's poles in a
-  // quarter of the turns.  More workgroups fill the chip themselves, three of
-  // four waves to a CU.  Sixteen waves against four: n = 60 (48 workgroups)
-  // 27 and 38 us, n = 190 (240) 21 and 26, n = 230 (345) 34 and 28, n = 500
-  // (1280) 94 and 54.
-  if (y.ntask * batch <= 256)
-    hipLaunchKernelGGL(k_tri_tile<16>, dim3(y.ntask, 1, batch), dim3(1024), 0, st, w, nvec, L, S);
-  else
-    hipLaunchKernelGGL(k_tri_tile<4>, dim3(y.ntask, 1, batch), dim3(256), 0, st, w, nvec, L, S);
+  tri_tiles(w, batch, nvec, L, nullptr, S, st);
   hipLaunchKernelGGL(k_tri_sums, dim3(2 * L, batch), dim3(64), 0, st, w, g_tri_pin.dev<double>());
   NK_HIP(hipGetLastError());
   *sums = g_tri_pin.host<double>();
@@ -786,8 +799,10 @@ __global__ void __launch_bounds__(256) k_tri_restart(int ld, const int* __restri
   }
 }
 
-int tri_rh_restart(int batch, int ld, const int* nvec, const int* redo, const TriIn& h, C64* S, hipStream_t st) {
-  hipLaunchKernelGGL(k_tri_restart, dim3(64, batch), dim3(256), 0, st, ld, nvec, redo, h, S);
+int tri_rh_retake(int batch, int ld, int maxn, const int* nvec, const int* steps, const TriIn& h, C64* S, int L,
+                  hipStream_t st) {
+  hipLaunchKernelGGL(k_tri_restart, dim3(64, batch), dim3(256), 0, st, ld, nvec, steps, h, S);
+  tri_tiles(tri_ws(tri_layout(batch, ld, maxn, L), batch, ld, L, nullptr), batch, nvec, L, steps, S, st);
   NK_HIP(hipGetLastError());
   return NK_OK;
 }

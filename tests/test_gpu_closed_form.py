@@ -4,7 +4,8 @@ loose tolerances, wide spectra and the workspace's bound."""
 import numpy as np
 import pytest
 
-from tests.gpu_helpers import banner, nk
+import latgen
+from tests.gpu_helpers import banner, make_lattice, nk, rel, to_dev, to_host, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -94,3 +95,68 @@ def test_badly_scaled_inner_problem(n, ell, r):
         z, info, rc = b.nk_small_sign(n, ell, True, a, be, de, b.nk_sign_params_default(rh_scaling=scaling))
         assert rc == 0 and info.ell_used == ell
         assert abs(np.linalg.norm(z) - 1.0) < 1e-10
+
+
+@pytest.mark.parametrize("n", [6, 60, 128, 130, 300])
+@pytest.mark.parametrize("tol", [0.3, 1e-2, 1e-4, 2e-9, 1e-10])
+def test_loose_tolerance_returns_the_iterate_it_names(n, tol):
+    """With a loose tolerance the result is iterate rh_iters of Eq. (4), not a
+    later one: against the oracle's iteration stopped by the same test, at the
+    capped iterates' 1e-11 (at 1e-10 and below S_L is that iterate to rounding:
+    the next change is of the square)."""
+    from oracle import rh as R
+    b = nk()
+    a, be, de = _intervals(n, 3)
+    a[-1], be[n - 2], de[n - 2] = 0.05, 0.0, 0.0  # an eigenvalue far from 1: more steps
+    T = _dense(a, be, de)
+    for scaling, scale in ((b.NK_RH_NONE, None), (b.NK_RH_DET, R.determinant_scale)):
+        S, it, _ = R.roberts_higham(T, tol=tol, scale=scale)
+        banner(f"tolerance {tol:g} n={n} scaling={scaling}")
+        z, info, rc = b.nk_small_sign(n, 0, True, a, be, de, b.nk_sign_params_default(rh_scaling=scaling, rh_tol=tol))
+        assert rc == 0 and info.rh_iters == it
+        assert np.linalg.norm(z - S[:, 0]) <= 1e-11
+        res = np.linalg.norm(S @ S - np.eye(n)) / np.sqrt(n)
+        assert abs(info.rh_residual - res) <= 1e-10 + 1e-6 * res
+
+
+DIMS, MU = (4, 4, 2, 6), 0.3
+
+
+def _sources(lat, xs, block, **kw):
+    b = nk()
+    p = b.nk_sign_params_default(mu=MU, nrhs=len(xs), block=block, **kw)
+    dx = to_dev(xs)
+    dy = torch_cuda().empty_like(dx)
+    info, rc = b.nk_sign_apply_device(lat.h, p, dx, dy)
+    assert rc == 0
+    return to_host(dy).reshape(len(xs), -1), info
+
+
+def test_loose_tolerance_of_a_batch():
+    """Sources of one call that stop at different steps, in lockstep against
+    one at a time (k = 60 on this lattice: 1e-9, the tolerance of that
+    comparison at k = 100)."""
+    lat, _ = make_lattice(DIMS, 0.6, seed=1)
+    xs = latgen.random_sources(DIMS, 4, 7)
+    for tol in (0.3, 1e-2, 1e-4):
+        banner(f"lockstep with tolerance {tol:g}")
+        kw = dict(k=60, ell_per_rhs=[2, 9, 20, 30], rh_tol=tol)
+        (yb, ib), (ys, i1) = _sources(lat, xs, 1, **kw), _sources(lat, xs, 0, **kw)
+        assert ib.rh_iters == i1.rh_iters
+        for s in range(len(xs)):
+            assert rel(yb[s], ys[s]) < 1e-9, (tol, s)
+    lat.close()
+
+
+@pytest.mark.parametrize("r", [40, 130, 400, 560])
+def test_batches_at_the_workspace_bound(r):
+    """Plain problems of order 60 by the hundred: nine, eight and six steps in
+    closed form, and none, within 512 MB; the others with explicit inverses.
+    In lockstep against one at a time (k = 60: 1e-9 as above)."""
+    lat, _ = make_lattice(DIMS, 0.6, seed=1)
+    xs = latgen.random_sources(DIMS, r, 7)
+    banner(f"{r} plain problems in one batch")
+    (yb, ib), (ys, i1) = _sources(lat, xs, 1, k=60, ell=0), _sources(lat, xs, 0, k=60, ell=0)
+    assert abs(ib.rh_iters - i1.rh_iters) <= 1
+    assert max(rel(yb[s], ys[s]) for s in range(r)) < 1e-9
+    lat.close()
