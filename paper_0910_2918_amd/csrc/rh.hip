@@ -1038,6 +1038,7 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
                     int* iters_host, double* resid_host, hipStream_t st, const TriIn* tri) {
   std::lock_guard<std::mutex> lock(g_rh_mu);
   if (batch <= 0 || ld <= 0) return NK_OK;
+  if (scaling != NK_RH_DET && scaling != NK_RH_LEARNED) scaling = NK_RH_NONE;  // (callers need not refuse other values)
   if (ld > 4 * PT) {
     set_error("Roberts-Higham: matrix size %d exceeds %d", ld, 4 * PT);
     return NK_EINVAL;
@@ -1334,9 +1335,8 @@ int rh_sign_batched(int batch, int ld, const int* n_host, C64* S, int scaling, i
       const int nbw = gj_nb(ld);
       launch_inverse_shape(shape, batch, ld, maxn, nvec, act, S, g_G0.as<C64>(), g_G1.as<C64>(), rowof, posof, logdet,
                            sing, st);
-      const int rs = scaling == NK_RH_LEARNED ? NK_RH_LEARNED : (scaling == NK_RH_DET ? NK_RH_DET : NK_RH_NONE);
       hipLaunchKernelGGL(k_gjcombine, dim3(nbl, batch), dim3(256), 0, st, ld, nbw, nvec, act, g_G0.as<C64>(),
-                         g_G1.as<C64>(), S, rowof, posof, logdet, rs, mdev, mu_steps, it - 1, part);
+                         g_G1.as<C64>(), S, rowof, posof, logdet, scaling, mdev, mu_steps, it - 1, part);
       NK_HIP(hipGetLastError());
     }
     if (int e = sums()) return e;

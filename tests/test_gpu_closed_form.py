@@ -160,3 +160,16 @@ def test_batches_at_the_workspace_bound(r):
     assert abs(ib.rh_iters - i1.rh_iters) <= 1
     assert max(rel(yb[s], ys[s]) for s in range(r)) < 1e-9
     lat.close()
+
+
+@pytest.mark.parametrize("n,ell", [(20, 0), (140, 0), (140, 20)])
+def test_unnamed_scaling_is_no_scaling(n, ell):
+    """nk_small_sign takes any rh_scaling; values that name no scaling iterate
+    unscaled (the same steps: the same bits)."""
+    b = nk()
+    a, be, de = _intervals(n, 5)
+    banner(f"unnamed scaling n={n} ell={ell}")
+    z0, i0, _ = b.nk_small_sign(n, ell, True, a, be, de, b.nk_sign_params_default())
+    for scaling in (-1, 3, 7):
+        z, i, rc = b.nk_small_sign(n, ell, True, a, be, de, b.nk_sign_params_default(rh_scaling=scaling))
+        assert rc == 0 and i.rh_iters == i0.rh_iters and np.array_equal(z, z0)
