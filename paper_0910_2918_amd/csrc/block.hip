@@ -41,7 +41,11 @@ struct BArgs {
   C64* delta;     // [r][k]
   double* sv;     // [r][k + 1]
   C64* sw;        // [r][k + 1]
-  int* flags;     // [r]: 0 running, > 0 breakdown step, -1 zero source
+  // [r]: 0 running, > 0 breakdown step, -1 zero source.  k_blk1 reads flags and
+  // writes flags1, k_blk2 reads flags1 and hands it on to flags: no launch reads
+  // what it writes, so every wave of a workgroup decides alike.
+  int* flags;
+  int* flags1;
   double* part1;  // [r][2][nb1]
   double* part2;  // [r][4][nb2]
   int nb1, nb2;
@@ -160,7 +164,7 @@ __global__ void __launch_bounds__(BT) k_bred2(BArgs a, int j) {
   if (threadIdx.x != 0) return;
   Fin f;
   if (const int flag = finish(red, j, f))
-    a.flags[s] = flag;
+    a.flags[s] = a.flags1[s] = flag;
   else
     store_fin(a, s, j, f);
 }
@@ -214,7 +218,7 @@ __global__ void __launch_bounds__(BT) k_blk1(Geom g, LinksPlain<double> lk, doub
   Fin fin;
   const bool first = blockIdx.x == 0 && threadIdx.x == 0;
   if (const int flag = finish(red, j, fin)) {
-    if (first) a.flags[src] = flag;
+    if (first) a.flags1[src] = flag;
     return;
   }
   if (first) store_fin(a, src, j, fin);
@@ -339,7 +343,10 @@ __global__ void __launch_bounds__(BT) k_blkS(Geom g, LinksPlain<double> lk, doub
 // launch for that cost 4.8 us a step).
 __global__ void __launch_bounds__(BT, 8) k_blk2(BArgs a, int j) {
   const int s = blockIdx.y;
-  if (a.flags[s]) return;
+  if (const int flag = a.flags1[s]) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.flags[s] = flag;
+    return;
+  }
   const C64* p = vp(a, s);
   const C64* q = vq(a, s);
   const C64* v = colv(a, s, j);
@@ -494,7 +501,7 @@ int sweep_graph(nk_lattice* lat, const BArgs& a, int ng, int grp, double m_w, do
     kb.insert(kb.end(), c, c + sizeof v);
   };
   put(a.base), put(a.n), put(a.nslots), put(a.ncols), put(a.store), put(a.r), put(a.k);
-  put(a.alpha), put(a.beta), put(a.delta), put(a.sv), put(a.sw), put(a.flags), put(a.part1), put(a.part2);
+  put(a.alpha), put(a.beta), put(a.delta), put(a.sv), put(a.sw), put(a.flags), put(a.flags1), put(a.part1), put(a.part2);
   put(a.nb1), put(a.nb2), put(a.lc), put(a.kused), put(ng), put(grp), put(kmax), put(m_w), put(mu);
   put(lat->U64.p), put(lat->g.V);
   hipGraphExec_t exec = nullptr;
@@ -575,7 +582,7 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
   };
   const size_t oA = take((size_t)r * k * sizeof(C64)), oB = take((size_t)r * k * sizeof(C64)),
                oD = take((size_t)r * k * sizeof(C64)), oSv = take((size_t)r * (k + 1) * sizeof(double)),
-               oSw = take((size_t)r * (k + 1) * sizeof(C64)), oF = take((size_t)r * sizeof(int)),
+               oSw = take((size_t)r * (k + 1) * sizeof(C64)), oF = take((size_t)2 * r * sizeof(int)),
                oP1 = take((size_t)r * 2 * a.nb1 * sizeof(double)), oP2 = take((size_t)r * 4 * a.nb2 * sizeof(double)),
                oZ = take((size_t)r * k * sizeof(C64)), oLc = take((size_t)r * k * sizeof(C64)),
                oKv = take((size_t)r * sizeof(int)), oLv = take((size_t)r * sizeof(int)),
@@ -589,6 +596,7 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
   a.sv = (double*)(base + oSv);
   a.sw = (C64*)(base + oSw);
   a.flags = (int*)(base + oF);
+  a.flags1 = a.flags + r;
   a.part1 = (double*)(base + oP1);
   a.part2 = (double*)(base + oP2);
   C64* z = (C64*)(base + oZ);
@@ -614,7 +622,7 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
     C64* xs = a.base + ((size_t)s * a.nslots + a.ncols + 4) * n;
     if (int e = pack_spinor<double>(g, x_canon + (size_t)s * n, xs, st)) return e;
   }
-  NK_HIP(hipMemsetAsync(a.flags, 0, r * sizeof(int), st));
+  NK_HIP(hipMemsetAsync(a.flags, 0, 2 * r * sizeof(int), st));
   NK_HIP(hipMemsetAsync(a.beta, 0, (size_t)r * k * sizeof(C64), st));
   NK_HIP(hipMemsetAsync(a.delta, 0, (size_t)r * k * sizeof(C64), st));
   // sources per workgroup of the stencil step: chosen once per handle by
@@ -729,7 +737,7 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
     BArgs b = a;
     b.lc = lc;
     // the second sweep recomputes the coefficients bit for bit; reset the state it reads
-    NK_HIP(hipMemsetAsync(a.flags, 0, r * sizeof(int), st));
+    NK_HIP(hipMemsetAsync(a.flags, 0, 2 * r * sizeof(int), st));
     int kmax = 0;
     for (int s = 0; s < r; ++s) kmax = std::max(kmax, kus[s]);
     if (int e = run_sweep(b, kmax - 1 > 0 ? kmax - 1 : 0)) return e;

@@ -201,6 +201,36 @@ def test_lockstep_breakdown_leaves_the_other_source_alone():
     lat.close()
 
 
+@pytest.mark.parametrize("grp", [1, 2, 4])
+def test_lockstep_breakdown_in_every_form(grp):
+    """The same beside three Gaussian sources, with one, two and four sources
+    per workgroup, one and two sweeps, and direct launches and graph replays:
+    the broken-down source ends at its step in each form and is told to the
+    launches after it, the others agree with the first form (the same sums in
+    another lift: 1e-13)."""
+    b = nk()
+    mu, k, ell = 0.3, 24, 6
+    x0, y0ref = _breakdown_case(mu)
+    xs = latgen.random_sources(BS.DIMS, 3, 11)
+    lat, _ = make_lattice(BS.DIMS, 0.0, unit=True)
+    b.nk_block_group(lat.h, grp)
+    banner(f"lockstep breakdown, {grp} sources per workgroup")
+    xb = to_dev(np.stack([xs[0], x0, xs[1], xs[2]]))
+    first = None
+    for block in (1, 2, 2):
+        for two_pass in (2, 1):
+            yb = torch_cuda().empty_like(xb)
+            p = b.nk_sign_params_default(k=k, ell=ell, mu=mu, nrhs=4, block=block, two_pass=two_pass)
+            info, rc = b.nk_sign_apply_device(lat.h, p, xb, yb)
+            assert rc == b.NK_WARN_BREAKDOWN and info.breakdown_step == 1 and info.k_used == k
+            y = to_host(yb).reshape(4, -1)
+            assert rel(y[1], y0ref) < 1e-12
+            first = y if first is None else first
+            for s in (0, 2, 3):
+                assert rel(y[s], first[s]) < 1e-13
+    lat.close()
+
+
 def test_destroyed_handles_and_host_calls_free_their_device_memory():
     """A cycle of handle create, host-pointer application, lockstep run and
     destroy, twice: the second cycle ends with as much free device memory as
