@@ -627,7 +627,9 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
   NK_HIP(hipMemsetAsync(a.delta, 0, (size_t)r * k * sizeof(C64), st));
   // sources per workgroup of the stencil step: chosen once per handle by
   // timing the step with 1, 2 and 4 (five launches each at step 0, after the
-  // start kernels; the real sweep repeats them); a larger group is taken only
+  // start kernels; the real sweep repeats them), each with all that its step
+  // needs: k_blk1 finishes the step before by itself, k_blkS after a launch of
+  // k_bred2 (4.8 us).  A larger group is taken only
   // when it is more than 5% faster, so that timing noise does not change the
   // kernel, and so the grouping of the partial sums, from one process to the
   // next
@@ -635,7 +637,6 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
   if (grp == 0) {
     const LinksPlain<double> lk{lat->U64.as<C64>(), g.V};
     hipLaunchKernelGGL(k_bstart, dim3(a.nb2, a.r), dim3(BT), 0, st, a);
-    hipLaunchKernelGGL(k_bred2, dim3(a.r), dim3(BT), 0, st, a, 0);
     hipEvent_t t0, t1;
     NK_HIP(hipEventCreate(&t0));
     NK_HIP(hipEventCreate(&t1));
@@ -644,10 +645,13 @@ static int block_range(nk_lattice* lat, const nk_sign_params* p, const int* ell,
     for (int gsz : {1, 2, 4}) {
       BArgs at = a;
       at.nb1 = nb1_of(gsz);
-      launch_blk1(g, lk, ng, gsz, p->m_w, exp(p->mu), exp(-p->mu), 0, at, nullptr, nullptr, st);
-      NK_HIP(hipEventRecord(t0, st));
-      for (int rep = 0; rep < 5; ++rep)
+      auto step = [&]() {
+        if (gsz > 1) hipLaunchKernelGGL(k_bred2, dim3(a.r), dim3(BT), 0, st, at, 0);
         launch_blk1(g, lk, ng, gsz, p->m_w, exp(p->mu), exp(-p->mu), 0, at, nullptr, nullptr, st);
+      };
+      step();
+      NK_HIP(hipEventRecord(t0, st));
+      for (int rep = 0; rep < 5; ++rep) step();
       NK_HIP(hipEventRecord(t1, st));
       NK_HIP(hipEventSynchronize(t1));
       float ms = 0.f;
