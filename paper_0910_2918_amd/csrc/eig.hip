@@ -19,7 +19,7 @@
 //     tol * sqrt(b2).
 // Vector work runs in kernels on whole blocks: the stencil with the Chebyshev
 // step in its epilogue (k_apply_block), Gram matrices (k_gram) and block
-// rotations (k_rotate) on the FP64 matrix cores, residual norms (k_resid).
+// rotations (k_rotate) on the FP64 matrix cores, residual norms (k_cols).
 // The p x p Cholesky and Jacobi steps run on the host; their matrices pass
 // through pinned memory.  The iteration works in the library's packed device
 // layout: every step but the stencil is an inner product or a linear

@@ -203,7 +203,7 @@ __global__ void __launch_bounds__(NT) k_lan2(int n, int j, const Cx<R>* __restri
                                              Cx<R>* __restrict__ vnext, const double* __restrict__ partIn, int nbIn,
                                              double* __restrict__ partOut, Coefs c, LiftAcc lift) {
   // the loads of four elements per thread are issued before the partial sums
-  // of K1 are reduced, and those of the next four before these are stored
+  // of K1 are reduced, those of the next four right after these are stored
   constexpr int U = 4;
   const int stride = gridDim.x * NT;
   int i0 = blockIdx.x * NT + threadIdx.x;

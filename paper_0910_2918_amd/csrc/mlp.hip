@@ -5,7 +5,7 @@
 // so the factors change only the iteration count.  For the first T steps the
 // factor is determinant scaling times a learned correction,
 //   mu_t = |det S_t|^{-1/n} exp(y_t),
-// with y predicted by a 16-64-64-64-T network (tanh, FP32) from cheap
+// with y predicted by a 16-64-64-64-T network (tanh, FP32 weights) from cheap
 // features f of S_0:
 //   x = (f - mean) * inv_std,  a_l = tanh(W_l a_{l-1} + b_l) (l = 1, 2, 3),
 //   y = W4 a3 + b4,
@@ -19,8 +19,9 @@
 // spectral loss with its gradient, backward pass (per-sample deltas, then the
 // weight gradients summed over the batch in a fixed order -- deterministic),
 // and Adam.  The forward pass and the weight gradients are contractions over
-// the units and over the batch and run on the FP32 matrix cores; the
-// per-sample deltas are small matrix-vector products on the vector ALUs.
+// the units and over the batch and run on the matrix cores, in FP64 and in
+// FP32; the per-sample deltas are small matrix-vector products on the vector
+// ALUs.
 #include <cmath>
 #include <mutex>
 

@@ -63,19 +63,13 @@ __device__ __forceinline__ C64 cmul_b(C64 a, C64 b) {
 __device__ __forceinline__ C64 csel(bool c, C64 a, C64 b) { return mk(c ? a.re : b.re, c ? a.im : b.im); }
 // 1 / b = conj(b) / |b|^2 with b first scaled by a power of two (exact) so
 // that |b|^2 neither overflows nor underflows: one division on the
-// recurrence's critical path instead of cdiv's four
+// recurrence's critical path
 __device__ __forceinline__ C64 crecip(C64 b) {
   int e;
   (void)frexp(fmax(fabs(b.re), fabs(b.im)), &e);
   const double br = ldexp(b.re, -e), bi = ldexp(b.im, -e);
   const double q = 1.0 / (br * br + bi * bi);
   return mk(ldexp(br * q, -e), ldexp(-bi * q, -e));
-}
-__device__ __forceinline__ C64 cdiv(C64 a, C64 b) {
-  const double s = fmax(fabs(b.re), fabs(b.im));
-  const double br = b.re / s, bi = b.im / s;
-  const double d = (br * br + bi * bi) * s;
-  return mk((a.re * br + a.im * bi) / d, (a.im * br - a.re * bi) / d);
 }
 
 // LU with partial pivoting of the tridiagonal H (diag alpha, super beta,

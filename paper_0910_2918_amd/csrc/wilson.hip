@@ -64,8 +64,8 @@ __global__ void __launch_bounds__(256) k_apply(Geom g, LK lk, R diag, int g5, Fi
 // 8^4 one vector is 64 workgroups, a quarter of the compute units, and its
 // launches follow each other no faster than every 5 us; the block runs 48
 // vectors in 28 us (with the recurrence step 34).  The hardware deals
-// workgroup b to XCD b mod 8, so every vector's site block lands on the XCD
-// that holds its links.  Folding the recurrence step in saves writing and
+// workgroup b to XCD b mod 8, so where a vector has a multiple of eight site
+// blocks, each lands on the XCD that holds its links.  Folding the recurrence step in saves writing and
 // reading A x (a third of the bytes of the step).
 template <int NG, bool CHEB>
 __global__ void __launch_bounds__(256) k_apply_block(Geom g, LinksPlain<double> lk, double diag, ApplyBlock a) {
