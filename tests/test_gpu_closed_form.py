@@ -173,3 +173,29 @@ def test_unnamed_scaling_is_no_scaling(n, ell):
     for scaling in (-1, 3, 7):
         z, i, rc = b.nk_small_sign(n, ell, True, a, be, de, b.nk_sign_params_default(rh_scaling=scaling))
         assert rc == 0 and i.rh_iters == i0.rh_iters and np.array_equal(z, z0)
+
+
+@pytest.mark.parametrize("n", [6, 60, 128, 130, 300])
+@pytest.mark.parametrize("det", [False, True])
+def test_cap_is_reported_only_when_it_ended_the_iteration(n, det):
+    """The return code under every cap from 1 to 12, past the steps in closed
+    form too: a warning if and only if the stopping test had not held by then,
+    with the iterate (1e-11).  The tolerance, 1e-10, lies a factor of 10 or
+    more from every change of these iterations."""
+    from oracle import rh as R
+    b = nk()
+    a, be, de = _intervals(n, 3)
+    a[-1], be[n - 2], de[n - 2] = 0.05, 0.0, 0.0
+    T = _dense(a, be, de)
+    scale = R.determinant_scale if det else None
+    _, stop, _ = R.roberts_higham(T, tol=1e-10, scale=scale)
+    assert 6 < stop < 12
+    banner(f"caps n={n} det={det}, stops at {stop}")
+    for maxit in range(1, 13):
+        S, it, _ = R.roberts_higham(T, tol=1e-10, maxit=maxit, scale=scale)
+        p = b.nk_sign_params_default(rh_maxit=maxit, rh_tol=1e-10,
+                                     rh_scaling=b.NK_RH_DET if det else b.NK_RH_NONE)
+        z, info, rc = b.nk_small_sign(n, 0, True, a, be, de, p)
+        assert info.rh_iters == it == min(maxit, stop)
+        assert rc == (0 if stop <= maxit else b.NK_WARN_NOTCONV), maxit
+        assert np.linalg.norm(z - S[:, 0]) <= 1e-11 * max(1.0, np.linalg.norm(S[:, 0]))

@@ -45,6 +45,28 @@ def test_mlp_batch_remainders(B, shift):
     assert off(grad.cpu().numpy(), g) < 2e-5
 
 
+@pytest.mark.parametrize("B", [1, 17, 65, 2048])
+def test_mlp_forward_is_double_up_to_storage(B):
+    """The forward pass computes in FP64 and rounds to FP32 where y and the
+    activations are stored: 2^-24 of each, 6e-8, and no more of their norms
+    (sums in FP32 are off by 2e-7)."""
+    torch = torch_cuda()
+    b = nk()
+    rng = np.random.default_rng(B)
+    p = latgen.mlp_init(B).astype(np.float32)
+    p[:L.NTRAIN] += (0.1 * rng.standard_normal(L.NTRAIN)).astype(np.float32)
+    f = rng.standard_normal((B, L.NIN)).astype(np.float32)
+    banner(f"mlp forward in FP64, batch {B}")
+    y = torch.zeros((B, L.T), dtype=torch.float32, device="cuda")
+    act = torch.zeros((B, 3, L.NH), dtype=torch.float32, device="cuda")
+    b.nk_mlp_forward_device(torch.from_numpy(p).cuda(), torch.from_numpy(f).cuda(), y, act)
+    ref, acts = L.forward(p.astype(np.float64), f.astype(np.float64))
+    off = lambda got, want: np.linalg.norm(got - want) / np.linalg.norm(want)  # noqa: E731
+    assert off(y.cpu().numpy(), ref) < 6e-8
+    for i in range(3):
+        assert off(act.cpu().numpy()[:, i], acts[1 + i]) < 6e-8
+
+
 def test_spectral_loss_sizes():
     """Spectra at the edges of the kernel's slots (256, 512 and 1024
     eigenvalues) and of a wave, and an empty one, in one batch against the
