@@ -121,9 +121,11 @@ __global__ void __launch_bounds__(256) k_apply_block(Geom g, LinksPlain<double> 
 // too, each lane reading its neighbours' 192 bytes where they lie (twelve loads
 // that share their lines; the L1 holds a wave's 12 KB of them); grid y =
 // vector.  That spares the packing launch and its pass over memory.  The
-// results are stored past the L2, which the neighbours and links need: 24^4 96
-// -> 79 us, 16^4 18.8 -> 17.8 (y read back by the next application: 98.6 ->
-// 91.4, 19.0 -> 18.8).
+// results are stored past the L2, which the neighbours and links need, on every
+// lattice: with them kept in it and past it, 24^4 95 and 79 us, 16^4 18.6 and
+// 17.6, 20736 sites 9.7 and 9.4, 8^4 5.45 and 5.47 (y read back by the next
+// application: 98 and 90, 18.9 and 18.3, 10.5 and 10.4, 5.86 and 5.86; so on 4^4
+// and 6^4, 5.5 and 5.5, 5.8 and 5.7: what one XCD stored, seven others read).
 template <int NG, bool CIN>
 __global__ void __launch_bounds__(256) k_apply_canon(Geom g, LinksPlain<double> lk, double diag, int g5, const C64* in,
                                                      C64* out, double ef, double eb) {
