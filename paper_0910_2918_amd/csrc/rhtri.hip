@@ -45,7 +45,7 @@
 // singular), when a row is more than 2^50 below the largest entry (a pivot
 // below 1e-30 could then be the true one), or when the minors leave 2^-900
 // within a block of rows (the next one could underflow).  Entries of up to
-// 2^50 of their neighbours are taken: the reciprocals are formed of operands
+// 2^50 of their neighbours are taken: the quotients of minors are formed of operands
 // scaled by a power of two, since the minors of small rows fall by that factor
 // row after row (order 64, diagonal +-2 with one entry of 1e12: 2e-16 of S_9 e_1
 // from the explicit inverses; squares of unscaled minors underflowed from
@@ -88,16 +88,14 @@ __device__ __forceinline__ int expo(C64 a) {
   (void)frexp(fmax(fabs(a.re), fabs(a.im)), &e);
   return e;
 }
-// 1 / a: one reciprocal with two Newton steps, of |a|^2 scaled by a power of
-// two (exact), so that minors anywhere in the exponent range will do
+// 1 / a: one reciprocal with two Newton steps (of pivots, between 1e-30 and
+// 1e30 by the replacement of smaller ones, and what they are combined to)
 __device__ __forceinline__ C64 recip(C64 a) {
-  const int e = expo(a);
-  const double re = ldexp(a.re, -e), im = ldexp(a.im, -e);
-  const double n = fma(im, im, re * re);
+  const double n = fma(a.im, a.im, a.re * a.re);
   double y = __builtin_amdgcn_rcp(n);
   y = fma(y, fma(-n, y, 1.0), y);
   y = fma(y, fma(-n, y, 1.0), y);
-  return mk(ldexp(re * y, -e), ldexp(-im * y, -e));
+  return mk(a.re * y, -a.im * y);
 }
 
 // the zero with index q = 2^n + j of S_n and its residue (mu == nullptr: unscaled)
@@ -337,6 +335,12 @@ __global__ void __launch_bounds__(512) k_tri_chain_mu(TriWs w, TriIn h, const in
 __device__ __forceinline__ C64 quot(C64 a, C64 b) {
   return cmul(a, recip(b));
 }
+// the quotient of two minors, which may lie anywhere in the exponent range:
+// both scaled by the power of two (exact) that brings b to one
+__device__ __forceinline__ C64 quot_minors(C64 a, C64 b) {
+  const int e = expo(b);
+  return quot(mk(ldexp(a.re, -e), ldexp(a.im, -e)), mk(ldexp(b.re, -e), ldexp(b.im, -e)));
+}
 // rho / g and the products within a block of 16 rows: a lane per pole, a wave
 // per block and direction (y = 2 block + direction); every load is known at
 // the start, so the whole block costs about one memory round trip
@@ -384,7 +388,7 @@ __global__ void __launch_bounds__(64) k_tri_mid(TriWs w, TriIn h, const int* __r
     C64 ln = mk(0.0, 0.0);
     if (more) {
       const C64 d = de[lo + nr - 1];
-      ln = quot(mk(-kap * d.re, -kap * d.im), quot(m0, m1));
+      ln = quot(mk(-kap * d.re, -kap * d.im), quot_minors(m0, m1));
     }
     if (nr == TB && more) mv[TB] = fix(mv[TB], mp1);  // (M_n = 1 needs none)
 #pragma unroll
@@ -394,7 +398,7 @@ __global__ void __launch_bounds__(64) k_tri_mid(TriWs w, TriIn h, const int* __r
     for (int k = TB - 1; k >= 0; --k) {
       if (k < nr) {
         const int j = lo + k;
-        const C64 D = quot(nv[k + 1], nv[k]);  // kappa D_j
+        const C64 D = quot_minors(nv[k + 1], nv[k]);  // kappa D_j
         const C64 bj = be[j + 1 < n ? j : 0];
         C64 gj = D;
         if (j + 1 < n) gj = gj + cmul(mk(kap * bj.re, kap * bj.im), ln);
@@ -402,7 +406,7 @@ __global__ void __launch_bounds__(64) k_tri_mid(TriWs w, TriIn h, const int* __r
         const double f0 = rho * kap;
         g[k] = mk(rho != 0.0 ? f0 * r.re : 0.0, rho != 0.0 ? f0 * r.im : 0.0);  // (rho = 0: padding)
         const C64 dj = de[j > 0 ? j - 1 : 0];
-        const C64 l = j > 0 ? quot(mk(-kap * dj.re, -kap * dj.im), quot(mv[k], mv[k + 1])) : mk(0.0, 0.0);
+        const C64 l = j > 0 ? quot(mk(-kap * dj.re, -kap * dj.im), quot_minors(mv[k], mv[k + 1])) : mk(0.0, 0.0);
         f[k] = dir ? l : (j + 1 < n ? quot(mk(-kap * bj.re, -kap * bj.im), D) : mk(0.0, 0.0));
         ln = l;
       } else {
