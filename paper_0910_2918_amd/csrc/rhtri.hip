@@ -145,7 +145,9 @@ __device__ __forceinline__ size_t mix(const TriWs& w, int b, int c, int r) {
 }
 
 // 64 rows of a matrix in LDS: the diagonal, and the product b d of the pair
-// that couples a row to the one before it in the recurrence
+// that couples a row to the one before it in the recurrence, both of the matrix
+// over the power of two that brings its largest entry to one (exact; products
+// of entries below 1e-154 would underflow)
 struct Rows {
   C64 a[64], c[64];
 };
@@ -185,17 +187,19 @@ __device__ __forceinline__ void chain(const TriWs& w, const TriIn& h, int b, int
     sc = fmax(sc, __shfl_xor(sc, o, 64));
     if (DIR == 0 && rows) low = fmin(low, __shfl_xor(low, o, 64));
   }
-  int ke;
+  int ks, ke;
+  (void)frexp(sc, &ks);
   (void)frexp(sc + fabs(t), &ke);
-  const double kap = ldexp(1.0, -ke), kap2 = kap * kap, kt = kap * t;
-  if (DIR == 0) w.kap[(size_t)b * w.np + q] = kap;
+  const double kt = ldexp(t, -ke), kap = ldexp(1.0, ks - ke), kap2 = kap * kap;  // kap: of the rows in LDS
+  if (DIR == 0) w.kap[(size_t)b * w.np + q] = ldexp(1.0, -ke);
+  auto sca = [&](C64 v) { return mk(ldexp(v.re, -ks), ldexp(v.im, -ks)); };
   C64 ra, rc;
   auto fetch = [&](int k) {  // rows 64 k ..
     const int i = 64 * k + lane;
     const bool in = i < n;
     const int j = DIR == 0 ? i - 1 : i;  // the pair that couples row i to the row before it
     const bool inb = j >= 0 && j + 1 < n;
-    const C64 va = a[in ? i : 0], vc = cmul(be[inb ? j : 0], de[inb ? j : 0]);
+    const C64 va = sca(a[in ? i : 0]), vc = cmul(sca(be[inb ? j : 0]), sca(de[inb ? j : 0]));
     ra = mk(in ? va.re : 0.0, in ? va.im : 0.0);
     rc = mk(inb ? vc.re : 0.0, inb ? vc.im : 0.0);
   };

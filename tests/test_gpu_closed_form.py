@@ -199,3 +199,18 @@ def test_cap_is_reported_only_when_it_ended_the_iteration(n, det):
         assert info.rh_iters == it == min(maxit, stop)
         assert rc == (0 if stop <= maxit else b.NK_WARN_NOTCONV), maxit
         assert np.linalg.norm(z - S[:, 0]) <= 1e-11 * max(1.0, np.linalg.norm(S[:, 0]))
+
+
+@pytest.mark.parametrize("n", [6, 64, 130, 300])
+def test_size_of_the_whole_matrix(n):
+    """sgn(f T) e_1 = sgn(T) e_1 with determinant scaling, f down to where the
+    products of two entries leave the exponent range and up to where they
+    exceed it (condition below 10: 1e-12)."""
+    b = nk()
+    a, be, de = _intervals(n, 4)
+    w, q = np.linalg.eigh(_dense(a, be, de))
+    ref = (q * np.sign(w)) @ q[0].conj()
+    for f in (1e-200, 1e-165, 1e-156, 1e-120, 1e120, 1e150, 1e165):
+        banner(f"matrix times {f:g}, n={n}")
+        z, info, rc = b.nk_small_sign(n, 0, True, f * a, f * be, f * de, b.nk_sign_params_default(rh_scaling=b.NK_RH_DET))
+        assert rc == 0 and np.linalg.norm(z - ref) < 1e-12, f
