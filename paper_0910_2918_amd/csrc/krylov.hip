@@ -850,7 +850,11 @@ int two_pass_lift(nk_lattice* lat, const BasisPlan& bp0, const C64* x_canon, int
   BasisPlan bp = bp0;
   bp.store = 0;
   const LiftAcc lift{y_dev, lc, kused};
-  if (bp.hermitian) return run_any(lat, bp, x_canon, 0, kused - 1, c, nullptr, lift, st);
+  if (bp.hermitian) {
+    // a breakdown that ended the first sweep at kused must not end this one
+    NK_HIP(hipMemsetAsync(c.flags, 0, 4 * sizeof(int), st));
+    return run_any(lat, bp, x_canon, 0, kused - 1, c, nullptr, lift, st);
+  }
   const Geom& g = lat->g;
   if (bp.prec == NK_PREC_FP64)
     return regen_run<double>(lat, bp, LinksPlain<double>{lat->U64.as<C64>(), g.V}, x_canon, kused, c, lift, st);

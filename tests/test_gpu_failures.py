@@ -160,6 +160,31 @@ def _breakdown_case(mu):
     return x, y
 
 
+@pytest.mark.parametrize("ell", [0, 2])
+@pytest.mark.parametrize("two_pass", [1, 2])
+def test_lanczos_on_an_exactly_invariant_space(ell, two_pass):
+    """On the free field with four-periodic phases in t (momentum pi / 2) and
+    m_w = -1, gamma5 Dw(0) maps spinor component 0 to one other and back, in
+    exact arithmetic: Lanczos ends after two steps, with one sweep and with
+    two, and sgn(A) x = A x."""
+    b = nk()
+    dims = (2, 2, 2, 2)
+    lat, u = make_lattice(dims, 0.0, unit=True)
+    x = np.zeros((2, 2, 2, 2, 4, 3), np.complex128)
+    x[0, ..., 0, 0], x[1, ..., 0, 0] = 1.0, 1j
+    ref = np.asarray(W.a_apply(u, x, -1.0, 0.0))
+    assert np.array_equal(np.asarray(W.a_apply(u, ref, -1.0, 0.0)), x) and not np.array_equal(abs(ref), abs(x))
+    banner(f"invariant space of two vectors, ell={ell} two_pass={two_pass}")
+    dx = to_dev(x)
+    dy = torch_cuda().empty_like(dx)
+    p = b.nk_sign_params_default(k=10, ell=ell, mu=0.0, m_w=-1.0, two_pass=two_pass)
+    info, rc = b.nk_sign_apply_device(lat.h, p, dx, dy)
+    assert rc == b.NK_WARN_BREAKDOWN and info.breakdown_step == 2 and info.k_used == 2
+    assert info.two_pass == (1 if two_pass == b.NK_TWO_PASS_ON else 0)
+    assert rel(to_host(dy), ref.reshape(-1)) < 1e-13
+    lat.close()
+
+
 @pytest.mark.parametrize("mu", [0.3, 0.5])
 @pytest.mark.parametrize("ell", [0, 4])
 def test_two_sided_serious_breakdown(mu, ell):
