@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(NT) k_lan1(Geom g, LK lk, R diag, int j, const
   block_sum<1>(red);  // also completes the exchange
   const double beta = sqrt(red[0]);
   if (!(beta > 0.0) || !(beta < 1e300)) {  // invariant subspace reached (or non-finite input)
-    if (blockIdx.x == 0 && threadIdx.x == 0) c.flags[0] = j > 0 ? j : -1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) c.flags[1] = j > 0 ? j : -1;
     return;
   }
   const double svj = 1.0 / beta;
@@ -216,9 +216,12 @@ __global__ void __launch_bounds__(NT) k_lan2(int n, int j, const Cx<R>* __restri
       vv[u] = vj[i];
     }
   };
-  const int flag = c.flags[0];
+  const int flag = c.flags[1];
   load(i0);
-  if (flag) return;
+  if (flag) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) c.flags[0] = flag;
+    return;
+  }
   double red[1];
   reduce_partials<1>(partIn, nbIn, red);
   const double alpha = red[0];
@@ -303,11 +306,11 @@ __global__ void __launch_bounds__(NT) k_bil1(Geom g, LK lk, R diag, R eft, R ebt
   const C64 sdot = mk(red[0], red[1]);
   const double sabs = sqrt(norm2(sdot));
   if (j == 0 && !(sabs > 0.0 && sabs < 1e300)) {  // zero or non-finite source
-    if (blockIdx.x == 0 && threadIdx.x == 0) c.flags[0] = -1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) c.flags[1] = -1;
     return;
   }
   if (j > 0 && !(sabs > 1e-14 * sqrt(red[2] * red[3]))) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) c.flags[0] = j;
+    if (blockIdx.x == 0 && threadIdx.x == 0) c.flags[1] = j;
     return;
   }
   const double delta = sqrt(sabs);
@@ -391,9 +394,12 @@ __global__ void __launch_bounds__(NT) k_bil2(int n, int j, const Cx<R>* __restri
       }
     }
   };
-  const int flag = c.flags[0];
+  const int flag = c.flags[1];
   load(i0);
-  if (flag) return;
+  if (flag) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) c.flags[0] = flag;
+    return;
+  }
   double red[2];
   reduce_partials<2>(partIn, nbIn, red);
   const double svj = c.sv[j];

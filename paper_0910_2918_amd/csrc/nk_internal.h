@@ -307,7 +307,10 @@ struct Coefs {
   C64* delta;  // [k]  delta[j] = H[j+1][j]
   double* sv;  // [k+1] v_j = sv[j] * vt_j
   C64* sw;     // [k+1] w_j = sw[j] * wt_j
-  int* flags;  // [4]: 0 = breakdown step (0 = none)
+  // [4]: 0 = breakdown step (0 = none); 1 = the same from K1, which reads the
+  // first and writes this one, to K2, which hands it on to the first: no launch
+  // reads what it writes, so every wave of a workgroup decides alike
+  int* flags;
 };
 struct BasisPlan {
   int prec;       // NK_PREC_*

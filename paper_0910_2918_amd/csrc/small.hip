@@ -46,6 +46,9 @@ struct Inner {
   C64* a;
   C64* b;
   C64* d;
+  // breakdown step (0: none), singular H_k, and the breakdown step from
+  // k_in_gemv, which reads the first and writes this one, to k_in_sub, which
+  // hands it on to the first: no launch reads what it writes
   int* flags;
   C64* hcol;     // [lmax][lmax] Arnoldi: column i of H_l at i * lmax (both passes summed)
   int arnoldi;   // 1: one-sided recurrence on a general B, every coefficient kept
@@ -229,7 +232,7 @@ __global__ void __launch_bounds__(256) k_tri_lu(const Inner s0, const Inner* __r
     stg(as_global(s.d) + j, z);
   }
   gp<int> flags = as_global(s.flags);
-  if (threadIdx.x == 0) flags[0] = 0;
+  if (threadIdx.x == 0) flags[0] = flags[2] = 0;
   const bool lds = k <= TRI_LDS_MAX, rec = k <= TRI_REC_MAX;
   if (lds) {
     for (int i = threadIdx.x; i < k; i += blockDim.x) {
@@ -597,7 +600,7 @@ __global__ void __launch_bounds__(GR * 64) k_in_gemv(const Inner s0, const Inner
     const C64 sd = s.herm ? mk(v[2], 0.0) : mk(v[0], v[1]);
     const double sabs = sqrt(fma(sd.re, sd.re, sd.im * sd.im));  // (rounded in this order in every build)
     if (!(sabs > 1e-14 * sqrt(v[2] * (s.herm ? v[2] : v[3])))) {
-      if (blk == 0 && side == 0 && threadIdx.x == 0) s.flags[0] = i;
+      if (blk == 0 && side == 0 && threadIdx.x == 0) s.flags[2] = i;
       return;
     }
     const double delta = sqrt(sabs);
@@ -739,7 +742,7 @@ __global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __re
     }
   };
   static_assert(SR == 8 * TPJ, "one batch of loads covers the block's rows");
-  int flag = s.flags[0];
+  int flag = s.flags[2];
   load_part(side1, j1, l4);
   load_basis(jl);
   gp<C64> x = rawv(s, side2, (i + 1) & 1);
@@ -773,7 +776,10 @@ __global__ void __launch_bounds__(ST) k_in_sub(const Inner s0, const Inner* __re
     o[0] = flag;
     o[1] = s.flags[1];
   }
-  if (flag) return;
+  if (flag) {
+    if (blk == 0 && threadIdx.x == 0) s.flags[0] = flag;
+    return;
+  }
   __syncthreads();
   if (!last && blk == 0 && threadIdx.x == 0) stg(s.a + i, s.herm ? mk(s_c[0][i].re, 0.0) : s_c[0][i]);
   if (s.arnoldi && blk == 0)  // column i of H_l: the first pass stores, the second adds
