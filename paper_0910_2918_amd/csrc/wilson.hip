@@ -10,7 +10,7 @@ namespace nk {
 // Directions split over the waves of the workgroup (hop_group); NF lanes per
 // site, lane f on field f.  Bound by the caches: an XCD's 4 MB L2 holds about
 // eight tiles' links and spinors, so the spinors that cross a tile in z and t
-// are fetched again (573 MB read for 318 on 24^4).  PAST: results, a fifth of
+// are fetched again (529 to 573 MB read for 318 on 24^4).  PAST: results, a fifth of
 // what would share that L2, are stored past it (see apply_pair_dev).
 template <class R, int NF, class LK, int NG, bool PAST = false>
 __global__ void __launch_bounds__(256) k_apply(Geom g, LK lk, R diag, int g5, FieldPtrs<R, NF> in,
