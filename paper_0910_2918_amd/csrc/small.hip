@@ -929,6 +929,11 @@ std::mutex g_coef_mu;
 DevBuf g_coef;        // coefficients of small_sign_host, and
 HostBuf g_coef_pin;   // their pinned staging, with the result
 
+__global__ void k_zeros(int n, C64* __restrict__ z) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) z[i] = mk(0.0, 0.0);
+}
+
 __global__ void k_upload(int n, const C64* __restrict__ host, C64* __restrict__ dev) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dev[i] = host[i];
@@ -1070,7 +1075,9 @@ int small_sign_dev(int k, int ell, int hermitian, const C64* alpha, const C64* b
   NK_HIP(hipStreamSynchronize(st));
   const int* fl = g_small_pin.host<int>();
   const int brk = fl[0];
-  if (fl[1]) {
+  if (fl[1]) {  // no result: zeros, not what the buffer held
+    if (z) hipLaunchKernelGGL(k_zeros, dim3((k + 255) / 256), dim3(256), 0, st, k, z);
+    NK_HIP(hipGetLastError());
     set_error("nested small problem: H_k is singular");
     return NK_WARN_NOTCONV;
   }
@@ -1138,7 +1145,8 @@ int small_sign_host(int k, int ell, int hermitian, const void* alpha, const void
 // H_ell (diagonal, super-, sub-diagonal, zero from its last step on) goes to
 // hl_dev + s * 3 * ldh (rows of ldh) and its basis V_ell (column j at
 // j * k[s]) to vl_dev + s * vl_stride; ell_used[s] < ell[s] after an
-// invariant subspace or a breakdown.
+// invariant subspace or a breakdown, 0 where H_k is singular (the others are
+// not concerned).
 int small_inner_batch(int r, const int* k, const int* ell, int hermitian, const C64* alpha, const C64* beta,
                       const C64* delta, size_t cstride, C64* hl_dev, int ldh, C64* vl_dev, size_t vl_stride,
                       int* ell_used, hipStream_t st) {
@@ -1178,10 +1186,12 @@ int small_inner_batch(int r, const int* k, const int* ell, int hermitian, const 
   for (int s = 0; s < r; ++s) {
     if (fl[2 * s + 1]) {
       set_error("nested small problem %d: H_k is singular", s);
-      return NK_WARN_NOTCONV;
+      ell_used[s] = 0;
+      warn = NK_WARN_NOTCONV;
+      continue;
     }
     ell_used[s] = fl[2 * s] ? fl[2 * s] : ell[s];
-    if (fl[2 * s]) warn = NK_WARN_BREAKDOWN;
+    if (fl[2 * s] && warn == NK_OK) warn = NK_WARN_BREAKDOWN;
   }
   return warn;
 }

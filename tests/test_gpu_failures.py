@@ -185,6 +185,26 @@ def test_lanczos_on_an_exactly_invariant_space(ell, two_pass):
     lat.close()
 
 
+def test_singular_ritz_matrix_gives_zeros():
+    """The same source with k = 1: H_1 = 0, whose inverse the nested method
+    needs.  The call warns and returns zeros, not the small problem of the
+    application before it."""
+    b = nk()
+    dims = (2, 2, 2, 2)
+    lat, _ = make_lattice(dims, 0.0, unit=True)
+    x = np.zeros((2, 2, 2, 2, 4, 3), np.complex128)
+    x[0, ..., 0, 0], x[1, ..., 0, 0] = 1.0, 1j
+    dx, other = to_dev(x), to_dev(latgen.random_sources(dims, 1, 3))
+    dy = torch_cuda().empty_like(dx)
+    banner("singular H_k, nested")
+    _, rc = b.nk_sign_apply_device(lat.h, b.nk_sign_params_default(k=20, ell=8, mu=0.0), other, dy)
+    assert rc == 0 and np.linalg.norm(to_host(dy)) > 1.0
+    _, rc = b.nk_sign_apply_device(lat.h, b.nk_sign_params_default(k=1, ell=1, mu=0.0, m_w=-1.0), dx, dy)
+    assert rc == b.NK_WARN_NOTCONV and "singular" in b.nk_last_error()
+    assert np.array_equal(to_host(dy), np.zeros(x.size))
+    lat.close()
+
+
 @pytest.mark.parametrize("mu", [0.3, 0.5])
 @pytest.mark.parametrize("ell", [0, 4])
 def test_two_sided_serious_breakdown(mu, ell):
